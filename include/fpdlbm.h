@@ -188,6 +188,11 @@ int fpd_init_fiber_line(fpd_sim *s, double cx, double cy, double theta);
  * step (2) runs as two kernels, the tiles away from the fiber on a second stream of the
  * library's own (non-blocking, default priority) while the bead kernel of the step before
  * finishes, and the tiles near it after that bead kernel; the results are the same bits.
+ * Passes: a lattice of about a million nodes or more (one fiber or none, no fixed profile,
+ * not FPD_FLAG_NO_SPLIT) advances four steps per pass over memory, the fluid away from the
+ * fiber in one kernel on that second stream, the nodes around the fiber step by step in two
+ * buffers of their size that the simulation holds besides its populations; the results are
+ * the same bits, and steps left over by a multiple of four are split or whole ones.
  * The simulation's stream waits for the second stream before fpd_step returns, so work
  * enqueued on it afterwards follows every step.  The first step after fpd_init_fiber or
  * fpd_load runs whole.  FPD_HEALTH_SUPPORT is raised if a bead outran the split's margin

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfpdlbm.so")
-SOURCES = ["fpd_kernels.hip", "fpd_runtime.hip"]
+SOURCES = ["fpd_kernels.hip", "fpd_march.hip", "fpd_runtime.hip"]
 ARCH = os.environ.get("FPD_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

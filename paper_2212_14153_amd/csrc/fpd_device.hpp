@@ -339,6 +339,56 @@ __device__ inline void pull(const typename Cd::store_t* __restrict__ src, int nx
     }
 }
 
+// Populations of a whole lattice or of a patch of it: value (k, y, x) at
+// (y - oy) * stride + k * plane + (x - ox), columns and rows modulo the lattice.
+struct View {
+    const void* p;
+    int ox, oy, stride;
+    long long plane;
+};
+
+// pull() from a view.  SCALED: values in the collision's units (as pull_group).
+template <class Cd, bool SCALED>
+__device__ inline void pull_view(const View& v, int nx, int ny, int x, int y, bool per,
+                                 typename Cd::T u6, typename Cd::T g[9]) {
+    using S = typename Cd::store_t;
+    const S* p = (const S*)v.p;
+    auto col = [&](int c) { c -= v.ox; return c < 0 ? c + nx : c; };
+    auto row = [&](int r) { r -= v.oy; return (long long)(r < 0 ? r + ny : r) * v.stride; };
+    auto at = [&](int k, long long r, int c) -> typename Cd::T {
+        const S* q = p + r + k * v.plane + c;
+        if constexpr (SCALED && sizeof(S) == 2)
+            return Cd::from_bits_scaled(*(const uint16_t*)q);
+        else
+            return Cd::load(q);
+    };
+    const int xc = col(x), xm = col(x == 0 ? nx - 1 : x - 1), xp = col(x == nx - 1 ? 0 : x + 1);
+    const long long r0 = row(y);
+    g[0] = at(0, r0, xc);
+    g[1] = at(1, r0, xm);
+    g[3] = at(3, r0, xp);
+    if (y > 0 || per) {
+        const long long rm = row(y > 0 ? y - 1 : ny - 1);
+        g[2] = at(2, rm, xc);
+        g[5] = at(5, rm, xm);
+        g[6] = at(6, rm, xp);
+    } else {
+        g[2] = at(4, r0, xc);
+        g[5] = at(7, r0, xc) - u6;
+        g[6] = at(8, r0, xc) + u6;
+    }
+    if (y < ny - 1 || per) {
+        const long long rp = row(y < ny - 1 ? y + 1 : 0);
+        g[4] = at(4, rp, xc);
+        g[7] = at(7, rp, xp);
+        g[8] = at(8, rp, xm);
+    } else {
+        g[4] = at(2, r0, xc);
+        g[7] = at(5, r0, xc) - u6;
+        g[8] = at(6, r0, xc) + u6;
+    }
+}
+
 // Two-byte storage: a lane updates G = nodes_per_lane consecutive nodes x0 .. x0 + G - 1
 // (x0 a multiple of G) of one row and moves populations as aligned G/2-dword vectors, so
 // every memory request carries 2 G bytes per lane.  A value left of x0, or right of the
@@ -594,8 +644,11 @@ __device__ inline void mrt_collide(T g[9], T Fx, T Fy, T s_nu, T s_q, T s_e, T s
 // the moments of h are S times those of g; rho and u come from the unscaled drho and j, the
 // equilibria and force terms enter scaled by S, and the result is S g*.  The same operator
 // as mrt_collide; the scale leaves the nine decodes and encodes of each node.
+// g*_0 comes as its last FMA's operands, g*_0 = 4 z + g[0] with z the return value: the
+// two-byte format narrows that FMA with a single rounding (narrow_fma4).
 template <typename T, bool kForce = true>
-__device__ inline void mrt_collide_scaled(T g[9], T Fx, T Fy, T s_nu, T s_q, T s_e, T s_eps) {
+__device__ inline T mrt_collide_scaled_open(T g[9], T Fx, T Fy, T s_nu, T s_q, T s_e,
+                                            T s_eps) {
     constexpr T S = T(16384), iS = T(1.0 / 16384.0);
     const T s14 = (g[1] + g[2]) + (g[3] + g[4]);
     const T s58 = (g[5] + g[6]) + (g[7] + g[8]);
@@ -651,7 +704,7 @@ __device__ inline void mrt_collide_scaled(T g[9], T Fx, T Fy, T s_nu, T s_q, T s
     const T axis = a - b - T(2) * c;
     const T diag = a + T(2) * b + c;
     const T de = d + e, fh = f + h;
-    g[0] = a - T(4) * b + T(4) * c;
+    g[0] = a - T(4) * b;
     g[1] = axis + (d - T(2) * e) + p;
     g[3] = axis - (d - T(2) * e) + p;
     g[2] = axis + (f - T(2) * h) - p;
@@ -660,6 +713,27 @@ __device__ inline void mrt_collide_scaled(T g[9], T Fx, T Fy, T s_nu, T s_q, T s
     g[6] = diag - de + fh - q;
     g[7] = diag - de - fh + q;
     g[8] = diag + de - fh - q;
+    return c;
+}
+
+template <typename T, bool kForce = true>
+__device__ inline void mrt_collide_scaled(T g[9], T Fx, T Fy, T s_nu, T s_q, T s_e, T s_eps) {
+    const T z = mrt_collide_scaled_open<T, kForce>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
+    g[0] = g[0] + T(4) * z;
+}
+
+// 4 z + t rounded once to binary16, in the low (resp. low and high) half of the result.
+// Written out because the compiler narrows this FMA with one rounding in some kernels and,
+// where it packs two conversions, with two; every kernel has to store the same bits.
+__device__ inline uint32_t narrow_fma4(float z, float t) {
+    uint32_t w;
+    asm("v_fma_mixlo_f16 %0, 4.0, %1, %2" : "=v"(w) : "v"(z), "v"(t));
+    return w;
+}
+__device__ inline uint32_t narrow_fma4(float z0, float t0, float z1, float t1) {
+    uint32_t w = narrow_fma4(z0, t0);
+    asm("v_fma_mixhi_f16 %0, 4.0, %1, %2" : "+v"(w) : "v"(z1), "v"(t1));
+    return w;
 }
 
 // Rest weights, for decoding g back to f.

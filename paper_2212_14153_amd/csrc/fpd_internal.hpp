@@ -74,6 +74,18 @@ constexpr int kPartMargin = 3;
 // and those inside it (kPartFiber: the fiber tiles and the step's bookkeeping).
 enum { kPartAll = 0, kPartFluid = 1, kPartFiber = 2 };
 
+// A pass advances the lattice by kPassSteps time steps: the fluid away from the fiber in one
+// kernel that reads and writes every node once (march_kernel), the nodes around the fiber
+// step by step (patch_kernel, bead_kernel).  The pass's partition is a support window grown
+// by kPassMargin nodes: a bead moves less than one node per step, so the window of the
+// step before the pass, grown by kPassSteps, holds the supports of all its steps; one node
+// more holds the ring the bead kernel pulls from, and one is slack.
+constexpr int kPassSteps = 4;
+constexpr int kPassMargin = kPassSteps + 2;
+// Partition columns start and end at multiples of this (a lane of the march holds that many
+// columns at most).
+constexpr int kPassAlign = 4;
+
 // Value (k, y, x) of a population buffer sits at y * stride + k * plane + x.  The nine
 // direction rows of one lattice row are adjacent (plane = nx padded to 64 elements, stride
 // = 9 * plane): the streams of a tile stay within a few hundred KB of each other.
@@ -164,6 +176,18 @@ struct NodeBox {
     bool wrap_x, wrap_y;
 };
 
+// One axis of a pass's partition at step t of the pass: the partition grown by the steps
+// that follow, since those pull from one node further out each.
+struct PatchArgs {
+    int t;                     // step of the pass, 1 .. kPassSteps
+    const int* part;           // the pass's partition: x0, width, y0, height
+    int* part_next;            // the next pass's (written at the last step)
+    const void* src;           // populations the step reads and writes: the lattice's
+    void* dst;                 //   buffers, or (step t > 1, resp. t < kPassSteps) the
+    int src_patch, dst_patch;  //   patch buffers, which hold the grown partition alone
+    int pitch;                 // nodes of a patch row
+};
+
 // Kernel launchers (fpd_kernels.hip).  Given events t0 and t1, the lattice and bead
 // launches stamp them with the dispatch's own start and end (hipExtLaunchKernel); they are
 // then not for stream capture.
@@ -177,6 +201,17 @@ hipError_t launch_step_part(int storage, const StepArgs& a, dim3 block, int rows
 hipError_t launch_bead(int storage, const StepArgs& a, int do_velocity, int win_out,
                        hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_forces(const StepArgs& a, hipStream_t st);
+// A pass: its partition from the current support window; step q.t of the nodes around the
+// fiber (patch_w x patch_h: the largest grown partition) and the step's bead kernel; and
+// the fluid outside the partition, kPassSteps steps at once (fpd_march.hip; part: the
+// partition, NULL for none).  march_ok: whether the march handles the lattice.
+hipError_t launch_pass_setup(const StepArgs& a, int* part, hipStream_t st);
+hipError_t launch_patch(int storage, const StepArgs& a, const PatchArgs& q, int patch_w,
+                        int patch_h, hipStream_t st);
+hipError_t launch_patch_bead(int storage, const StepArgs& a, const PatchArgs& q, int win_out,
+                             hipStream_t st);
+bool march_ok(int storage, const Lattice& L);
+hipError_t launch_march(int storage, const StepArgs& a, const int* part, hipStream_t st);
 // excluded-volume forces of the step's start into BeadState::Fev (before the lattice step;
 // needed only when BeadState::ev_k > 0)
 hipError_t launch_ev(const StepArgs& a, hipStream_t st);

@@ -388,7 +388,7 @@ __device__ inline int gather_beads(const Fiber& fib, int nx, int ny, bool per, i
             sB[i].C[1] = (T)C1;
             int ox, oy;
             sB[i].g.node(nx, ny, per, ox, oy);
-            if (ox >= cx0 && ox < cx0 + cw && oy >= ry0 && oy < ry0 + rh)
+            if (imod(ox - cx0, nx) < cw && (per ? imod(oy - ry0, ny) : oy - ry0) < rh && (per || oy >= ry0))
                 own_bead(fib, B, b, F, C0, C1);
         }
     }
@@ -841,6 +841,136 @@ __global__ void __launch_bounds__(256) fiber_kernel(StepArgs a) {
     tile_any<ST, SPT, BC, false, kPartFiber>(a, win, ty * a.tiles_x + tx, lds);
 }
 
+// ------------------------------------------------------- the fiber's part of a pass ----
+
+// A pass's partition and, for step t of it, the nodes that step updates: the partition
+// grown by the kPassSteps - t steps still to come.  The patch buffers hold the largest of
+// these (t = 1), from its first column and row on.
+struct PatchRect {
+    int x0, w, y0, h;
+};
+__device__ inline PatchRect patch_rect(const int* P, int t, int nx, int ny, bool per) {
+    PatchRect r;
+    const int m = kPassSteps - t;
+    grow_axis(P[0], P[1], m, nx, true, r.x0, r.w);
+    grow_axis(P[2], P[3], m, ny, per, r.y0, r.h);
+    return r;
+}
+
+__device__ inline View patch_view(const PatchArgs& q, const Lattice& L, const void* p,
+                                  bool patch, const PatchRect& first) {
+    if (!patch) return View{p, 0, 0, L.stride, L.plane};
+    return View{p, first.x0, first.y0, 9 * q.pitch, q.pitch};
+}
+
+// A support window grown into a pass's partition (columns to multiples of kPassAlign).
+__device__ inline void pass_partition(const Window& win, int nx, int ny, bool per, int* Q) {
+    const int ww = win.h > 0 ? win.w : 0;
+    grow_axis(win.x0, ww, kPassMargin, nx, true, Q[0], Q[1]);
+    grow_axis(win.y0, ww > 0 ? win.h : 0, kPassMargin, ny, per, Q[2], Q[3]);
+    if (Q[1] == 0 || Q[3] == 0) {
+        Q[0] = Q[1] = Q[2] = Q[3] = 0;
+        return;
+    }
+    const int lead = Q[0] % kPassAlign;
+    Q[0] -= lead;
+    Q[1] = (Q[1] + lead + kPassAlign - 1) / kPassAlign * kPassAlign;
+    if (Q[1] >= nx) {
+        Q[0] = 0;
+        Q[1] = nx;
+    }
+}
+
+__global__ void pass_setup_kernel(StepArgs a, int* part) {
+    if (threadIdx.x == 0)
+        pass_partition(tile_window(a), a.L.nx, a.L.ny, a.L.periodic != 0, part);
+}
+
+// Step q.t of a pass for the nodes around the fiber, one node per thread: the same
+// arithmetic per node as a fiber tile of step_kernel, read from and written to the lattice
+// or a patch buffer.  The grid covers the largest partition the reserved window allows;
+// block 0 also does the step's bookkeeping.
+constexpr int kPatchX = 64, kPatchY = 4;
+
+template <int ST, int BC, bool FR>
+__device__ inline void patch_tile(const StepArgs& a, const PatchArgs& q, const Window& win,
+                                  int bx, int by, TileLds& lds) {
+    using Cd = Codec<ST>;
+    using T = typename Cd::T;
+    using S = typename Cd::store_t;
+    constexpr bool kScaled = ST == FPD_F16DEV;
+    const bool per = periodic_of(BC, a);
+    const int nx = a.L.nx, ny = a.L.ny;
+    const PatchRect first = patch_rect(q.part, 1, nx, ny, per);
+    const PatchRect r = patch_rect(q.part, q.t, nx, ny, per);
+    const int cx = bx * kPatchX, cy = by * kPatchY;
+    if (cx >= r.w || cy >= r.h) return;  // block-uniform
+    const int cw = min(kPatchX, r.w - cx), ch = min(kPatchY, r.h - cy);
+    int x0 = r.x0 + cx, y0 = r.y0 + cy;
+    if (x0 >= nx) x0 -= nx;
+    if (per && y0 >= ny) y0 -= ny;
+    const int lx = threadIdx.x % kPatchX, ly = threadIdx.x / kPatchX;
+    const bool in = lx < cw && ly < ch;
+    int x = x0 + lx, y = y0 + ly;
+    if (x >= nx) x -= nx;
+    if (per && y >= ny) y -= ny;
+    const T u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
+    T g[9];
+    if (in)
+        pull_view<Cd, true>(patch_view(q, a.L, q.src, q.src_patch != 0, first), nx, ny, x, y, per,
+                            u6, g);
+    TileBead<T>* sB = (TileBead<T>*)lds.beads;
+    const int nb = gather_beads<T>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
+                                   lds.bonds, FR);
+    if (!in) return;
+    T Fx = (T)a.gx, Fy = (T)a.gy, s_nu = (T)a.s_nu_f, s_q = (T)a.s_q_f;
+    const T s_e = (T)a.s_e, s_eps = (T)a.s_eps;
+    if (nb > 0)
+        fiber_node<T>(a, per, sB, nb, x, y, win.x0, win.y0, win.w, win.h, Fx, Fy, s_nu, s_q);
+    const View v = patch_view(q, a.L, q.dst, q.dst_patch != 0, first);
+    int c = x - v.ox, w = y - v.oy;
+    if (c < 0) c += nx;
+    if (w < 0) w += ny;
+    S* o = (S*)v.p + (long long)w * v.stride + c;
+    // one collision for every node: with F = 0 it gives the bits of the unforced one
+    if constexpr (kScaled) {
+        const T z = mrt_collide_scaled_open<T>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
+        *(uint16_t*)o = (uint16_t)narrow_fma4(z, g[0]);
+    } else {
+        mrt_collide<T>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
+    }
+#pragma unroll
+    for (int k = kScaled ? 1 : 0; k < 9; ++k) {
+        if constexpr (sizeof(S) == 2)
+            ((uint16_t*)o)[k * v.plane] = (uint16_t)Cd::pack2_scaled(g[k], g[k]);
+        else
+            o[k * v.plane] = g[k];
+    }
+}
+
+// The bookkeeping of step q.t (every thread of one block): that of any step, the check
+// that the partition held the window and what the rest of the pass reads around it, and at
+// the last step the next pass's partition.
+__device__ inline void patch_duties(const StepArgs& a, const PatchArgs& q, const Window& win) {
+    step_duties(a, win, false);
+    if (threadIdx.x != 0) return;
+    const int nx = a.L.nx, ny = a.L.ny;
+    const bool per = a.L.periodic != 0;
+    const int ww = win.h > 0 ? win.w : 0, m = max(kPassSteps - q.t, 1);
+    if (!axis_inside(win.x0, ww, m, q.part[0], q.part[1], nx, true) ||
+        !axis_inside(win.y0, ww > 0 ? win.h : 0, m, q.part[2], q.part[3], ny, per))
+        atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
+    if (q.t == kPassSteps) pass_partition(win, nx, ny, per, q.part_next);
+}
+
+template <int ST, int BC>
+__global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, PatchArgs q) {
+    __shared__ TileLds lds;
+    const Window win = tile_window(a);
+    if (blockIdx.x == 0 && blockIdx.y == 0) patch_duties(a, q, win);
+    patch_tile<ST, BC, false>(a, q, win, blockIdx.x, blockIdx.y, lds);
+}
+
 // The argument table is read-only while a batch kernel runs: viewing it in the constant
 // address space lets the per-simulation arguments come in through scalar loads.
 typedef const StepArgs __attribute__((address_space(4))) ConstStepArgs;
@@ -931,9 +1061,10 @@ __device__ inline void publish_support(const Fiber& fib, int win_out, double Rx,
 // only on the cutoff test, so phi is evaluated while they are in flight.  The sums run
 // over kBeadLanes virtual lanes (NT threads of R = kBeadLanes / NT lanes each): lane v
 // takes nodes t = v, v + kBeadLanes, ... in increasing t, whatever VB and NT.
-template <int ST, int VB, int NT>
+// PATCH: the step's populations are read from the view `pv` (a step of a pass).
+template <int ST, int VB, int NT, bool PATCH = false>
 __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int win_out,
-                                  double* scratch, double* s_R) {
+                                  double* scratch, double* s_R, const View& pv = View{}) {
     constexpr int R = kBeadLanes / NT;
     using Cd = Codec<ST>;
     using T = typename Cd::T;
@@ -983,8 +1114,11 @@ __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int
                     fw[u][0] = (T)a.gx;  // outside the window f^n is the body force alone
                     fw[u][1] = (T)a.gy;
                     if (in[u]) {
-                        pull<Cd>(cur, nx, ny, a.L.stride, a.L.plane, ii[u], jj[u], per,
-                                 (T)a.u6, g[u]);
+                        if constexpr (PATCH)
+                            pull_view<Cd, false>(pv, nx, ny, ii[u], jj[u], per, (T)a.u6, g[u]);
+                        else
+                            pull<Cd>(cur, nx, ny, a.L.stride, a.L.plane, ii[u], jj[u], per,
+                                     (T)a.u6, g[u]);
                         // f^n at this node from the window the lattice kernel filled (the
                         // window covers every support box unless it was clamped, which
                         // raises FPD_HEALTH_SUPPORT)
@@ -1083,6 +1217,22 @@ __global__ void __launch_bounds__(kBeadBlock) bead_kernel(StepArgs a, int do_vel
     __shared__ double s_R[2];
     bead_block<ST, kBeadVelBatch, kBeadBlock>(a, blockIdx.x, do_velocity, win_out, scratch,
                                               s_R);
+}
+
+// The bead kernel of a step of a pass.  It runs beside the march, whose waves hold most of
+// the registers: in FP64 a block of a wave per SIMD still fits where the usual two do not
+// (the sums are over the same virtual lanes in the same order).
+template <int ST> constexpr int kPatchBeadBlock = ST == FPD_F64 ? 256 : kBeadBlock;
+
+template <int ST>
+__global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArgs a, PatchArgs q,
+                                                                         int win_out) {
+    __shared__ double scratch[2 * (kBeadLanes / 64)];
+    __shared__ double s_R[2];
+    const PatchRect first = patch_rect(q.part, 1, a.L.nx, a.L.ny, a.L.periodic != 0);
+    bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
+        a, blockIdx.x, 1, win_out, scratch, s_R,
+        patch_view(q, a.L, q.dst, q.dst_patch != 0, first));
 }
 
 // Bead kernel over a batch: one block per (simulation, bead) item.
@@ -1624,6 +1774,42 @@ hipError_t launch_bead(int storage, const StepArgs& a, int do_velocity, int win_
         default: return hipErrorInvalidValue;
     }
     return launch_k(k, dim3(a.fib.n), dim3(kBeadBlock), st, t0, t1, a, do_velocity, win_out);
+}
+
+hipError_t launch_pass_setup(const StepArgs& a, int* part, hipStream_t st) {
+    hipLaunchKernelGGL(pass_setup_kernel, dim3(1), dim3(64), 0, st, a, part);
+    return hipGetLastError();
+}
+
+hipError_t launch_patch(int storage, const StepArgs& a, const PatchArgs& q, int patch_w,
+                        int patch_h, hipStream_t st) {
+    const dim3 grid((patch_w + kPatchX - 1) / kPatchX, (patch_h + kPatchY - 1) / kPatchY);
+    const dim3 block(kPatchX * kPatchY);
+    const bool per = a.L.periodic != 0;
+    void (*k)(StepArgs, PatchArgs) = nullptr;
+    switch (storage) {
+        case FPD_F64: k = per ? patch_kernel<FPD_F64, kPeriodic> : patch_kernel<FPD_F64, kWalls>; break;
+        case FPD_F32: k = per ? patch_kernel<FPD_F32, kPeriodic> : patch_kernel<FPD_F32, kWalls>; break;
+        case FPD_F16DEV: k = per ? patch_kernel<FPD_F16DEV, kPeriodic> : patch_kernel<FPD_F16DEV, kWalls>; break;
+        case FPD_BF16DEV: k = per ? patch_kernel<FPD_BF16DEV, kPeriodic> : patch_kernel<FPD_BF16DEV, kWalls>; break;
+        default: return hipErrorInvalidValue;
+    }
+    return launch_k(k, grid, block, st, nullptr, nullptr, a, q);
+}
+
+hipError_t launch_patch_bead(int storage, const StepArgs& a, const PatchArgs& q, int win_out,
+                             hipStream_t st) {
+    if (a.fib.n <= 0) return hipSuccess;
+    void (*k)(StepArgs, PatchArgs, int) = nullptr;
+    switch (storage) {
+        case FPD_F64: k = patch_bead_kernel<FPD_F64>; break;
+        case FPD_F32: k = patch_bead_kernel<FPD_F32>; break;
+        case FPD_F16DEV: k = patch_bead_kernel<FPD_F16DEV>; break;
+        case FPD_BF16DEV: k = patch_bead_kernel<FPD_BF16DEV>; break;
+        default: return hipErrorInvalidValue;
+    }
+    const int threads = storage == FPD_F64 ? kPatchBeadBlock<FPD_F64> : kPatchBeadBlock<FPD_F32>;
+    return launch_k(k, dim3(a.fib.n), dim3(threads), st, nullptr, nullptr, a, q, win_out);
 }
 
 // Forces F^n, F/A and bond strains of every simulation of a batch, one block per

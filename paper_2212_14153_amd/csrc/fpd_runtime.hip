@@ -122,6 +122,7 @@ struct fpd_sim {
     void* buf[2] = {nullptr, nullptr};
     bool own_bufs = true;
     int cur = 0;                 // buffer holding the post-collision state of the last step
+    int wpar = 0;                // support window slot of the current bead state
     hipStream_t stream = nullptr;
     bool own_stream = false;
     BeadState* bs = nullptr;
@@ -134,13 +135,18 @@ struct fpd_sim {
     bool fiber = false;
     int64_t steps = 0;
     fpd_launch launch{};
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t graph[4] = {};  // by (cur, wpar)
     int graph_chunk = 0;
+    // passes: two buffers for the steps of the nodes around the fiber (nullptr: no passes)
+    // of patch_w x patch_h nodes, and the partitions of the passes from either buffer
+    void* patch[2] = {nullptr, nullptr};
+    int* pass_part = nullptr;    // [2][4]
+    int patch_w = 0, patch_h = 0, patch_pitch = 0;
     // split steps: the fluid kernels on a side stream, the fiber and bead kernels on
     // `stream`, ordered by the two events (created with the first split step)
     hipStream_t side = nullptr;
     hipEvent_t ev_fluid = nullptr, ev_fiber = nullptr;
-    bool part_valid = false;     // BeadState::part[cur] was written by the step before
+    bool part_valid = false;     // BeadState::part[wpar] was written by the step before
     // kernel timing
     std::vector<hipEvent_t> events;
     double ms_lat = 0.0, ms_bead = 0.0;
@@ -149,9 +155,10 @@ struct fpd_sim {
 
 namespace {
 
-StepArgs make_args(const fpd_sim* s, int src_idx) {
+// The step from buffer src_idx whose support window is slot wpar.
+StepArgs make_args(const fpd_sim* s, int src_idx, int wpar) {
     StepArgs a{};
-    a.parity = src_idx;
+    a.parity = wpar;
     a.src = s->buf[src_idx];
     a.dst = s->buf[1 - src_idx];
     a.L = s->L;
@@ -277,7 +284,7 @@ bool has_ev(const fpd_sim* s) {
 bool use_split(const fpd_sim* s) {
     if (!s->fiber || s->p.n_beads <= 0 || s->row_phi) return false;
     if (s->p.flags & FPD_FLAG_NO_SPLIT) return false;
-    const StepArgs a = make_args(s, s->cur);
+    const StepArgs a = make_args(s, s->cur, s->wpar);
     return 4LL * a.part_gw * a.part_gh <= (long long)a.n_tiles;
 }
 
@@ -311,8 +318,8 @@ int ensure_split(fpd_sim* s) {
 // step n - 1, whose positions it needs; the bead kernel of step n reads only tiles of the
 // partition, which the fiber kernel wrote.  first: the start of a run (split_steps), whose
 // stream is already after every earlier kernel.
-int enqueue_split_step(fpd_sim* s, int from, bool first) {
-    const StepArgs a = make_args(s, from);
+int enqueue_split_step(fpd_sim* s, int from, int wpar, bool first) {
+    const StepArgs a = make_args(s, from, wpar);
     const dim3 block(s->launch.block_x, s->launch.block_y);
     const int rpt = s->launch.rows_per_thread;
     HIP_TRY(hipStreamWaitEvent(s->side, s->ev_fiber, 0));
@@ -323,54 +330,126 @@ int enqueue_split_step(fpd_sim* s, int from, bool first) {
     if (has_ev(s)) HIP_TRY(launch_ev(a, s->stream));
     HIP_TRY(launch_step_part(s->p.storage, a, block, rpt, kPartFiber, s->stream));
     HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
-    HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - from, s->stream));
+    HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - wpar, s->stream));
     return FPD_OK;
 }
 
 // n split steps from buffer `from`, then `stream` waits for the side stream's last kernel,
 // so work enqueued on `stream` afterwards follows all of them (also inside a capture, where
 // this joins the side stream back).
-int split_steps(fpd_sim* s, int from, int64_t n) {
+int split_steps(fpd_sim* s, int from, int wpar, int64_t n) {
     HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
-    int b = from;
     for (int64_t i = 0; i < n; ++i) {
-        int rc = enqueue_split_step(s, b, i == 0);
+        int rc = enqueue_split_step(s, from, wpar, i == 0);
         if (rc) return rc;
-        b = 1 - b;
+        from = 1 - from;
+        wpar = 1 - wpar;
     }
     HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
     return FPD_OK;
 }
 
 // One step from buffer `from` (launches only).
-int enqueue_step(fpd_sim* s, int from) {
-    const StepArgs a = make_args(s, from);
+int enqueue_step(fpd_sim* s, int from, int wpar) {
+    const StepArgs a = make_args(s, from, wpar);
     const dim3 block(s->launch.block_x, s->launch.block_y);
     HIP_TRY(launch_record(a, s->stream));
     if (has_ev(s)) HIP_TRY(launch_ev(a, s->stream));
     HIP_TRY(launch_step(s->p.storage, a, block, s->launch.rows_per_thread, s->stream));
-    if (a.fib.n > 0) HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - from, s->stream));
+    if (a.fib.n > 0) HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - wpar, s->stream));
     return FPD_OK;
 }
 
-int build_graph(fpd_sim* s, int from, int chunk, hipGraphExec_t* out) {
+// Whether fpd_step advances kPassSteps steps per pass over the lattice (march_kernel beside
+// the patch and bead kernels): not with a fixed profile or FPD_FLAG_NO_SPLIT, and only
+// where the simulation has the patch buffers.
+bool use_passes(const fpd_sim* s) {
+    if (s->row_phi || (s->p.flags & FPD_FLAG_NO_SPLIT)) return false;
+    if (!s->pass_part || (s->p.n_beads > 0 && (!s->fiber || !s->patch[0]))) return false;
+    return true;
+}
+
+// One pass from buffer `from`: the fluid kernel on the side stream, the steps of the nodes
+// around the fiber on `stream`.  The fluid kernel reads what the pass before wrote and
+// overwrites the buffer that pass read, so it waits for that pass's last patch kernel
+// (ev_fiber; its fluid kernel is before it on the side stream); the first patch kernel
+// waits for the fluid kernel of the pass before (ev_fluid).  first: the start of a run,
+// whose stream is already after every earlier kernel.
+int enqueue_pass(fpd_sim* s, int from, int wpar, bool first) {
+    StepArgs a = make_args(s, from, wpar);
+    if (a.fib.n <= 0) {
+        HIP_TRY(launch_march(s->p.storage, a, nullptr, s->stream));
+        return FPD_OK;
+    }
+    const int* part = s->pass_part + 4 * from;
+    HIP_TRY(hipStreamWaitEvent(s->side, s->ev_fiber, 0));
+    HIP_TRY(launch_march(s->p.storage, a, part, s->side));
+    if (!first) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
+    HIP_TRY(hipEventRecord(s->ev_fluid, s->side));
+    for (int t = 1; t <= kPassSteps; ++t) {
+        PatchArgs q{};
+        q.t = t;
+        q.part = part;
+        q.part_next = s->pass_part + 4 * (1 - from);
+        q.src_patch = t > 1;
+        q.dst_patch = t < kPassSteps;
+        q.src = t > 1 ? s->patch[t & 1] : s->buf[from];
+        q.dst = t < kPassSteps ? s->patch[(t + 1) & 1] : s->buf[1 - from];
+        q.pitch = s->patch_pitch;
+        a.parity = wpar;
+        HIP_TRY(launch_record(a, s->stream));
+        if (has_ev(s)) HIP_TRY(launch_ev(a, s->stream));
+        HIP_TRY(launch_patch(s->p.storage, a, q, s->patch_w, s->patch_h, s->stream));
+        if (t == kPassSteps) HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
+        HIP_TRY(launch_patch_bead(s->p.storage, a, q, 1 - wpar, s->stream));
+        wpar = 1 - wpar;
+    }
+    return FPD_OK;
+}
+
+// n steps from buffer `from` and window slot `wpar` (launches only; ensure_split first):
+// passes while they last, then single steps.
+int enqueue_steps(fpd_sim* s, int from, int wpar, int64_t n) {
+    if (use_passes(s) && n >= kPassSteps) {
+        const bool fib = s->fiber && s->p.n_beads > 0;
+        if (fib) {
+            HIP_TRY(launch_pass_setup(make_args(s, from, wpar), s->pass_part + 4 * from,
+                                      s->stream));
+            HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
+        }
+        for (bool first = true; n >= kPassSteps; n -= kPassSteps, first = false) {
+            int rc = enqueue_pass(s, from, wpar, first);
+            if (rc) return rc;
+            from = 1 - from;
+            wpar ^= kPassSteps & 1;
+        }
+        if (fib) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
+    }
+    if (n > 0 && use_split(s)) return split_steps(s, from, wpar, n);
+    for (; n > 0; --n) {
+        int rc = enqueue_step(s, from, wpar);
+        if (rc) return rc;
+        from = 1 - from;
+        wpar = 1 - wpar;
+    }
+    return FPD_OK;
+}
+
+// The state after the n steps of enqueue_steps.
+void advance_state(fpd_sim* s, int64_t n) {
+    const int64_t passes = use_passes(s) ? n / kPassSteps : 0;
+    if ((passes + n - passes * kPassSteps) & 1) s->cur = 1 - s->cur;
+    if (n & 1) s->wpar = 1 - s->wpar;
+}
+
+int build_graph(fpd_sim* s, int from, int wpar, int chunk, hipGraphExec_t* out) {
     hipGraph_t g = nullptr;
-    const bool split = use_split(s);
-    if (split) {
+    if (use_split(s) || use_passes(s)) {
         int rs = ensure_split(s);
         if (rs) return rs;
     }
     HIP_TRY(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-    int rc = FPD_OK;
-    if (split) {
-        rc = split_steps(s, from, chunk);
-    } else {
-        int b = from;
-        for (int i = 0; i < chunk && rc == FPD_OK; ++i) {
-            rc = enqueue_step(s, b);
-            b = 1 - b;
-        }
-    }
+    const int rc = enqueue_steps(s, from, wpar, chunk);
     hipError_t e = hipStreamEndCapture(s->stream, &g);
     if (rc != FPD_OK) {
         if (g) (void)hipGraphDestroy(g);
@@ -386,6 +465,12 @@ int build_graph(fpd_sim* s, int from, int chunk, hipGraphExec_t* out) {
     return FPD_OK;
 }
 
+// The state after one step.
+void flip(fpd_sim* s) {
+    s->cur = 1 - s->cur;
+    s->wpar = 1 - s->wpar;
+}
+
 // Steps launched one by one, the lattice and bead kernels each stamped with the start and
 // end of their own dispatch (durations summed into ms_lat and ms_bead).  Split steps (the
 // order of enqueue_split_step) stamp the fluid and the fiber kernel; their lattice pass
@@ -397,9 +482,9 @@ int step_timed(fpd_sim* s, int64_t n) {
         int rc = ensure_split(s);
         if (rc) return rc;
         if (!s->part_valid && n > 0) {  // the first split step's partition (untimed)
-            rc = enqueue_step(s, s->cur);
+            rc = enqueue_step(s, s->cur, s->wpar);
             if (rc) return rc;
-            s->cur = 1 - s->cur;
+            flip(s);
             s->part_valid = true;
             --n;
         }
@@ -417,7 +502,7 @@ int step_timed(fpd_sim* s, int64_t n) {
         }
         if (split) HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
         for (int64_t i = 0; i < batch; ++i) {
-            const StepArgs a = make_args(s, s->cur);
+            const StepArgs a = make_args(s, s->cur, s->wpar);
             hipEvent_t* ev = &s->events[(size_t)i * per];
             if (split) {
                 HIP_TRY(hipStreamWaitEvent(s->side, s->ev_fiber, 0));
@@ -432,14 +517,14 @@ int step_timed(fpd_sim* s, int64_t n) {
                 HIP_TRY(launch_step_part(s->p.storage, a, block, rpt, kPartFiber, s->stream,
                                          ev[2], ev[3]));
                 HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
-                HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - s->cur, s->stream, ev[4], ev[5]));
+                HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - s->wpar, s->stream, ev[4], ev[5]));
             } else {
                 HIP_TRY(launch_step(s->p.storage, a, block, rpt, s->stream, ev[0], ev[1]));
                 if (fib)
-                    HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - s->cur, s->stream, ev[2],
+                    HIP_TRY(launch_bead(s->p.storage, a, 1, 1 - s->wpar, s->stream, ev[2],
                                         ev[3]));
             }
-            s->cur = 1 - s->cur;
+            flip(s);
         }
         if (split) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
         HIP_TRY(hipStreamSynchronize(s->stream));
@@ -469,8 +554,8 @@ int step_timed(fpd_sim* s, int64_t n) {
 }
 
 int fiber_init_device(fpd_sim* s) {
-    const StepArgs a = make_args(s, s->cur);
-    HIP_TRY(launch_bead(s->p.storage, a, 0, s->cur, s->stream));
+    const StepArgs a = make_args(s, s->cur, s->wpar);
+    HIP_TRY(launch_bead(s->p.storage, a, 0, s->wpar, s->stream));
     return FPD_OK;
 }
 
@@ -505,6 +590,44 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
            a.f_ext[0] == b.f_ext[0] && a.f_ext[1] == b.f_ext[1] &&
            a.g_body[0] == b.g_body[0] && a.g_body[1] == b.g_body[1] && a.ev_k == b.ev_k &&
            a.ev_range == b.ev_range;
+}
+
+// Passes pay from about a million nodes on: below, a step is the latency of its kernels, and
+// the patch and bead kernels one after the other take longer than a whole step's two
+// (1024 x 256, float32: 20.9 against 16.5 us per step; 777 x 333: 19.3 against 17.4), while at
+// 2042 x 611 in float16 deviations passes gain (25.3 against 28.4).
+constexpr long long kMinPassNodes = 1LL << 20;
+
+// The patch buffers of the passes, where a lattice takes them: the march handles it, one
+// fiber at most, and the largest grown partition spans at most half the lattice.  A
+// simulation whose buffers cannot be allocated runs without passes.  Allocated with the
+// simulation, so that a step never allocates.
+void alloc_passes(fpd_sim* s) {
+    const fpd_params& p = s->p;
+    if (!march_ok(p.storage, s->L) || chains_of(&p) > 1) return;
+    if ((long long)p.nx * p.ny < kMinPassNodes) return;
+    void* part = nullptr;
+    if (p.n_beads > 0) {
+        const int grow = 2 * (kPassMargin + kPassSteps - 1);
+        s->patch_w = std::min(p.nx, s->rect_wmax + grow + 2 * kPassAlign);
+        s->patch_h = std::min(p.ny, s->rect_hmax + grow);
+        if (2LL * s->patch_w * s->patch_h > (long long)p.nx * p.ny) return;
+        s->patch_pitch = (s->patch_w + 15) / 16 * 16;
+        const size_t bytes = (size_t)9 * s->patch_pitch * s->patch_h * s->elem;
+        for (auto& b : s->patch)
+            if (hipMalloc(&b, bytes) != hipSuccess) b = nullptr;
+    }
+    if (hipMalloc(&part, sizeof(int) * 8) != hipSuccess) part = nullptr;
+    if (!part || (p.n_beads > 0 && (!s->patch[0] || !s->patch[1]))) {
+        (void)hipGetLastError();
+        for (auto& b : s->patch) {
+            if (b) (void)hipFree(b);
+            b = nullptr;
+        }
+        if (part) (void)hipFree(part);
+        return;
+    }
+    s->pass_part = (int*)part;
 }
 
 int create_impl(const fpd_params* p, void* stream, void* fa, void* fb, size_t bytes_each,
@@ -639,7 +762,9 @@ size_t fpd_population_bytes(const fpd_params* p) {
 
 int fpd_create(const fpd_params* p, void* hip_stream, fpd_sim** out) {
     TraceRange range("fpd_create");
-    return create_impl(p, hip_stream, nullptr, nullptr, 0, out);
+    const int rc = create_impl(p, hip_stream, nullptr, nullptr, 0, out);
+    if (rc == FPD_OK) alloc_passes(*out);
+    return rc;
 }
 
 int fpd_create_with_buffers(const fpd_params* p, void* hip_stream, void* f_a, void* f_b,
@@ -648,7 +773,9 @@ int fpd_create_with_buffers(const fpd_params* p, void* hip_stream, void* f_a, vo
     if (!f_a || !f_b) return fail(FPD_EINVAL, "buffers must not be NULL");
     if (((uintptr_t)f_a | (uintptr_t)f_b) & 15)
         return fail(FPD_EINVAL, "buffers must be 16-byte aligned");
-    return create_impl(p, hip_stream, f_a, f_b, bytes_each, out);
+    const int rc = create_impl(p, hip_stream, f_a, f_b, bytes_each, out);
+    if (rc == FPD_OK) alloc_passes(*out);
+    return rc;
 }
 
 void fpd_destroy(fpd_sim* s) {
@@ -665,6 +792,9 @@ void fpd_destroy(fpd_sim* s) {
             if (b) (void)hipFree(b);
     if (s->bs) (void)hipFree(s->bs);
     if (s->rect_f) (void)hipFree(s->rect_f);
+    for (auto& b : s->patch)
+        if (b) (void)hipFree(b);
+    if (s->pass_part) (void)hipFree(s->pass_part);
     if (s->row_phi) (void)hipFree(s->row_phi);
     if (s->rec) (void)hipFree(s->rec);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -751,9 +881,9 @@ int fpd_init_fiber_line(fpd_sim* s, double cx, double cy, double theta) {
 
 namespace {
 
-// Whether n steps from buffer `from` replay graphs, and the graph they replay captured
-// (nothing runs).
-int ensure_graph(fpd_sim* s, int from, int64_t n, bool* replay) {
+// Whether n steps from the current state replay graphs, and the graph that replays the
+// first of them (after `skip` single steps) captured (nothing runs).
+int ensure_graph(fpd_sim* s, int from, int wpar, int64_t n, bool* replay) {
     const int chunk = s->launch.graph_chunk;
     *replay = !(s->p.flags & (FPD_FLAG_NO_GRAPH | FPD_FLAG_TIME_KERNELS)) && chunk >= 2 &&
               n >= chunk;
@@ -762,8 +892,16 @@ int ensure_graph(fpd_sim* s, int from, int64_t n, bool* replay) {
         drop_graphs(s);
         s->graph_chunk = chunk;
     }
-    if (!s->graph[from]) return build_graph(s, from, chunk, &s->graph[from]);
+    hipGraphExec_t& g = s->graph[2 * from + wpar];
+    if (!g) return build_graph(s, from, wpar, chunk, &g);
     return FPD_OK;
+}
+
+// Whether the next n steps start with a whole step, which gives the first split step its
+// partition (passes find their own).
+bool whole_first(const fpd_sim* s, int64_t n) {
+    const bool pass = use_passes(s) && n >= kPassSteps && s->launch.graph_chunk >= kPassSteps;
+    return n > 0 && use_split(s) && !s->part_valid && !pass;
 }
 
 }  // namespace
@@ -777,9 +915,17 @@ int fpd_capture(fpd_sim* s, int64_t n) {
     if (s->p.n_beads > 0 && !s->fiber)
         return fail(FPD_ESTATE, "fpd_init_fiber must come before fpd_capture");
     bool replay = false;
-    if (use_split(s) && !s->part_valid && n > 0)  // fpd_step runs one whole step first
-        return ensure_graph(s, 1 - s->cur, n - 1, &replay);
-    return ensure_graph(s, s->cur, n, &replay);
+    const int64_t w = whole_first(s, n) ? 1 : 0;
+    int from = s->cur ^ (int)w, wpar = s->wpar ^ (int)w;
+    int rc = ensure_graph(s, from, wpar, n - w, &replay);
+    if (rc || !replay || n - w < 2 * (int64_t)s->launch.graph_chunk) return rc;
+    // a chunk of an odd number of passes and single steps ends in the other buffer
+    const int cur = s->cur;
+    s->cur = from;
+    advance_state(s, s->launch.graph_chunk);
+    from = s->cur;
+    s->cur = cur;
+    return ensure_graph(s, from, wpar, n - w, &replay);
 }
 
 int fpd_step(fpd_sim* s, int64_t n) {
@@ -797,39 +943,29 @@ int fpd_step(fpd_sim* s, int64_t n) {
         return FPD_OK;
     }
     int64_t left = n;
-    const bool split = use_split(s);
-    if (split) {
+    if (use_split(s) || use_passes(s)) {
         int rc = ensure_split(s);
         if (rc) return rc;
-        if (!s->part_valid) {  // the first split step's partition comes from a whole step
-            rc = enqueue_step(s, s->cur);
-            if (rc) return rc;
-            s->cur = 1 - s->cur;
-            s->part_valid = true;
-            --left;
-        }
+    }
+    if (whole_first(s, left)) {
+        int rc = enqueue_step(s, s->cur, s->wpar);
+        if (rc) return rc;
+        flip(s);
+        --left;
     }
     const int chunk = s->launch.graph_chunk;
-    bool replay = false;
-    int rg = ensure_graph(s, s->cur, left, &replay);
-    if (rg) return rg;
-    if (replay) {
-        while (left >= chunk) {
-            HIP_TRY(hipGraphLaunch(s->graph[s->cur], s->stream));
-            left -= chunk;  // chunk is even: the state returns to the same buffer
-        }
+    for (;;) {
+        bool replay = false;
+        int rg = ensure_graph(s, s->cur, s->wpar, left, &replay);
+        if (rg) return rg;
+        if (!replay) break;
+        HIP_TRY(hipGraphLaunch(s->graph[2 * s->cur + s->wpar], s->stream));
+        advance_state(s, chunk);
+        left -= chunk;
     }
-    if (left > 0 && split) {
-        int rc = split_steps(s, s->cur, left);
-        if (rc) return rc;
-        if (left & 1) s->cur = 1 - s->cur;
-        left = 0;
-    }
-    for (; left > 0; --left) {
-        int rc = enqueue_step(s, s->cur);
-        if (rc) return rc;
-        s->cur = 1 - s->cur;
-    }
+    int rc = enqueue_steps(s, s->cur, s->wpar, left);
+    if (rc) return rc;
+    advance_state(s, left);
     s->steps += n;
     s->part_valid = true;
     return FPD_OK;
@@ -885,7 +1021,7 @@ int fpd_read_fields(fpd_sim* s, double* rho, double* ux, double* uy, double* eta
     const size_t S = (size_t)s->p.nx * s->p.ny;
     double* d = nullptr;
     HIP_TRY(hipMalloc(&d, 4 * S * sizeof(double)));
-    const StepArgs a = make_args(s, s->cur);
+    const StepArgs a = make_args(s, s->cur, s->wpar);
     hipError_t e = launch_forces(a, s->stream);  // C = F / A of the current bead state
     if (e == hipSuccess)
         e = launch_fields(s->p.storage, a, d, d + S, d + 2 * S, d + 3 * S, s->stream);
@@ -1038,7 +1174,7 @@ int fpd_particle_stats(fpd_sim* s, int32_t bead, double* out) {
     double* d = nullptr;
     const size_t n = (size_t)B.cw * (size_t)B.ch;
     HIP_TRY(hipMalloc(&d, (4 * n + 8) * sizeof(double)));
-    const StepArgs a = make_args(s, s->cur);
+    const StepArgs a = make_args(s, s->cur, s->wpar);
     hipError_t e = launch_forces(a, s->stream);  // C = F / A of the current bead state
     if (e == hipSuccess)
         e = launch_particle_stats(s->p.storage, a, bead, B, d, d + 4 * n, s->stream);
@@ -1084,7 +1220,7 @@ int fpd_read_beads(fpd_sim* s, double* R, double* V, double* F) {
     if (!s) return fail(FPD_EINVAL, "NULL simulation");
     const int N = s->p.n_beads;
     if (N == 0) return FPD_OK;
-    HIP_TRY(launch_forces(make_args(s, s->cur), s->stream));  // F^n of the current positions
+    HIP_TRY(launch_forces(make_args(s, s->cur, s->wpar), s->stream));  // F^n of the current positions
     int rc = sync_check(s);
     if (rc) return rc;
     std::vector<double> h(2 * (size_t)kMaxBeads * 3);
@@ -1227,7 +1363,7 @@ int fpd_save(fpd_sim* s, const char* path) {
     FILE* fp = fopen(path, "wb");
     if (!fp) return fail(FPD_EINVAL, "cannot open %s for writing", path);
     const uint8_t fib = s->fiber ? 1 : 0;
-    const uint8_t par = (uint8_t)s->cur;  // the bead state's window slot follows the parity
+    const uint8_t par = (uint8_t)s->wpar;  // the bead state's window slot
     bool ok = fwrite(kMagic, 1, 8, fp) == 8 && fwrite(&s->p, sizeof s->p, 1, fp) == 1 &&
               fwrite(&s->steps, sizeof s->steps, 1, fp) == 1 && fwrite(&fib, 1, 1, fp) == 1 &&
               fwrite(&par, 1, 1, fp) == 1 &&
@@ -1266,7 +1402,7 @@ int fpd_load(fpd_sim* s, const char* path) {
     if (!ok) return fail(FPD_EINVAL, "%s is truncated", path);
     drop_graphs(s);
     s->part_valid = false;
-    s->cur = par;
+    s->cur = s->wpar = par;
     HIP_TRY(hipMemcpy(s->buf[s->cur], pops.data(), bytes, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->bs, &h, sizeof h, hipMemcpyHostToDevice));
     s->steps = steps;
@@ -1364,8 +1500,8 @@ int batch_rebuild(fpd_batch* b) {
         BatchEntry& e = b->entries[i];
         if (e.status != FPD_SIM_ACTIVE || e.remaining <= 0) continue;
         fpd_sim* s = e.sim;
-        b->h_args[2 * r] = make_args(s, s->cur);
-        b->h_args[2 * r + 1] = make_args(s, 1 - s->cur);
+        b->h_args[2 * r] = make_args(s, s->cur, s->wpar);
+        b->h_args[2 * r + 1] = make_args(s, 1 - s->cur, 1 - s->wpar);
         tiles += b->h_args[2 * r].n_tiles;
         beads += b->h_args[2 * r].fib.n;
         b->h_tile_off[r + 1] = tiles;
@@ -1655,7 +1791,7 @@ int fpd_batch_wait(fpd_batch* b) {
         BatchEntry& e = b->entries[b->table[r]];
         e.remaining -= steps;
         e.sim->steps += steps;
-        if (steps & 1) e.sim->cur ^= 1;
+        if (steps & 1) flip(e.sim);
         if (b->h_health[r]) {
             e.status = FPD_SIM_FAILED;
         } else if (e.remaining == 0) {
@@ -1898,12 +2034,12 @@ int fpd_run_static(const fpd_params* p, void* hip_stream, void* f_a, void* f_b,
         const double ev_d = p->ev_range > 0.0 ? p->ev_range : 2.0 * p->radius;
         HIP_TRY(launch_fiber_setup(s.bs, R_in, N, ev_k, ev_d, s.stream));
         s.fiber = true;
-        HIP_TRY(launch_bead(p->storage, make_args(&s, 0), 0, 0, s.stream));
+        HIP_TRY(launch_bead(p->storage, make_args(&s, 0, 0), 0, 0, s.stream));
     }
     for (int64_t i = 0; i < n_steps; ++i) {
-        rc = enqueue_step(&s, s.cur);
+        rc = enqueue_step(&s, s.cur, s.wpar);
         if (rc) return rc;
-        s.cur = 1 - s.cur;
+        flip(&s);
     }
     if (N > 0 || health) HIP_TRY(launch_beads_out(s.bs, N, R_out, health, s.stream));
     return FPD_OK;
