@@ -291,6 +291,82 @@ template <> struct BeadGeom<float> {
     }
 };
 
+// ----------------------------------------------------------------- batch tables ----
+// The argument table is read-only while a batch kernel runs: viewing it in the constant
+// address space lets the per-simulation arguments come in through scalar loads.
+typedef const StepArgs __attribute__((address_space(4))) ConstStepArgs;
+
+__device__ inline StepArgs load_args(const StepArgs* table, int i) {
+    const ConstStepArgs* c = (const ConstStepArgs*)table;
+    StepArgs a;
+    __builtin_memcpy(&a, c + i, sizeof(StepArgs));
+    return a;
+}
+
+typedef const int __attribute__((address_space(4))) ConstInt;
+
+// A work item's simulation and index from its table (uniform: one scalar load of both).
+__device__ inline ItemRef item_ref(const ItemRef* table, int item) {
+    const ConstInt* e = (const ConstInt*)(table + item);
+    return ItemRef{e[0], e[1]};
+}
+
+// The arguments of a pass: those of the buffer it starts from, with the window slot of its
+// step.
+__device__ inline StepArgs load_pass_args(const BatchArgs& b, int sim) {
+    StepArgs a = load_args(b.args, 2 * sim + b.gpar);
+    a.parity ^= b.gpar ^ b.wpar;
+    return a;
+}
+
+typedef const PassSim __attribute__((address_space(4))) ConstPassSim;
+
+__device__ inline PassSim load_pass(const PassSim* table, int i) {
+    const ConstPassSim* c = (const ConstPassSim*)table;
+    PassSim p;
+    __builtin_memcpy(&p, c + i, sizeof(PassSim));
+    return p;
+}
+
+typedef const PatchUnit __attribute__((address_space(4))) ConstPatchUnit;
+
+__device__ inline PatchUnit load_unit(const PatchUnit* table, int i) {
+    const ConstPatchUnit* c = (const ConstPatchUnit*)table;
+    PatchUnit u;
+    __builtin_memcpy(&u, c + i, sizeof(PatchUnit));
+    return u;
+}
+
+// Unit i of a table whose first entry is at hand.
+__device__ inline PatchUnit pick_unit(const PatchUnit& unit0, const PatchUnit* table, int i) {
+    if (i == 0) return unit0;
+    const ConstPatchUnit* c = (const ConstPatchUnit*)table + i;
+    PatchUnit u;
+    u.patch[0] = c->patch[0];
+    u.patch[1] = c->patch[1];
+    u.plan = c->plan;
+    u.plan_len = c->plan_len;
+    u.pitch = c->pitch;
+    u.cap_w = c->cap_w;
+    u.cap_h = c->cap_h;
+    u.first = c->first;
+    u.n = c->n;
+    return u;
+}
+
+// A plan as the kernels of its pass read it: through the constant address space (scalar loads
+// where the index is uniform); a plan is never written by a kernel that reads it.
+typedef ConstInt* PlanPtr;
+
+__device__ inline PlanPtr unit_plan(const PatchUnit& u, int slot) {
+    return (PlanPtr)(u.plan + slot * u.plan_len);
+}
+// Columns [lo, hi) of patch row r that step t updates.
+__device__ inline int2 plan_row(const PatchUnit& u, PlanPtr plan, int t, int r) {
+    PlanPtr c = plan + kPlanRows + 2 * ((t - 1) * u.cap_h + r);
+    return int2{c[0], c[1]};
+}
+
 // -------------------------------------------------------------- pull streaming -----
 // g[k] <- post-collision g*_k at x - e_k; x wraps (y too in a periodic box, per); a
 // population that would come from behind a wall is the node's own reflected g*_{opp(k)}

@@ -74,17 +74,43 @@ constexpr int kPartMargin = 3;
 // and those inside it (kPartFiber: the fiber tiles and the step's bookkeeping).
 enum { kPartAll = 0, kPartFluid = 1, kPartFiber = 2 };
 
-// A pass advances the lattice by kPassSteps time steps: the fluid away from the fiber in one
-// kernel that reads and writes every node once (march_kernel), the nodes around the fiber
-// step by step (patch_kernel, bead_kernel).  The pass's partition is a support window grown
-// by kPassMargin nodes: a bead moves less than one node per step, so the window of the
-// step before the pass, grown by kPassSteps, holds the supports of all its steps; one node
-// more holds the ring the bead kernel pulls from, and one is slack.
+// A pass advances the lattice by kPassSteps time steps: the fluid away from the fibers in one
+// kernel that reads and writes every node once (march_kernel), the nodes around each fiber
+// step by step (patch_kernel, patch_bead_kernel).  The pass's partition is the beads' support
+// boxes grown by kPassMargin nodes: a bead moves less than one node per step (0.3 c_s, 0.17
+// nodes, already raises FPD_HEALTH_MACH) and the boxes are taken at most two steps before the
+// pass, so grown by kPassSteps + 1 they hold the supports of all its steps; one node more holds
+// the ring the bead kernel pulls from.
 constexpr int kPassSteps = 4;
 constexpr int kPassMargin = kPassSteps + 2;
-// Partition columns start and end at multiples of this (a lane of the march holds that many
-// columns at most).
+// Columns of a partition start and end at multiples of this (a lane of the march holds that
+// many columns at most), relative to a patch origin that is one.
 constexpr int kPassAlign = 4;
+constexpr int kMaxUnits = 64;      // fibers of a simulation that takes passes (bits of a mask)
+
+// One fiber's part of a pass: two buffers for its nodes' populations between the steps (nine
+// rows of `pitch` nodes side by side, cap_w x cap_h nodes at most) and two plans (by the
+// buffer a pass starts from).
+struct PatchUnit {
+    void* patch[2];
+    int* plan;                     // [2][plan_ints]
+    int plan_len;                  // plan_ints(cap_w, cap_h)
+    int pitch, cap_w, cap_h;
+    int first, n;                  // its beads
+};
+// A plan: the patch rectangle (first column, width, first row, height: the partition grown by
+// the kPassSteps - 1 nodes the first step needs around it) and the number of its tiles that
+// any step updates; each bead's support box when the plan was made; per step t = 1 ..
+// kPassSteps and patch row the columns [lo, hi) that the step updates, relative to the
+// rectangle (the last step's are the partition itself); and those tiles (ty << 16 | tx).
+constexpr int kPatchX = 32, kPatchY = 8;   // nodes of a tile of the patch kernel
+constexpr int kPlanBoxes = 8;
+constexpr int kPlanRows = kPlanBoxes + 4 * kMaxBeads;
+constexpr int plan_tiles_at(int cap_h) { return kPlanRows + 2 * kPassSteps * cap_h; }
+constexpr int plan_ints(int cap_w, int cap_h) {
+    return (plan_tiles_at(cap_h) +
+            ((cap_w + kPatchX - 1) / kPatchX) * ((cap_h + kPatchY - 1) / kPatchY) + 1) / 2 * 2;
+}
 
 // Value (k, y, x) of a population buffer sits at y * stride + k * plane + x.  The nine
 // direction rows of one lattice row are adjacent (plane = nx padded to 64 elements, stride
@@ -154,6 +180,15 @@ struct ItemRef {
     int sim, local;
 };
 
+// What a pass needs of one simulation of a batch besides its StepArgs: its fibers and the
+// tiles of its march.
+struct PassSim {
+    PatchUnit unit0;            // the first fiber's
+    const PatchUnit* units;
+    int n_units, blocks;        // blocks of the patch kernel per unit
+    int strips, seg_rows;
+};
+
 // A batch step: per simulation two StepArgs (the step parities of a chunk), item tables
 // and counts {simulations, tiles, beads}; all in device memory, so a captured graph stays
 // valid while the tables are rewritten with the same counts (the grids are sized from the
@@ -164,7 +199,17 @@ struct BatchArgs {
     const ItemRef* bead_items;  // [beads]: simulation and bead of each bead item
     const int* counts;          // [3]
     int gpar;                   // parity of this step within the chunk
+    // passes: `gpar` is then the buffer the pass starts from, wpar the window slot of its step
+    // t, both relative to the chunk's start
+    const PassSim* pass;        // [n]
+    const ItemRef* patch_items; // [counts[3]]: simulation and patch block
+    const ItemRef* march_items; // [counts[4]]: simulation and march tile
+    int wpar, t;
 };
+
+// Kinds of a march (its kernel variants); a batch's march items are sorted by kind.
+constexpr int kMarchKinds = 8;
+enum { kMarchForce = 1, kMarchPeriodic = 2, kMarchNarrow = 4 };  // bits: body force, no walls, odd nx
 
 // A box of nodes: columns cx0 + [0, cw) and rows cy0 + [0, ch), modulo the lattice along
 // periodic directions.  A box that spans a whole period along a direction (wrap_x: cw ==
@@ -176,16 +221,13 @@ struct NodeBox {
     bool wrap_x, wrap_y;
 };
 
-// One axis of a pass's partition at step t of the pass: the partition grown by the steps
-// that follow, since those pull from one node further out each.
-struct PatchArgs {
-    int t;                     // step of the pass, 1 .. kPassSteps
-    const int* part;           // the pass's partition: x0, width, y0, height
-    int* part_next;            // the next pass's (written at the last step)
-    const void* src;           // populations the step reads and writes: the lattice's
-    void* dst;                 //   buffers, or (step t > 1, resp. t < kPassSteps) the
-    int src_patch, dst_patch;  //   patch buffers, which hold the grown partition alone
-    int pitch;                 // nodes of a patch row
+// A step of a pass.
+struct PassArgs {
+    PatchUnit unit0;           // the first fiber's (most simulations have one)
+    const PatchUnit* units;
+    int n_units, blocks;       // blocks of the patch kernel per unit
+    int slot;                  // the pass's plans (the next pass's: 1 - slot)
+    int t;                     // step, 1 .. kPassSteps
 };
 
 // Kernel launchers (fpd_kernels.hip).  Given events t0 and t1, the lattice and bead
@@ -201,17 +243,27 @@ hipError_t launch_step_part(int storage, const StepArgs& a, dim3 block, int rows
 hipError_t launch_bead(int storage, const StepArgs& a, int do_velocity, int win_out,
                        hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_forces(const StepArgs& a, hipStream_t st);
-// A pass: its partition from the current support window; step q.t of the nodes around the
-// fiber (patch_w x patch_h: the largest grown partition) and the step's bead kernel; and
-// the fluid outside the partition, kPassSteps steps at once (fpd_march.hip; part: the
-// partition, NULL for none).  march_ok: whether the march handles the lattice.
-hipError_t launch_pass_setup(const StepArgs& a, int* part, hipStream_t st);
-hipError_t launch_patch(int storage, const StepArgs& a, const PatchArgs& q, int patch_w,
-                        int patch_h, hipStream_t st);
-hipError_t launch_patch_bead(int storage, const StepArgs& a, const PatchArgs& q, int win_out,
+// A pass: its plans from the current positions; step q.t of the nodes around the fibers, and
+// the step's bead kernel; and the fluid outside the partition, kPassSteps steps at once
+// (fpd_march.hip).  march_ok: whether the march handles the lattice.
+hipError_t launch_pass_setup(const StepArgs& a, const PassArgs& q, hipStream_t st);
+hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st);
+hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, int win_out,
                              hipStream_t st);
 bool march_ok(int storage, const Lattice& L);
-hipError_t launch_march(int storage, const StepArgs& a, const int* part, hipStream_t st);
+hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st);
+// Blocks of the patch kernel for a unit whose partition covers about `nodes` nodes.
+int patch_blocks(long long nodes);
+// The same for the simulations of a batch: march_kind and march_cols (columns of a march
+// tile) of a lattice; the partitions; step b.t of the patches and beads; the marches, kind by
+// kind (kind_count items each).
+int march_kind(int storage, const Lattice& L, bool force);
+int march_cols(int storage, const Lattice& L);
+hipError_t launch_batch_pass_setup(const BatchArgs& b, int sims, hipStream_t st);
+hipError_t launch_batch_patch(int storage, const BatchArgs& b, const int counts[5],
+                              bool any_periodic, bool any_record, hipStream_t st);
+hipError_t launch_batch_march(int storage, const BatchArgs& b, const int kind_count[kMarchKinds],
+                              hipStream_t st);
 // excluded-volume forces of the step's start into BeadState::Fev (before the lattice step;
 // needed only when BeadState::ev_k > 0)
 hipError_t launch_ev(const StepArgs& a, hipStream_t st);

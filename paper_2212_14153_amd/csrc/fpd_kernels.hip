@@ -841,93 +841,248 @@ __global__ void __launch_bounds__(256) fiber_kernel(StepArgs a) {
     tile_any<ST, SPT, BC, false, kPartFiber>(a, win, ty * a.tiles_x + tx, lds);
 }
 
-// ------------------------------------------------------- the fiber's part of a pass ----
+// ------------------------------------------------------- the fibers' part of a pass ----
 
-// A pass's partition and, for step t of it, the nodes that step updates: the partition
-// grown by the kPassSteps - t steps still to come.  The patch buffers hold the largest of
-// these (t = 1), from its first column and row on.
-struct PatchRect {
-    int x0, w, y0, h;
+__device__ inline View patch_view(const PatchUnit& u, PlanPtr plan, const Lattice& L,
+                                  const void* whole, int which) {
+    if (which < 0) return View{whole, 0, 0, L.stride, L.plane};
+    return View{which ? u.patch[1] : u.patch[0], plan[0], plan[2], 9 * u.pitch, u.pitch};
+}
+// The patch buffer step t reads (t - 1 wrote it) and the one it writes; -1: the lattice's.
+__device__ inline int patch_src(int t) { return t > 1 ? (t & 1) : -1; }
+__device__ inline int patch_dst(int t) { return t < kPassSteps ? ((t + 1) & 1) : -1; }
+
+// A bead's support box: node columns and rows, unwrapped (publish_support's bounds).
+struct BeadSpan {
+    int x0, x1, y0, y1;
 };
-__device__ inline PatchRect patch_rect(const int* P, int t, int nx, int ny, bool per) {
-    PatchRect r;
-    const int m = kPassSteps - t;
-    grow_axis(P[0], P[1], m, nx, true, r.x0, r.w);
-    grow_axis(P[2], P[3], m, ny, per, r.y0, r.h);
-    return r;
+__device__ inline BeadSpan bead_span(double Rx, double Ry, double rc) {
+    return BeadSpan{(int)floor(Rx - 0.5 - rc), (int)ceil(Rx - 0.5 + rc),
+                    (int)floor(Ry - 0.5 - rc), (int)ceil(Ry - 0.5 + rc)};
 }
 
-__device__ inline View patch_view(const PatchArgs& q, const Lattice& L, const void* p,
-                                  bool patch, const PatchRect& first) {
-    if (!patch) return View{p, 0, 0, L.stride, L.plane};
-    return View{p, first.x0, first.y0, 9 * q.pitch, q.pitch};
-}
+// LDS of make_plan: the beads' boxes, and the partition's columns on a run of patch rows with
+// the kPassSteps - 1 rows on either side that the first step's growth looks at.
+constexpr int kPlanRun = 512;
+struct PlanLds {
+    int bound[4];
+    int box[kMaxBeads][4];  // x0, x1, y0, y1; x1 < x0: none
+    int lo[kPlanRun + 2 * (kPassSteps - 1)], hi[kPlanRun + 2 * (kPassSteps - 1)];
+    int tiles;
+};
 
-// A support window grown into a pass's partition (columns to multiples of kPassAlign).
-__device__ inline void pass_partition(const Window& win, int nx, int ny, bool per, int* Q) {
-    const int ww = win.h > 0 ? win.w : 0;
-    grow_axis(win.x0, ww, kPassMargin, nx, true, Q[0], Q[1]);
-    grow_axis(win.y0, ww > 0 ? win.h : 0, kPassMargin, ny, per, Q[2], Q[3]);
-    if (Q[1] == 0 || Q[3] == 0) {
-        Q[0] = Q[1] = Q[2] = Q[3] = 0;
-        return;
+// The plan of unit u for a pass, from the current positions (every thread of one 1-D block).
+// A row's columns are the hull of the grown boxes that meet it, so a fiber at an angle does not
+// take its whole rectangle.
+__device__ inline void make_plan(const StepArgs& a, const PatchUnit& u, int* plan, PlanLds& sm) {
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int nx = a.L.nx, ny = a.L.ny;
+    const bool per = a.L.periodic != 0;
+    const BeadState* bs = a.fib.bs;
+    constexpr int M = kPassMargin, E = kPassSteps - 1, P = kPassAlign - 1;
+    if (tid < 4) sm.bound[tid] = tid & 1 ? -0x3fffffff : 0x3fffffff;
+    if (tid == 4) sm.tiles = 0;
+    __syncthreads();
+    for (int i = tid; i < u.n; i += nt) {
+        const double Rx = bs->R[u.first + i][0], Ry = bs->R[u.first + i][1];
+        BeadSpan s{0, -1, 0, -1};
+        if (bead_sane(Rx, Ry)) {
+            s = bead_span(Rx, Ry, a.fib.rc);
+            atomicMin(&sm.bound[0], s.x0);
+            atomicMax(&sm.bound[1], s.x1);
+            atomicMin(&sm.bound[2], s.y0);
+            atomicMax(&sm.bound[3], s.y1);
+        }
+        const int o[4] = {s.x0, s.x1, s.y0, s.y1};
+        for (int k = 0; k < 4; ++k) {
+            sm.box[i][k] = o[k];
+            plan[kPlanBoxes + 4 * i + k] = o[k];
+        }
     }
-    const int lead = Q[0] % kPassAlign;
-    Q[0] -= lead;
-    Q[1] = (Q[1] + lead + kPassAlign - 1) / kPassAlign * kPassAlign;
-    if (Q[1] >= nx) {
-        Q[0] = 0;
-        Q[1] = nx;
+    __syncthreads();
+    // the patch rectangle: first column bx and row by (unwrapped), W x H nodes; a side that
+    // would span the lattice is the lattice (allx, ally)
+    const bool none = sm.bound[0] > sm.bound[1];
+    int bx = sm.bound[0] - M - E - P, W = sm.bound[1] - sm.bound[0] + 1 + 2 * (M + E + P);
+    int X0 = none ? 0 : imod(bx, nx);
+    const int lead = X0 % kPassAlign;
+    X0 -= lead;
+    bx -= lead;
+    W += lead;
+    const bool allx = W >= nx;
+    if (allx) {
+        X0 = bx = 0;
+        W = nx;
     }
+    int by = sm.bound[2] - M - E, H = sm.bound[3] - sm.bound[2] + 1 + 2 * (M + E);
+    const bool ally = per && H >= ny;
+    if (ally) {
+        by = 0;
+        H = ny;
+    } else if (!per) {
+        const int top = min(by + H, ny);
+        by = max(by, 0);
+        H = max(top - by, 0);
+    }
+    if (none) W = H = 0;
+    if (W > u.cap_w || H > u.cap_h) {  // outgrew the reserved window
+        if (tid == 0) atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
+        W = min(W, u.cap_w);
+        H = min(H, u.cap_h);
+    }
+    if (tid == 0) {
+        plan[0] = X0;
+        plan[1] = W;
+        plan[2] = none ? 0 : (per ? imod(by, ny) : by);
+        plan[3] = H;
+    }
+    int tall = (int)ceil(2.0 * a.fib.rc) + 4 + 2 * M;  // rows of a grown box, at most
+    if (per) tall = min(tall, ny);
+    int* tiles = plan + plan_tiles_at(u.cap_h);
+    for (int r0 = 0; r0 < H; r0 += kPlanRun) {
+        const int run = min(kPlanRun, H - r0), span = run + 2 * E;
+        __syncthreads();
+        for (int i = tid; i < span; i += nt) {
+            sm.lo[i] = 0x3fffffff;
+            sm.hi[i] = -0x3fffffff;
+        }
+        __syncthreads();
+        // rows r0 - E .. r0 + run + E - 1 of the partition
+        for (int k = tid; k < u.n * tall; k += nt) {
+            const int i = k / tall, j = k - i * tall;
+            const int* o = sm.box[i];
+            if (o[1] < o[0] || j > o[3] - o[2] + 2 * M) continue;
+            int c0 = o[0] - M - bx, c1 = o[1] + M + 1 - bx;
+            if (allx) {
+                const int w = c1 - c0;
+                c0 = imod(c0, nx);
+                c1 = c0 + w;
+            }
+            c0 = c0 / kPassAlign * kPassAlign;  // (c0 >= 0); the march masks whole lanes
+            c1 = (c1 + P) / kPassAlign * kPassAlign;
+            if (allx && c1 > nx) {
+                c0 = 0;
+                c1 = nx;
+            }
+            const int r = o[2] - M + j - by;
+            for (int q = ally ? imod(r, ny) - ny : r; q < r0 + run + E; q += ny) {
+                if (q >= r0 - E && (ally || (q >= 0 && q < H))) {
+                    atomicMin(&sm.lo[q - r0 + E], c0);
+                    atomicMax(&sm.hi[q - r0 + E], c1);
+                }
+                if (!ally) break;
+            }
+        }
+        __syncthreads();
+        // each step's columns: m rows and columns more on either side, m = kPassSteps - t
+        int2* rows = (int2*)(plan + kPlanRows);
+        for (int i = tid; i < run; i += nt) {
+            int l = sm.lo[i + E], h = sm.hi[i + E];
+            for (int m = 0; m < kPassSteps; ++m) {
+                if (m > 0) {
+                    l = min(l, min(sm.lo[i + E - m], sm.lo[i + E + m]));
+                    h = max(h, max(sm.hi[i + E - m], sm.hi[i + E + m]));
+                }
+                int cl = l - m, ch = h + m;
+                if (allx && l < h && (cl < 0 || ch > nx)) {
+                    cl = 0;
+                    ch = nx;
+                }
+                cl = max(cl, 0);
+                ch = min(ch, W);
+                rows[(kPassSteps - 1 - m) * u.cap_h + r0 + i] = l < h && cl < ch ? int2{cl, ch}
+                                                                                : int2{0, 0};
+            }
+        }
+        // the tiles of the first step (kPlanRun is a multiple of a tile's rows)
+        for (int ty = tid; ty < (run + kPatchY - 1) / kPatchY; ty += nt) {
+            int l = 0x3fffffff, h = -0x3fffffff;
+            for (int i = ty * kPatchY; i < min((ty + 1) * kPatchY, run) + 2 * E; ++i) {
+                l = min(l, sm.lo[i]);
+                h = max(h, sm.hi[i]);
+            }
+            if (l >= h) continue;
+            l -= E;
+            h += E;
+            if (allx && (l < 0 || h > nx)) {
+                l = 0;
+                h = nx;
+            }
+            l = max(l, 0);
+            h = min(h, W);
+            if (l >= h) continue;
+            const int t0 = l / kPatchX, t1 = (h - 1) / kPatchX;
+            const int at = atomicAdd(&sm.tiles, t1 - t0 + 1);
+            for (int tx = t0; tx <= t1; ++tx)
+                tiles[at + tx - t0] = ((r0 / kPatchY + ty) << 16) | tx;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) plan[4] = sm.tiles;
+}
+static_assert(kPlanRun % kPatchY == 0, "a run of plan rows is whole tiles");
+
+// The next pass's plan, by a block of the bead kernel of step kPassSteps - 1, beside the beads:
+// each position is read as it was before or after its update, either at most two steps from
+// the pass's first, which the margin covers.
+__device__ inline void next_plan(const StepArgs& a, const PatchUnit& u, int slot, PlanLds& sm) {
+    make_plan(a, u, u.plan + (1 - slot) * u.plan_len, sm);
 }
 
-__global__ void pass_setup_kernel(StepArgs a, int* part) {
-    if (threadIdx.x == 0)
-        pass_partition(tile_window(a), a.L.nx, a.L.ny, a.L.periodic != 0, part);
+__global__ void __launch_bounds__(256) pass_setup_kernel(StepArgs a, PassArgs q) {
+    __shared__ PlanLds sm;
+    const PatchUnit u = load_unit(q.units, blockIdx.x);
+    make_plan(a, u, u.plan + q.slot * u.plan_len, sm);
 }
 
-// Step q.t of a pass for the nodes around the fiber, one node per thread: the same
-// arithmetic per node as a fiber tile of step_kernel, read from and written to the lattice
-// or a patch buffer.  The grid covers the largest partition the reserved window allows;
-// block 0 also does the step's bookkeeping.
-constexpr int kPatchX = 64, kPatchY = 4;
+// The patch and bead kernels of a pass are the latency chain beside the march: their waves
+// are issued ahead of its waves on a SIMD.
+__device__ inline void chain_priority() { __builtin_amdgcn_s_setprio(3); }
 
-template <int ST, int BC, bool FR>
-__device__ inline void patch_tile(const StepArgs& a, const PatchArgs& q, const Window& win,
-                                  int bx, int by, TileLds& lds) {
+// Step q.t of a pass for the nodes around one fiber, one node per thread in tiles of
+// kPatchX x kPatchY: the same arithmetic per node as a fiber tile of step_kernel, read from
+// and written to the lattice or a patch buffer.  A unit has q.blocks blocks, about one per
+// tile of its plan, and one more for the bookkeeping.  Nodes that two fibers' partitions
+// share are computed by both, alike.  32 x 8 nodes: a fiber at an angle leaves out more of
+// narrow tiles, and a tile gathers fewer beads than 64 x 4 ones.
+template <int ST, int BC>
+__device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
+                                  const Window& win, int tx, int ty, TileLds& lds) {
     using Cd = Codec<ST>;
     using T = typename Cd::T;
     using S = typename Cd::store_t;
     constexpr bool kScaled = ST == FPD_F16DEV;
     const bool per = periodic_of(BC, a);
     const int nx = a.L.nx, ny = a.L.ny;
-    const PatchRect first = patch_rect(q.part, 1, nx, ny, per);
-    const PatchRect r = patch_rect(q.part, q.t, nx, ny, per);
-    const int cx = bx * kPatchX, cy = by * kPatchY;
-    if (cx >= r.w || cy >= r.h) return;  // block-uniform
-    const int cw = min(kPatchX, r.w - cx), ch = min(kPatchY, r.h - cy);
-    int x0 = r.x0 + cx, y0 = r.y0 + cy;
+    const int cx = tx * kPatchX, cy = ty * kPatchY;
+    const int cw = min(kPatchX, plan[1] - cx), ch = min(kPatchY, plan[3] - cy);
+    int x0 = plan[0] + cx, y0 = plan[2] + cy;
     if (x0 >= nx) x0 -= nx;
     if (per && y0 >= ny) y0 -= ny;
     const int lx = threadIdx.x % kPatchX, ly = threadIdx.x / kPatchX;
-    const bool in = lx < cw && ly < ch;
+    bool in = ly < ch && lx < cw;
+    if (in) {
+        const int2 c = plan_row(u, plan, t, cy + ly);
+        in = cx + lx >= c.x && cx + lx < c.y;
+    }
+    if (t > 1 && !__syncthreads_or(in)) return;  // a tile of an earlier step's ring
     int x = x0 + lx, y = y0 + ly;
     if (x >= nx) x -= nx;
     if (per && y >= ny) y -= ny;
     const T u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
     T g[9];
     if (in)
-        pull_view<Cd, true>(patch_view(q, a.L, q.src, q.src_patch != 0, first), nx, ny, x, y, per,
-                            u6, g);
+        pull_view<Cd, true>(patch_view(u, plan, a.L, a.src, patch_src(t)), nx, ny, x, y, per, u6,
+                            g);
     TileBead<T>* sB = (TileBead<T>*)lds.beads;
     const int nb = gather_beads<T>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
-                                   lds.bonds, FR);
+                                   lds.bonds, false);
     if (!in) return;
     T Fx = (T)a.gx, Fy = (T)a.gy, s_nu = (T)a.s_nu_f, s_q = (T)a.s_q_f;
     const T s_e = (T)a.s_e, s_eps = (T)a.s_eps;
     if (nb > 0)
         fiber_node<T>(a, per, sB, nb, x, y, win.x0, win.y0, win.w, win.h, Fx, Fy, s_nu, s_q);
-    const View v = patch_view(q, a.L, q.dst, q.dst_patch != 0, first);
+    const View v = patch_view(u, plan, a.L, a.dst, patch_dst(t));
     int c = x - v.ox, w = y - v.oy;
     if (c < 0) c += nx;
     if (w < 0) w += ny;
@@ -948,46 +1103,82 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchArgs& q, const W
     }
 }
 
-// The bookkeeping of step q.t (every thread of one block): that of any step, the check
-// that the partition held the window and what the rest of the pass reads around it, and at
-// the last step the next pass's partition.
-__device__ inline void patch_duties(const StepArgs& a, const PatchArgs& q, const Window& win) {
-    step_duties(a, win, false);
-    if (threadIdx.x != 0) return;
-    const int nx = a.L.nx, ny = a.L.ny;
-    const bool per = a.L.periodic != 0;
-    const int ww = win.h > 0 ? win.w : 0, m = max(kPassSteps - q.t, 1);
-    if (!axis_inside(win.x0, ww, m, q.part[0], q.part[1], nx, true) ||
-        !axis_inside(win.y0, ww > 0 ? win.h : 0, m, q.part[2], q.part[3], ny, per))
-        atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
-    if (q.t == kPassSteps) pass_partition(win, nx, ny, per, q.part_next);
+// The bookkeeping of a unit (its last block): for the first unit that of any step, and the
+// check that the unit's beads stayed near enough to where the plan found them for the partition
+// to hold what the rest of the pass needs.
+__device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
+                                    bool first, const Window& win) {
+    if (first) step_duties(a, win, false);
+    const int k = kPassMargin - max(kPassSteps - t, 1);
+    for (int i = threadIdx.x; i < u.n; i += blockDim.x) {
+        const double Rx = a.fib.bs->R[u.first + i][0], Ry = a.fib.bs->R[u.first + i][1];
+        if (!bead_sane(Rx, Ry)) continue;
+        const BeadSpan s = bead_span(Rx, Ry, a.fib.rc);
+        PlanPtr g = plan + kPlanBoxes + 4 * i;
+        if (s.x0 < g[0] - k || s.x1 > g[1] + k || s.y0 < g[2] - k || s.y1 > g[3] + k)
+            atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
+    }
 }
 
 template <int ST, int BC>
-__global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, PatchArgs q) {
-    __shared__ TileLds lds;
+__device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int blocks, int slot,
+                                   int t, int k, bool first, TileLds& lds) {
     const Window win = tile_window(a);
-    if (blockIdx.x == 0 && blockIdx.y == 0) patch_duties(a, q, win);
-    patch_tile<ST, BC, false>(a, q, win, blockIdx.x, blockIdx.y, lds);
+    PlanPtr plan = unit_plan(u, slot);
+    if (k == blocks) {
+        patch_duties(a, u, plan, t, first, win);
+        return;
+    }
+    PlanPtr list = plan + plan_tiles_at(u.cap_h);
+    const int tiles = plan[4];
+    for (int i = k; i < tiles; i += blocks) {
+        const int e = list[i];
+        patch_tile<ST, BC>(a, u, plan, t, win, e & 0xffff, e >> 16, lds);
+        __syncthreads();  // the next tile's beads overwrite this one's
+    }
 }
 
-// The argument table is read-only while a batch kernel runs: viewing it in the constant
-// address space lets the per-simulation arguments come in through scalar loads.
-typedef const StepArgs __attribute__((address_space(4))) ConstStepArgs;
-
-__device__ inline StepArgs load_args(const StepArgs* table, int i) {
-    const ConstStepArgs* c = (const ConstStepArgs*)table;
-    StepArgs a;
-    __builtin_memcpy(&a, c + i, sizeof(StepArgs));
-    return a;
+template <int ST, int BC>
+__global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, PassArgs q) {
+    __shared__ TileLds lds;
+    chain_priority();
+    const PatchUnit u = pick_unit(q.unit0, q.units, blockIdx.y);
+    patch_block<ST, BC>(a, u, q.blocks, q.slot, q.t, blockIdx.x, blockIdx.y == 0, lds);
 }
 
-typedef const int __attribute__((address_space(4))) ConstInt;
+// The passes of a batch: the plans, one block per simulation; the patch tiles and the beads of
+// step b.t, one block per item.
+__global__ void __launch_bounds__(256) batch_pass_setup_kernel(BatchArgs b) {
+    __shared__ PlanLds sm;
+    const int s = blockIdx.x;
+    if (s >= b.counts[0]) return;
+    const StepArgs a = load_pass_args(b, s);
+    const PassSim p = load_pass(b.pass, s);
+    for (int i = 0; i < p.n_units; ++i) {
+        const PatchUnit u = load_unit(p.units, i);
+        make_plan(a, u, u.plan + b.gpar * u.plan_len, sm);
+        __syncthreads();
+    }
+}
 
-// A work item's simulation and index from its table (uniform: one scalar load of both).
-__device__ inline ItemRef item_ref(const ItemRef* table, int item) {
-    const ConstInt* e = (const ConstInt*)(table + item);
-    return ItemRef{e[0], e[1]};
+template <int ST, int BC>
+__global__ void __launch_bounds__(kPatchX * kPatchY) batch_patch_kernel(BatchArgs b) {
+    __shared__ TileLds lds;
+    chain_priority();
+    const ItemRef e = item_ref(b.patch_items, blockIdx.x);
+    if ((int)blockIdx.x >= b.counts[3] || e.sim < 0) return;
+    const StepArgs a = load_pass_args(b, e.sim);
+    const PassSim p = load_pass(b.pass, e.sim);
+    const int per = p.blocks + 1, unit = e.local / per;
+    patch_block<ST, BC>(a, pick_unit(p.unit0, p.units, unit), p.blocks, b.gpar, b.t,
+                        e.local - unit * per, unit == 0, lds);
+}
+
+// The fiber-ends recorders of a batch's simulations, ahead of a step of a pass.
+__global__ void __launch_bounds__(kBeadThreads) batch_record_kernel(BatchArgs b) {
+    if ((int)blockIdx.x >= b.counts[0]) return;
+    const StepArgs a = load_pass_args(b, blockIdx.x);
+    if (a.rec && a.fib.n > 0) record_ends(a);
 }
 
 // Lattice kernel over a batch of simulations of different sizes: one block per (simulation,
@@ -1225,14 +1416,21 @@ __global__ void __launch_bounds__(kBeadBlock) bead_kernel(StepArgs a, int do_vel
 template <int ST> constexpr int kPatchBeadBlock = ST == FPD_F64 ? 256 : kBeadBlock;
 
 template <int ST>
-__global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArgs a, PatchArgs q,
+__global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArgs a, PassArgs q,
                                                                          int win_out) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
     __shared__ double s_R[2];
-    const PatchRect first = patch_rect(q.part, 1, a.L.nx, a.L.ny, a.L.periodic != 0);
+    __shared__ PlanLds plan;
+    chain_priority();
+    if ((int)blockIdx.x >= a.fib.n) {  // (step kPassSteps - 1 only)
+        next_plan(a, pick_unit(q.unit0, q.units, (int)blockIdx.x - a.fib.n), q.slot, plan);
+        return;
+    }
+    const int unit = (int)blockIdx.x / a.fib.chain_len;
+    const PatchUnit u = pick_unit(q.unit0, q.units, unit);
     bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
         a, blockIdx.x, 1, win_out, scratch, s_R,
-        patch_view(q, a.L, q.dst, q.dst_patch != 0, first));
+        patch_view(u, unit_plan(u, q.slot), a.L, a.dst, patch_dst(q.t)));
 }
 
 // Bead kernel over a batch: one block per (simulation, bead) item.
@@ -1246,6 +1444,36 @@ __global__ void __launch_bounds__(kBatchBeadBlock) batch_bead_kernel(BatchArgs b
     const StepArgs a = load_args(b.args, 2 * e.sim + b.gpar);
     bead_block<ST, kBatchBeadVelBatch, kBatchBeadBlock>(a, e.local, 1, 1 - a.parity,
                                                         scratch, s_R);
+}
+
+// The beads of step b.t of a batch's passes.
+template <int ST>
+__global__ void __launch_bounds__(kBatchBeadBlock) batch_patch_bead_kernel(BatchArgs b) {
+    __shared__ double scratch[2 * (kBeadLanes / 64)];
+    __shared__ double s_R[2];
+    __shared__ PlanLds plan;
+    chain_priority();
+    const int beads = b.counts[2];
+    if ((int)blockIdx.x >= beads) {  // (step kPassSteps - 1 only)
+        const int s = (int)blockIdx.x - beads;
+        if (s >= b.counts[0]) return;
+        const StepArgs a = load_pass_args(b, s);
+        const PassSim p = load_pass(b.pass, s);
+        for (int i = 0; i < p.n_units; ++i) {
+            next_plan(a, pick_unit(p.unit0, p.units, i), b.gpar, plan);
+            __syncthreads();
+        }
+        return;
+    }
+    const ItemRef e = item_ref(b.bead_items, blockIdx.x);
+    if (e.sim < 0) return;
+    const StepArgs a = load_pass_args(b, e.sim);
+    const PassSim p = load_pass(b.pass, e.sim);
+    const int unit = e.local / a.fib.chain_len;
+    const PatchUnit u = pick_unit(p.unit0, p.units, unit);
+    bead_block<ST, kBatchBeadVelBatch, kBatchBeadBlock, true>(
+        a, e.local, 1, 1 - a.parity, scratch, s_R,
+        patch_view(u, unit_plan(u, b.gpar), a.L, a.dst, patch_dst(b.t)));
 }
 
 // Excluded-volume forces of every bead at the step's start (one block).
@@ -1776,17 +2004,21 @@ hipError_t launch_bead(int storage, const StepArgs& a, int do_velocity, int win_
     return launch_k(k, dim3(a.fib.n), dim3(kBeadBlock), st, t0, t1, a, do_velocity, win_out);
 }
 
-hipError_t launch_pass_setup(const StepArgs& a, int* part, hipStream_t st) {
-    hipLaunchKernelGGL(pass_setup_kernel, dim3(1), dim3(64), 0, st, a, part);
+hipError_t launch_pass_setup(const StepArgs& a, const PassArgs& q, hipStream_t st) {
+    hipLaunchKernelGGL(pass_setup_kernel, dim3(q.n_units), dim3(256), 0, st, a, q);
     return hipGetLastError();
 }
 
-hipError_t launch_patch(int storage, const StepArgs& a, const PatchArgs& q, int patch_w,
-                        int patch_h, hipStream_t st) {
-    const dim3 grid((patch_w + kPatchX - 1) / kPatchX, (patch_h + kPatchY - 1) / kPatchY);
-    const dim3 block(kPatchX * kPatchY);
+int patch_blocks(long long nodes) {
+    // a fiber at 45 degrees takes about twice the tiles of its band's area
+    const long long n = 2 * nodes / (kPatchX * kPatchY) + 8;
+    return (int)std::min<long long>(n, 1024);
+}
+
+hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st) {
+    const dim3 grid(q.blocks + 1, q.n_units), block(kPatchX * kPatchY);
     const bool per = a.L.periodic != 0;
-    void (*k)(StepArgs, PatchArgs) = nullptr;
+    void (*k)(StepArgs, PassArgs) = nullptr;
     switch (storage) {
         case FPD_F64: k = per ? patch_kernel<FPD_F64, kPeriodic> : patch_kernel<FPD_F64, kWalls>; break;
         case FPD_F32: k = per ? patch_kernel<FPD_F32, kPeriodic> : patch_kernel<FPD_F32, kWalls>; break;
@@ -1797,10 +2029,10 @@ hipError_t launch_patch(int storage, const StepArgs& a, const PatchArgs& q, int 
     return launch_k(k, grid, block, st, nullptr, nullptr, a, q);
 }
 
-hipError_t launch_patch_bead(int storage, const StepArgs& a, const PatchArgs& q, int win_out,
+hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, int win_out,
                              hipStream_t st) {
     if (a.fib.n <= 0) return hipSuccess;
-    void (*k)(StepArgs, PatchArgs, int) = nullptr;
+    void (*k)(StepArgs, PassArgs, int) = nullptr;
     switch (storage) {
         case FPD_F64: k = patch_bead_kernel<FPD_F64>; break;
         case FPD_F32: k = patch_bead_kernel<FPD_F32>; break;
@@ -1809,7 +2041,8 @@ hipError_t launch_patch_bead(int storage, const StepArgs& a, const PatchArgs& q,
         default: return hipErrorInvalidValue;
     }
     const int threads = storage == FPD_F64 ? kPatchBeadBlock<FPD_F64> : kPatchBeadBlock<FPD_F32>;
-    return launch_k(k, dim3(a.fib.n), dim3(threads), st, nullptr, nullptr, a, q, win_out);
+    const int plans = q.t == kPassSteps - 1 ? q.n_units : 0;
+    return launch_k(k, dim3(a.fib.n + plans), dim3(threads), st, nullptr, nullptr, a, q, win_out);
 }
 
 // Forces F^n, F/A and bond strains of every simulation of a batch, one block per
@@ -1870,6 +2103,40 @@ hipError_t launch_batch_step(int storage, const BatchArgs& b, dim3 block, int sp
         case FPD_F32: return launch_batch_t<FPD_F32>(b, block, spt, counts, any_periodic, st);
         case FPD_F16DEV: return launch_batch_t<FPD_F16DEV>(b, block, spt, counts, any_periodic, st);
         case FPD_BF16DEV: return launch_batch_t<FPD_BF16DEV>(b, block, spt, counts, any_periodic, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_pass_setup(const BatchArgs& b, int sims, hipStream_t st) {
+    if (sims <= 0) return hipSuccess;
+    hipLaunchKernelGGL(batch_pass_setup_kernel, dim3(sims), dim3(256), 0, st, b);
+    return hipGetLastError();
+}
+
+template <int ST>
+static hipError_t launch_batch_patch_t(const BatchArgs& b, const int counts[5], bool any_periodic,
+                                       bool any_record, hipStream_t st) {
+    if (counts[2] <= 0) return hipSuccess;
+    if (any_record)
+        hipLaunchKernelGGL(batch_record_kernel, dim3(counts[0]), dim3(kBeadThreads), 0, st, b);
+    const dim3 grid(counts[3]), block(kPatchX * kPatchY);
+    if (any_periodic)
+        hipLaunchKernelGGL((batch_patch_kernel<ST, kAnyBoundary>), grid, block, 0, st, b);
+    else
+        hipLaunchKernelGGL((batch_patch_kernel<ST, kWalls>), grid, block, 0, st, b);
+    const int plans = b.t == kPassSteps - 1 ? counts[0] : 0;
+    hipLaunchKernelGGL((batch_patch_bead_kernel<ST>), dim3(counts[2] + plans),
+                       dim3(kBatchBeadBlock), 0, st, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_patch(int storage, const BatchArgs& b, const int counts[5],
+                              bool any_periodic, bool any_record, hipStream_t st) {
+    switch (storage) {
+        case FPD_F64: return launch_batch_patch_t<FPD_F64>(b, counts, any_periodic, any_record, st);
+        case FPD_F32: return launch_batch_patch_t<FPD_F32>(b, counts, any_periodic, any_record, st);
+        case FPD_F16DEV: return launch_batch_patch_t<FPD_F16DEV>(b, counts, any_periodic, any_record, st);
+        case FPD_BF16DEV: return launch_batch_patch_t<FPD_BF16DEV>(b, counts, any_periodic, any_record, st);
     }
     return hipErrorInvalidValue;
 }

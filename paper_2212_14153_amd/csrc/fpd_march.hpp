@@ -149,8 +149,9 @@ struct MarchArgs {
     void* dst;
     Lattice L;
     double u6, s_nu, s_q, s_e, s_eps, gx, gy;
-    const int* part;            // nodes not to store (x0, width, y0, height), or NULL
-    int strips, segs, seg_rows; // columns and rows of the waves' tiles
+    const PatchUnit* units;     // whose partitions (in plan `slot`) are not stored
+    int n_units, slot;
+    int strips, seg_rows;       // tiles: strips of columns, runs of rows
 };
 
 template <int ST, int NT, int C, int OL, int BC, bool FORCE>
@@ -172,8 +173,11 @@ struct March {
     char* dst;
     int nx, ny, y0, y1, lo1, hi1;
     unsigned rowb, planeb;              // bytes of a lattice row and of a direction row
-    unsigned ld, st, st_part;           // lane offsets of loads and stores; in rows of the partition
-    int part_y0, part_h;
+    unsigned ld, st;                    // lane offsets of loads and stores
+    int x0;                             // the lane's first column, before the wrap
+    const PatchUnit* units;
+    int slot;
+    unsigned long long near;            // units whose patch rectangle meets the wave's tile
     T u6, s_nu, s_q, s_e, s_eps, Fx, Fy;
     Held h[NT > 1 ? NT - 1 : 1];
     Row q[2][9];
@@ -181,10 +185,35 @@ struct March {
     __device__ inline int lo(int t) const { const int r = y0 - (NT - t); return per || r > 0 ? r : 0; }
     __device__ inline int hi(int t) const { const int r = y1 + (NT - t); return per || r < ny ? r : ny; }
     __device__ inline const char* row(int y) const { return src + (long long)y * rowb; }
-    __device__ inline bool row_in_part(int r) const {
-        int d = r - part_y0;
-        if (per && d < 0) d += ny;
-        return (unsigned)d < (unsigned)part_h;
+    // Lane offset of the stores of row r: off for the columns that some fiber's partition
+    // holds on that row (whole lanes; few waves have a fiber near, the others branch past).
+    __device__ inline unsigned store_offset(int r) const {
+        unsigned off = st;
+        for (unsigned long long m = near; m != 0ull; m &= m - 1ull) {
+            const PatchUnit u = load_unit(units, __builtin_ctzll(m));
+            PlanPtr plan = unit_plan(u, slot);
+            int d = r - plan[2];
+            if (per && d < 0) d += ny;
+            if ((unsigned)d >= (unsigned)plan[3]) continue;
+            const int2 c = plan_row(u, plan, kPassSteps, d);
+            int cl = x0 - plan[0];
+            if (cl < 0) cl += nx;
+            if (cl >= c.x && cl < c.y) off = kLaneOff;
+        }
+        return off;
+    }
+    // The units (bits) whose patch rectangle meets the wave's tile: lane i looks at unit i.
+    __device__ inline unsigned long long units_near(int n, int c0, int cols) const {
+        const int lane = (int)threadIdx.x & 63;
+        bool hit = false;
+        if (lane < n) {
+            const PatchUnit u = units[lane];
+            const int* plan = u.plan + slot * u.plan_len;
+            const int w = plan[1], h = plan[3], p0 = plan[2];
+            hit = w > 0 && h > 0 && cols_overlap(c0 % nx, min(cols, nx), plan[0], w, nx) &&
+                  (per ? cols_overlap(y0, y1 - y0, p0, h, ny) : (y0 < p0 + h && p0 < y1));
+        }
+        return __ballot(hit);
     }
     __device__ inline int wrap(int y) const {
         if (per) {
@@ -272,6 +301,9 @@ struct March {
     // Row i of the first stage and, behind it, row i - (t - 1) of stage t; PH alternates
     // from row to row.  FAST: every stage has a row, none at a wall, and row i + 1 follows.
     template <bool FAST, int PH> __device__ inline void row_step(int i) {
+        // (found before the row's work: few values are live here)
+        unsigned off = st;
+        if (near) off = store_offset(i - (NT - 1));
         Row p[9];
         if (FAST || i < hi1) {
             if (FAST || i + 1 < hi1) fetch<FAST>(i + 1, q[1 - PH]);
@@ -311,7 +343,6 @@ struct March {
         const int r = i - (NT - 1);
         if (FAST || (r >= y0 && r < y1)) {
             const auto o = row_rsrc(dst + (long long)r * rowb, rowb);
-            const unsigned off = row_in_part(r) ? st_part : st;
 #pragma unroll
             for (int k = 0; k < 9; ++k) row_store(o, off, k * planeb, p[k].w);
         }
@@ -326,19 +357,14 @@ struct March {
         src = (const char*)a.src;
         dst = (char*)a.dst;
         const int lane = (int)threadIdx.x & 63;
-        const int x0 = (strip * OL + lane - HL) * C;     // first column, before the wrap
+        x0 = (strip * OL + lane - HL) * C;
         int xw = x0 % nx;
         if (xw < 0) xw += nx;
         ld = (unsigned)(xw * (int)sizeof(S));
         st = lane >= HL && lane < HL + OL && x0 < nx ? (unsigned)(x0 * (int)sizeof(S)) : kLaneOff;
-        st_part = st;
-        part_y0 = part_h = 0;
-        if (a.part) {
-            const int px0 = a.part[0], pw = a.part[1];
-            part_y0 = a.part[2];
-            part_h = pw > 0 ? a.part[3] : 0;
-            if (imod(x0 - px0, nx) < pw) st_part = kLaneOff;
-        }
+        units = a.units;
+        slot = a.slot;
+        near = a.n_units > 0 ? units_near(a.n_units, strip * OL * C, OL * C) : 0ull;
         u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
         s_nu = (T)a.s_nu;
         s_q = (T)a.s_q;

@@ -137,11 +137,12 @@ struct fpd_sim {
     fpd_launch launch{};
     hipGraphExec_t graph[4] = {};  // by (cur, wpar)
     int graph_chunk = 0;
-    // passes: two buffers for the steps of the nodes around the fiber (nullptr: no passes)
-    // of patch_w x patch_h nodes, and the partitions of the passes from either buffer
-    void* patch[2] = {nullptr, nullptr};
-    int* pass_part = nullptr;    // [2][4]
-    int patch_w = 0, patch_h = 0, patch_pitch = 0;
+    // passes: the fibers' patch buffers and plans, one allocation that starts with the units
+    // (nullptr: no passes), and the patch kernel's blocks per unit
+    PatchUnit* units = nullptr;
+    PatchUnit unit0{};
+    int n_units = 0, patch_blocks = 1;
+    bool passes = false;         // the lattice takes passes
     // split steps: the fluid kernels on a side stream, the fiber and bead kernels on
     // `stream`, ordered by the two events (created with the first split step)
     hipStream_t side = nullptr;
@@ -365,12 +366,15 @@ int enqueue_step(fpd_sim* s, int from, int wpar) {
 // where the simulation has the patch buffers.
 bool use_passes(const fpd_sim* s) {
     if (s->row_phi || (s->p.flags & FPD_FLAG_NO_SPLIT)) return false;
-    if (!s->pass_part || (s->p.n_beads > 0 && (!s->fiber || !s->patch[0]))) return false;
-    return true;
+    return s->passes && (s->p.n_beads == 0 || s->fiber);
+}
+
+PassArgs pass_args(const fpd_sim* s, int from, int t) {
+    return PassArgs{s->unit0, s->units, s->n_units, s->patch_blocks, from, t};
 }
 
 // One pass from buffer `from`: the fluid kernel on the side stream, the steps of the nodes
-// around the fiber on `stream`.  The fluid kernel reads what the pass before wrote and
+// around the fibers on `stream`.  The fluid kernel reads what the pass before wrote and
 // overwrites the buffer that pass read, so it waits for that pass's last patch kernel
 // (ev_fiber; its fluid kernel is before it on the side stream); the first patch kernel
 // waits for the fluid kernel of the pass before (ev_fluid).  first: the start of a run,
@@ -378,28 +382,19 @@ bool use_passes(const fpd_sim* s) {
 int enqueue_pass(fpd_sim* s, int from, int wpar, bool first) {
     StepArgs a = make_args(s, from, wpar);
     if (a.fib.n <= 0) {
-        HIP_TRY(launch_march(s->p.storage, a, nullptr, s->stream));
+        HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->stream));
         return FPD_OK;
     }
-    const int* part = s->pass_part + 4 * from;
     HIP_TRY(hipStreamWaitEvent(s->side, s->ev_fiber, 0));
-    HIP_TRY(launch_march(s->p.storage, a, part, s->side));
+    HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->side));
     if (!first) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
     HIP_TRY(hipEventRecord(s->ev_fluid, s->side));
     for (int t = 1; t <= kPassSteps; ++t) {
-        PatchArgs q{};
-        q.t = t;
-        q.part = part;
-        q.part_next = s->pass_part + 4 * (1 - from);
-        q.src_patch = t > 1;
-        q.dst_patch = t < kPassSteps;
-        q.src = t > 1 ? s->patch[t & 1] : s->buf[from];
-        q.dst = t < kPassSteps ? s->patch[(t + 1) & 1] : s->buf[1 - from];
-        q.pitch = s->patch_pitch;
+        const PassArgs q = pass_args(s, from, t);
         a.parity = wpar;
         HIP_TRY(launch_record(a, s->stream));
         if (has_ev(s)) HIP_TRY(launch_ev(a, s->stream));
-        HIP_TRY(launch_patch(s->p.storage, a, q, s->patch_w, s->patch_h, s->stream));
+        HIP_TRY(launch_patch(s->p.storage, a, q, s->stream));
         if (t == kPassSteps) HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
         HIP_TRY(launch_patch_bead(s->p.storage, a, q, 1 - wpar, s->stream));
         wpar = 1 - wpar;
@@ -413,7 +408,7 @@ int enqueue_steps(fpd_sim* s, int from, int wpar, int64_t n) {
     if (use_passes(s) && n >= kPassSteps) {
         const bool fib = s->fiber && s->p.n_beads > 0;
         if (fib) {
-            HIP_TRY(launch_pass_setup(make_args(s, from, wpar), s->pass_part + 4 * from,
+            HIP_TRY(launch_pass_setup(make_args(s, from, wpar), pass_args(s, from, 1),
                                       s->stream));
             HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
         }
@@ -598,36 +593,59 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
 // 2042 x 611 in float16 deviations passes gain (25.3 against 28.4).
 constexpr long long kMinPassNodes = 1LL << 20;
 
-// The patch buffers of the passes, where a lattice takes them: the march handles it, one
-// fiber at most, and the largest grown partition spans at most half the lattice.  A
-// simulation whose buffers cannot be allocated runs without passes.  Allocated with the
-// simulation, so that a step never allocates.
-void alloc_passes(fpd_sim* s) {
+// The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
+// at most kMaxUnits fibers, and the patches together span at most `share` of the lattice's
+// nodes.  A simulation whose buffers cannot be allocated runs without passes.  Allocated with
+// the simulation, so that a step never allocates.
+int alloc_passes(fpd_sim* s, long long min_nodes, double share) {
     const fpd_params& p = s->p;
-    if (!march_ok(p.storage, s->L) || chains_of(&p) > 1) return;
-    if ((long long)p.nx * p.ny < kMinPassNodes) return;
-    void* part = nullptr;
-    if (p.n_beads > 0) {
-        const int grow = 2 * (kPassMargin + kPassSteps - 1);
-        s->patch_w = std::min(p.nx, s->rect_wmax + grow + 2 * kPassAlign);
-        s->patch_h = std::min(p.ny, s->rect_hmax + grow);
-        if (2LL * s->patch_w * s->patch_h > (long long)p.nx * p.ny) return;
-        s->patch_pitch = (s->patch_w + 15) / 16 * 16;
-        const size_t bytes = (size_t)9 * s->patch_pitch * s->patch_h * s->elem;
-        for (auto& b : s->patch)
-            if (hipMalloc(&b, bytes) != hipSuccess) b = nullptr;
+    const long long nodes = (long long)p.nx * p.ny;
+    if (!march_ok(p.storage, s->L) || nodes < min_nodes) return FPD_OK;
+    if (p.n_beads <= 0) {
+        s->passes = true;
+        return FPD_OK;
     }
-    if (hipMalloc(&part, sizeof(int) * 8) != hipSuccess) part = nullptr;
-    if (!part || (p.n_beads > 0 && (!s->patch[0] || !s->patch[1]))) {
+    const int n_units = chains_of(&p), len = p.n_beads / n_units;
+    if (n_units > kMaxUnits) return FPD_OK;
+    // one fiber's reserved window (window_size) and the margins around it
+    const double span = 1.5 * (len - 1) * p.l0 + 2.0 * s->rc + 4.0;
+    const int grow = 2 * (kPassMargin + kPassSteps - 1);
+    const int w = (int)fmin(ceil(span) + grow + 3 * kPassAlign, (double)p.nx);
+    const int h = (int)fmin(ceil(span) + grow, (double)p.ny);
+    if ((double)w * h * n_units > share * (double)nodes) return FPD_OK;
+    const int pitch = (w + 15) / 16 * 16;
+    const size_t patch = (size_t)9 * pitch * h * s->elem;
+    const size_t plan = sizeof(int) * 2 * (size_t)plan_ints(w, h);
+    auto round = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t table = round(sizeof(PatchUnit) * n_units);
+    const size_t each = 2 * round(patch) + round(plan);
+    char* m = nullptr;
+    if (hipMalloc((void**)&m, table + n_units * each) != hipSuccess) {
         (void)hipGetLastError();
-        for (auto& b : s->patch) {
-            if (b) (void)hipFree(b);
-            b = nullptr;
-        }
-        if (part) (void)hipFree(part);
-        return;
+        return FPD_OK;
     }
-    s->pass_part = (int*)part;
+    s->units = (PatchUnit*)m;
+    std::vector<PatchUnit> u(n_units);
+    for (int i = 0; i < n_units; ++i) {
+        char* b = m + table + i * each;
+        u[i].patch[0] = b;
+        u[i].patch[1] = b + round(patch);
+        u[i].plan = (int*)(b + 2 * round(patch));
+        u[i].plan_len = plan_ints(w, h);
+        u[i].pitch = pitch;
+        u[i].cap_w = w;
+        u[i].cap_h = h;
+        u[i].first = i * len;
+        u[i].n = len;
+    }
+    HIP_TRY(hipMemcpy(m, u.data(), sizeof(PatchUnit) * n_units, hipMemcpyHostToDevice));
+    s->n_units = n_units;
+    s->unit0 = u[0];
+    // blocks for the nodes of a straight fiber's band
+    s->patch_blocks = patch_blocks((long long)((len - 1) * p.l0 + 2.0 * s->rc + grow) *
+                                   (long long)(2.0 * s->rc + grow));
+    s->passes = true;
+    return FPD_OK;
 }
 
 int create_impl(const fpd_params* p, void* stream, void* fa, void* fb, size_t bytes_each,
@@ -760,11 +778,20 @@ size_t fpd_population_bytes(const fpd_params* p) {
     return (size_t)9 * (size_t)p->ny * padded_stride(p->nx) * storage_elem(p->storage);
 }
 
+// The passes of a simulation of its own (which is destroyed if that fails).
+static int create_passes(fpd_sim** out) {
+    const int rc = alloc_passes(*out, kMinPassNodes, 0.5);
+    if (rc) {
+        fpd_destroy(*out);
+        *out = nullptr;
+    }
+    return rc;
+}
+
 int fpd_create(const fpd_params* p, void* hip_stream, fpd_sim** out) {
     TraceRange range("fpd_create");
     const int rc = create_impl(p, hip_stream, nullptr, nullptr, 0, out);
-    if (rc == FPD_OK) alloc_passes(*out);
-    return rc;
+    return rc ? rc : create_passes(out);
 }
 
 int fpd_create_with_buffers(const fpd_params* p, void* hip_stream, void* f_a, void* f_b,
@@ -774,8 +801,7 @@ int fpd_create_with_buffers(const fpd_params* p, void* hip_stream, void* f_a, vo
     if (((uintptr_t)f_a | (uintptr_t)f_b) & 15)
         return fail(FPD_EINVAL, "buffers must be 16-byte aligned");
     const int rc = create_impl(p, hip_stream, f_a, f_b, bytes_each, out);
-    if (rc == FPD_OK) alloc_passes(*out);
-    return rc;
+    return rc ? rc : create_passes(out);
 }
 
 void fpd_destroy(fpd_sim* s) {
@@ -792,9 +818,7 @@ void fpd_destroy(fpd_sim* s) {
             if (b) (void)hipFree(b);
     if (s->bs) (void)hipFree(s->bs);
     if (s->rect_f) (void)hipFree(s->rect_f);
-    for (auto& b : s->patch)
-        if (b) (void)hipFree(b);
-    if (s->pass_part) (void)hipFree(s->pass_part);
+    if (s->units) (void)hipFree(s->units);
     if (s->row_phi) (void)hipFree(s->row_phi);
     if (s->rec) (void)hipFree(s->rec);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -1451,13 +1475,31 @@ struct fpd_batch {
     ItemRef* h_tile_items = nullptr;
     ItemRef* h_bead_items = nullptr;
     int cap_tiles = 0, cap_beads = 0;
+    // passes: per simulation the patch buffers and tiling, the patch and march items (the
+    // latter sorted by kind), and the stream and events that run the marches beside the rest
+    PassSim* d_pass = nullptr;
+    PassSim* h_pass = nullptr;
+    ItemRef* d_patch_items = nullptr;
+    ItemRef* h_patch_items = nullptr;
+    ItemRef* d_march_items = nullptr;
+    ItemRef* h_march_items = nullptr;
+    int cap_patch = 0, cap_march = 0;
+    int kind_count[kMarchKinds] = {};
+    bool passes = false;              // every active simulation takes passes
+    bool any_record = false;          // some of them record
+    bool graph_record = false;
+    hipStream_t side = nullptr;
+    hipEvent_t ev_fluid = nullptr, ev_fiber = nullptr;
     std::vector<int> table;  // entry index of table row r
     bool dirty = true;
     bool pending = false;        // steps enqueued by fpd_batch_launch, not yet waited for
     int64_t pending_steps = 0;
+    int pending_flips = 0;       // buffer changes of those steps
     hipGraphExec_t graph = nullptr;
     int graph_chunk = 0;
-    int graph_counts[3] = {0, 0, 0};  // counts the graph's grids were sized for
+    int graph_counts[5] = {0, 0, 0, 0, 0};  // counts the graph's grids were sized for
+    int graph_kinds[kMarchKinds] = {};
+    bool graph_passes = false;
     bool any_periodic = false;        // some active simulation has no walls
     bool graph_periodic = false;      // the kernel variant the graph was captured with
 };
@@ -1490,6 +1532,67 @@ size_t footprint_of(const fpd_params* p) {
     return 2 * pop + rect + sizeof(BeadState);
 }
 
+// Rows of a march tile in a batch: as many tiles as a single lattice's march, at least
+// kBatchMarchRows rows each.
+constexpr int kBatchMarchTiles = 2048;
+constexpr int kBatchMarchRows = 24;
+
+// Whether every active simulation takes passes, and then the counts of their items and each
+// one's tiling (h_pass; h_args filled).
+void batch_plan_passes(fpd_batch* b) {
+    const int r = b->h_counts[0];
+    b->h_counts[3] = b->h_counts[4] = 0;
+    for (int& k : b->kind_count) k = 0;
+    b->any_record = false;
+    b->passes = r > 0;
+    long long strip_rows = 0;
+    for (int q = 0; q < r; ++q) {
+        const fpd_sim* s = b->entries[b->table[q]].sim;
+        if (!use_passes(s) || has_ev(s)) {  // (the forces between fibers: batch_forces_kernel)
+            b->passes = false;
+            return;
+        }
+        const int cols = march_cols(s->p.storage, s->L);
+        strip_rows += (long long)((s->L.nx + cols - 1) / cols) * s->L.ny;
+    }
+    const long long rows = std::max<long long>(kBatchMarchRows, strip_rows / kBatchMarchTiles);
+    for (int q = 0; q < r; ++q) {
+        const fpd_sim* s = b->entries[b->table[q]].sim;
+        const StepArgs& a = b->h_args[2 * q];
+        PassSim& p = b->h_pass[q];
+        p.unit0 = s->unit0;
+        p.units = s->units;
+        p.n_units = s->n_units;
+        p.blocks = s->patch_blocks;
+        b->h_counts[3] += p.n_units * (p.blocks + 1);
+        if (s->rec) b->any_record = true;
+        const int cols = march_cols(s->p.storage, s->L);
+        p.strips = (s->L.nx + cols - 1) / cols;
+        const int runs = (int)std::max<long long>(1, (s->L.ny + rows / 2) / rows);
+        p.seg_rows = (s->L.ny + runs - 1) / runs;
+        const int n = p.strips * ((s->L.ny + p.seg_rows - 1) / p.seg_rows);
+        b->kind_count[march_kind(s->p.storage, s->L, a.gx != 0.0 || a.gy != 0.0)] += n;
+        b->h_counts[4] += n;
+    }
+}
+
+void batch_fill_pass_items(fpd_batch* b) {
+    int patch = 0, at[kMarchKinds], first = 0;
+    for (int k = 0; k < kMarchKinds; ++k) {
+        at[k] = first;
+        first += b->kind_count[k];
+    }
+    for (int q = 0; q < b->h_counts[0]; ++q) {
+        const fpd_sim* s = b->entries[b->table[q]].sim;
+        const StepArgs& a = b->h_args[2 * q];
+        const PassSim& p = b->h_pass[q];
+        for (int t = 0; t < p.n_units * (p.blocks + 1); ++t) b->h_patch_items[patch++] = ItemRef{q, t};
+        int& m = at[march_kind(s->p.storage, s->L, a.gx != 0.0 || a.gy != 0.0)];
+        const int n = p.strips * ((s->L.ny + p.seg_rows - 1) / p.seg_rows);
+        for (int t = 0; t < n; ++t) b->h_march_items[m++] = ItemRef{q, t};
+    }
+}
+
 // Rebuild the work tables for the active simulations (call with the stream idle).
 int batch_rebuild(fpd_batch* b) {
     b->table.clear();
@@ -1516,9 +1619,13 @@ int batch_rebuild(fpd_batch* b) {
     b->any_periodic = false;
     for (int q = 0; q < r; ++q)
         if (b->h_args[2 * q].L.periodic) b->any_periodic = true;
-    if (b->graph && (b->graph_counts[0] != r || b->graph_counts[1] != tiles ||
-                     b->graph_counts[2] != beads || b->graph_periodic != b->any_periodic))
-        batch_drop_graph(b);  // its grids or kernel variant no longer match the tables
+    batch_plan_passes(b);
+    const int patches = b->h_counts[3], marches = b->h_counts[4];
+    if (b->graph && (memcmp(b->graph_counts, b->h_counts, sizeof b->graph_counts) != 0 ||
+                     memcmp(b->graph_kinds, b->kind_count, sizeof b->graph_kinds) != 0 ||
+                     b->graph_periodic != b->any_periodic || b->graph_passes != b->passes ||
+                     b->graph_record != b->any_record))
+        batch_drop_graph(b);  // its grids or kernel variants no longer match the tables
     // item tables (grown geometrically; a new pointer drops the graph)
     auto grow = [&](int need, int& cap, ItemRef*& d, ItemRef*& h) -> int {
         if (need <= cap) return FPD_OK;
@@ -1538,7 +1645,19 @@ int batch_rebuild(fpd_batch* b) {
     };
     int rc = grow(tiles, b->cap_tiles, b->d_tile_items, b->h_tile_items);
     if (rc == FPD_OK) rc = grow(beads, b->cap_beads, b->d_bead_items, b->h_bead_items);
+    if (rc == FPD_OK) rc = grow(patches, b->cap_patch, b->d_patch_items, b->h_patch_items);
+    if (rc == FPD_OK) rc = grow(marches, b->cap_march, b->d_march_items, b->h_march_items);
     if (rc) return rc;
+    if (b->passes) {
+        batch_fill_pass_items(b);
+        HIP_TRY(hipMemcpyAsync(b->d_pass, b->h_pass, sizeof(PassSim) * r, hipMemcpyHostToDevice,
+                               b->stream));
+        if (patches > 0)
+            HIP_TRY(hipMemcpyAsync(b->d_patch_items, b->h_patch_items, sizeof(ItemRef) * patches,
+                                   hipMemcpyHostToDevice, b->stream));
+        HIP_TRY(hipMemcpyAsync(b->d_march_items, b->h_march_items, sizeof(ItemRef) * marches,
+                               hipMemcpyHostToDevice, b->stream));
+    }
     for (int q = 0; q < r; ++q) {
         for (int t = b->h_tile_off[q]; t < b->h_tile_off[q + 1]; ++t)
             b->h_tile_items[t] = ItemRef{q, t - b->h_tile_off[q]};
@@ -1557,25 +1676,92 @@ int batch_rebuild(fpd_batch* b) {
         HIP_TRY(hipMemcpyAsync(b->d_states, b->h_states, sizeof(BeadState*) * r,
                                hipMemcpyHostToDevice, b->stream));
     }
-    HIP_TRY(hipMemcpyAsync(b->d_counts, b->h_counts, sizeof(int) * 3, hipMemcpyHostToDevice,
+    HIP_TRY(hipMemcpyAsync(b->d_counts, b->h_counts, sizeof(int) * 5, hipMemcpyHostToDevice,
                            b->stream));
     b->dirty = false;
     return FPD_OK;
 }
 
+BatchArgs batch_args(const fpd_batch* b, int gpar, int wpar, int t) {
+    return BatchArgs{b->d_args, b->d_tile_items, b->d_bead_items, b->d_counts, gpar,
+                     b->d_pass, b->d_patch_items, b->d_march_items, wpar, t};
+}
+
 int batch_enqueue(fpd_batch* b, int gpar) {
-    BatchArgs a{b->d_args, b->d_tile_items, b->d_bead_items, b->d_counts, gpar};
     const dim3 block(b->launch.block_x, b->launch.block_y);
-    HIP_TRY(launch_batch_step(b->storage, a, block, b->launch.rows_per_thread, b->h_counts,
-                              b->any_periodic, b->stream));
+    HIP_TRY(launch_batch_step(b->storage, batch_args(b, gpar, gpar, 0), block,
+                              b->launch.rows_per_thread, b->h_counts, b->any_periodic,
+                              b->stream));
+    return FPD_OK;
+}
+
+// n passes from buffer gpar and window slot wpar (relative to the tables), as enqueue_pass
+// orders them for one simulation.
+int batch_enqueue_passes(fpd_batch* b, int gpar, int wpar, int64_t n) {
+    if (n <= 0) return FPD_OK;
+    HIP_TRY(launch_batch_pass_setup(batch_args(b, gpar, wpar, 1), b->h_counts[0], b->stream));
+    HIP_TRY(hipEventRecord(b->ev_fiber, b->stream));
+    for (int64_t i = 0; i < n; ++i) {
+        HIP_TRY(hipStreamWaitEvent(b->side, b->ev_fiber, 0));
+        HIP_TRY(launch_batch_march(b->storage, batch_args(b, gpar, wpar, 1), b->kind_count,
+                                   b->side));
+        if (i > 0) HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_fluid, 0));
+        HIP_TRY(hipEventRecord(b->ev_fluid, b->side));
+        for (int t = 1; t <= kPassSteps; ++t) {
+            HIP_TRY(launch_batch_patch(b->storage, batch_args(b, gpar, wpar, t), b->h_counts,
+                                       b->any_periodic, b->any_record, b->stream));
+            wpar = 1 - wpar;
+        }
+        HIP_TRY(hipEventRecord(b->ev_fiber, b->stream));
+        gpar = 1 - gpar;
+    }
+    HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_fluid, 0));
+    return FPD_OK;
+}
+
+// The single steps and the passes that n steps are taken in (single steps first); a chunk's
+// passes are even in number, so a replayed chunk returns to the buffer it started from.
+void batch_split_steps(const fpd_batch* b, int64_t n, bool chunk, int64_t* singles,
+                       int64_t* passes) {
+    *passes = b->passes ? n / kPassSteps : 0;
+    if (chunk) *passes &= ~(int64_t)1;
+    *singles = n - *passes * kPassSteps;
+}
+
+int batch_enqueue_steps(fpd_batch* b, int64_t n, bool chunk) {
+    int64_t singles = 0, passes = 0;
+    batch_split_steps(b, n, chunk, &singles, &passes);
+    for (int64_t i = 0; i < singles; ++i) {
+        int rc = batch_enqueue(b, (int)(i & 1));
+        if (rc) return rc;
+    }
+    return batch_enqueue_passes(b, (int)(singles & 1), (int)(singles & 1), passes);
+}
+
+// The stream of the marches and the events, on the device of the batch's stream.
+int batch_ensure_side(fpd_batch* b) {
+    if (!b->passes || (b->side && b->ev_fluid && b->ev_fiber)) return FPD_OK;
+    hipDevice_t dev = 0;
+    int cur = 0;
+    HIP_TRY(hipStreamGetDevice(b->stream, &dev));
+    HIP_TRY(hipGetDevice(&cur));
+    if (dev != cur) HIP_TRY(hipSetDevice(dev));
+    hipError_t e = hipSuccess;
+    if (!b->side) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+    if (e == hipSuccess && !b->ev_fluid)
+        e = hipEventCreateWithFlags(&b->ev_fluid, hipEventDisableTiming);
+    if (e == hipSuccess && !b->ev_fiber)
+        e = hipEventCreateWithFlags(&b->ev_fiber, hipEventDisableTiming);
+    if (dev != cur) (void)hipSetDevice(cur);
+    if (e != hipSuccess)
+        return fail(FPD_EDEVICE, "batch pass stream or events: %s", hipGetErrorString(e));
     return FPD_OK;
 }
 
 int batch_build_graph(fpd_batch* b, int chunk) {
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    int rc = FPD_OK;
-    for (int i = 0; i < chunk && rc == FPD_OK; ++i) rc = batch_enqueue(b, i & 1);
+    const int rc = batch_enqueue_steps(b, chunk, true);
     hipError_t e = hipStreamEndCapture(b->stream, &g);
     if (rc != FPD_OK) {
         if (g) (void)hipGraphDestroy(g);
@@ -1588,7 +1774,10 @@ int batch_build_graph(fpd_batch* b, int chunk) {
     e = hipGraphUpload(b->graph, b->stream);
     if (e != hipSuccess) return fail(FPD_EDEVICE, "batch graph upload: %s", hipGetErrorString(e));
     b->graph_chunk = chunk;
-    for (int k = 0; k < 3; ++k) b->graph_counts[k] = b->h_counts[k];
+    memcpy(b->graph_counts, b->h_counts, sizeof b->graph_counts);
+    memcpy(b->graph_kinds, b->kind_count, sizeof b->graph_kinds);
+    b->graph_passes = b->passes;
+    b->graph_record = b->any_record;
     b->graph_periodic = b->any_periodic;
     return FPD_OK;
 }
@@ -1632,15 +1821,17 @@ int fpd_batch_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t storage
     }
     const size_t n = (size_t)max_slots;
     bool ok = hipMalloc((void**)&b->d_args, sizeof(StepArgs) * 2 * n) == hipSuccess &&
-              hipMalloc((void**)&b->d_counts, sizeof(int) * 3) == hipSuccess &&
+              hipMalloc((void**)&b->d_counts, sizeof(int) * 5) == hipSuccess &&
               hipMalloc((void**)&b->d_states, sizeof(BeadState*) * n) == hipSuccess &&
               hipMalloc((void**)&b->d_health, sizeof(unsigned) * n) == hipSuccess &&
               hipHostMalloc((void**)&b->h_args, sizeof(StepArgs) * 2 * n, 0) == hipSuccess &&
               hipHostMalloc((void**)&b->h_tile_off, sizeof(int) * (n + 1), 0) == hipSuccess &&
               hipHostMalloc((void**)&b->h_bead_off, sizeof(int) * (n + 1), 0) == hipSuccess &&
-              hipHostMalloc((void**)&b->h_counts, sizeof(int) * 3, 0) == hipSuccess &&
+              hipHostMalloc((void**)&b->h_counts, sizeof(int) * 5, 0) == hipSuccess &&
               hipHostMalloc((void**)&b->h_states, sizeof(BeadState*) * n, 0) == hipSuccess &&
-              hipHostMalloc((void**)&b->h_health, sizeof(unsigned) * n, 0) == hipSuccess;
+              hipHostMalloc((void**)&b->h_health, sizeof(unsigned) * n, 0) == hipSuccess &&
+              hipMalloc((void**)&b->d_pass, sizeof(PassSim) * n) == hipSuccess &&
+              hipHostMalloc((void**)&b->h_pass, sizeof(PassSim) * n, 0) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         return bail(fail(FPD_ENOMEM, "batch table allocation failed"));
@@ -1654,6 +1845,7 @@ int fpd_batch_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t storage
 void fpd_batch_destroy(fpd_batch* b) {
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
+    if (b->side) (void)hipStreamSynchronize(b->side);
     batch_drop_graph(b);
     for (auto& e : b->entries) fpd_destroy(e.sim);
     b->entries.clear();
@@ -1671,6 +1863,15 @@ void fpd_batch_destroy(fpd_batch* b) {
     (void)hipHostFree(b->h_counts);
     (void)hipHostFree(b->h_states);
     (void)hipHostFree(b->h_health);
+    (void)hipFree(b->d_pass);
+    (void)hipFree(b->d_patch_items);
+    (void)hipFree(b->d_march_items);
+    (void)hipHostFree(b->h_pass);
+    (void)hipHostFree(b->h_patch_items);
+    (void)hipHostFree(b->h_march_items);
+    if (b->ev_fluid) (void)hipEventDestroy(b->ev_fluid);
+    if (b->ev_fiber) (void)hipEventDestroy(b->ev_fiber);
+    if (b->side) (void)hipStreamDestroy(b->side);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
 }
@@ -1710,7 +1911,8 @@ int fpd_batch_add(fpd_batch* b, const fpd_params* p, const double* R, int64_t n_
     fpd_sim* s = nullptr;
     rc = create_impl(p, b->stream, nullptr, nullptr, 0, &s);
     if (rc) return rc;
-    rc = fpd_set_launch(s, &b->launch);
+    rc = alloc_passes(s, 0, 1.0);
+    if (rc == FPD_OK) rc = fpd_set_launch(s, &b->launch);
     if (rc == FPD_OK && p->n_beads > 0) rc = fpd_init_fiber(s, R);
     if (rc) {
         fpd_destroy(s);
@@ -1749,6 +1951,8 @@ int fpd_batch_launch(fpd_batch* b, int64_t max_steps, int64_t* advanced) {
         rc = batch_rebuild(b);
         if (rc) return rc;
     }
+    rc = batch_ensure_side(b);
+    if (rc) return rc;
     int64_t left = steps;
     const int chunk = b->launch.graph_chunk;
     if (left >= chunk) {
@@ -1762,10 +1966,11 @@ int fpd_batch_launch(fpd_batch* b, int64_t max_steps, int64_t* advanced) {
             left -= chunk;
         }
     }
-    for (int i = 0; left > 0; --left, ++i) {
-        rc = batch_enqueue(b, i & 1);
-        if (rc) return rc;
-    }
+    rc = batch_enqueue_steps(b, left, false);
+    if (rc) return rc;
+    int64_t singles = 0, passes = 0;
+    batch_split_steps(b, left, false, &singles, &passes);
+    b->pending_flips = (int)((singles + passes) & 1);
     // health of every simulation, read back once the steps are done
     const int rows = (int)b->table.size();
     HIP_TRY(health_gather(b->d_states, b->d_health, rows, b->stream));
@@ -1791,7 +1996,8 @@ int fpd_batch_wait(fpd_batch* b) {
         BatchEntry& e = b->entries[b->table[r]];
         e.remaining -= steps;
         e.sim->steps += steps;
-        if (steps & 1) flip(e.sim);
+        if (b->pending_flips) e.sim->cur = 1 - e.sim->cur;
+        if (steps & 1) e.sim->wpar = 1 - e.sim->wpar;
         if (b->h_health[r]) {
             e.status = FPD_SIM_FAILED;
         } else if (e.remaining == 0) {
@@ -1799,7 +2005,7 @@ int fpd_batch_wait(fpd_batch* b) {
         }
         if (e.status != FPD_SIM_ACTIVE) b->dirty = true;
     }
-    if (steps & 1) b->dirty = true;
+    if ((steps & 1) || b->pending_flips) b->dirty = true;
     return FPD_OK;
 }
 

@@ -101,3 +101,13 @@ def test_recording_and_checkpoint_between_passes(tmp_path):
             out.append((sim.populations(), *sim.beads(), sim.record()))
     for x, y in zip(*out):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("storage", STORAGE)
+def test_passes_of_several_fibers(storage):
+    """One patch per fiber: apart, close enough that their partitions share nodes, and across
+    the periodic edge; with the excluded volume on."""
+    w = workloads.fiber_suspension(n_fibers=3, beads=6, nx=2048, ny=512, radius=3.0,
+                                   storage=storage, seed=11)
+    centres = ((300.0, 200.0, 0.4), (322.0, 215.0, 1.9), (2046.0, 300.0, 0.1))
+    same(w.with_(centres=centres, ev_k=1e-3, ev_range=9.0))
