@@ -342,8 +342,8 @@ __device__ inline PatchUnit pick_unit(const PatchUnit& unit0, const PatchUnit* t
     if (i == 0) return unit0;
     const ConstPatchUnit* c = (const ConstPatchUnit*)table + i;
     PatchUnit u;
-    u.patch[0] = c->patch[0];
-    u.patch[1] = c->patch[1];
+    u.patch = c->patch;
+    u.patch_bytes = c->patch_bytes;
     u.plan = c->plan;
     u.plan_len = c->plan_len;
     u.pitch = c->pitch;
@@ -351,6 +351,7 @@ __device__ inline PatchUnit pick_unit(const PatchUnit& unit0, const PatchUnit* t
     u.cap_h = c->cap_h;
     u.first = c->first;
     u.n = c->n;
+    u.tile_h = c->tile_h;
     return u;
 }
 

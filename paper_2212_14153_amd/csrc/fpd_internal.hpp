@@ -92,18 +92,24 @@ constexpr int kMaxUnits = 64;      // fibers of a simulation that takes passes (
 // rows of `pitch` nodes side by side, cap_w x cap_h nodes at most) and two plans (by the
 // buffer a pass starts from).
 struct PatchUnit {
-    void* patch[2];
+    char* patch;                   // the first buffer; the second patch_bytes further
+    long long patch_bytes;
     int* plan;                     // [2][plan_ints]
     int plan_len;                  // plan_ints(cap_w, cap_h)
     int pitch, cap_w, cap_h;
     int first, n;                  // its beads
+    int tile_h;                    // rows of a tile: kPatchY times the rows of a thread
 };
 // A plan: the patch rectangle (first column, width, first row, height: the partition grown by
 // the kPassSteps - 1 nodes the first step needs around it) and the number of its tiles that
 // any step updates; each bead's support box when the plan was made; per step t = 1 ..
 // kPassSteps and patch row the columns [lo, hi) that the step updates, relative to the
 // rectangle (the last step's are the partition itself); and those tiles (ty << 16 | tx).
-constexpr int kPatchX = 32, kPatchY = 8;   // nodes of a tile of the patch kernel
+constexpr int kPatchX = 32, kPatchY = 8;   // threads of a tile of the patch kernel
+constexpr int kPatchRows = 1;              // rows of a thread: one simulation
+// and a batch, where the tiles fill the device several times over and a block's fixed chain of
+// loads and barriers counts (float32 sweep: 142.7 / 137.3 / 142.2 ms per 1000 steps with 1 / 2 / 4)
+constexpr int kBatchPatchRows = 2;
 constexpr int kPlanBoxes = 8;
 constexpr int kPlanRows = kPlanBoxes + 4 * kMaxBeads;
 constexpr int plan_tiles_at(int cap_h) { return kPlanRows + 2 * kPassSteps * cap_h; }
@@ -253,7 +259,7 @@ hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, 
 bool march_ok(int storage, const Lattice& L);
 hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st);
 // Blocks of the patch kernel for a unit whose partition covers about `nodes` nodes.
-int patch_blocks(long long nodes);
+int patch_blocks(long long nodes, int tile_h);
 // The same for the simulations of a batch: march_kind and march_cols (columns of a march
 // tile) of a lattice; the partitions; step b.t of the patches and beads; the marches, kind by
 // kind (kind_count items each).

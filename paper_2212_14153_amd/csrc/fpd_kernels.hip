@@ -846,7 +846,7 @@ __global__ void __launch_bounds__(256) fiber_kernel(StepArgs a) {
 __device__ inline View patch_view(const PatchUnit& u, PlanPtr plan, const Lattice& L,
                                   const void* whole, int which) {
     if (which < 0) return View{whole, 0, 0, L.stride, L.plane};
-    return View{which ? u.patch[1] : u.patch[0], plan[0], plan[2], 9 * u.pitch, u.pitch};
+    return View{u.patch + which * u.patch_bytes, plan[0], plan[2], 9 * u.pitch, u.pitch};
 }
 // The patch buffer step t reads (t - 1 wrote it) and the one it writes; -1: the lattice's.
 __device__ inline int patch_src(int t) { return t > 1 ? (t & 1) : -1; }
@@ -995,9 +995,9 @@ __device__ inline void make_plan(const StepArgs& a, const PatchUnit& u, int* pla
             }
         }
         // the tiles of the first step (kPlanRun is a multiple of a tile's rows)
-        for (int ty = tid; ty < (run + kPatchY - 1) / kPatchY; ty += nt) {
+        for (int ty = tid; ty < (run + u.tile_h - 1) / u.tile_h; ty += nt) {
             int l = 0x3fffffff, h = -0x3fffffff;
-            for (int i = ty * kPatchY; i < min((ty + 1) * kPatchY, run) + 2 * E; ++i) {
+            for (int i = ty * u.tile_h; i < min((ty + 1) * u.tile_h, run) + 2 * E; ++i) {
                 l = min(l, sm.lo[i]);
                 h = max(h, sm.hi[i]);
             }
@@ -1014,13 +1014,13 @@ __device__ inline void make_plan(const StepArgs& a, const PatchUnit& u, int* pla
             const int t0 = l / kPatchX, t1 = (h - 1) / kPatchX;
             const int at = atomicAdd(&sm.tiles, t1 - t0 + 1);
             for (int tx = t0; tx <= t1; ++tx)
-                tiles[at + tx - t0] = ((r0 / kPatchY + ty) << 16) | tx;
+                tiles[at + tx - t0] = ((r0 / u.tile_h + ty) << 16) | tx;
         }
     }
     __syncthreads();
     if (tid == 0) plan[4] = sm.tiles;
 }
-static_assert(kPlanRun % kPatchY == 0, "a run of plan rows is whole tiles");
+static_assert(kPlanRun % (4 * kPatchY) == 0, "a run of plan rows is whole tiles");
 
 // The next pass's plan, by a block of the bead kernel of step kPassSteps - 1, beside the beads:
 // each position is read as it was before or after its update, either at most two steps from
@@ -1036,7 +1036,8 @@ __global__ void __launch_bounds__(256) pass_setup_kernel(StepArgs a, PassArgs q)
 }
 
 // The patch and bead kernels of a pass are the latency chain beside the march: their waves
-// are issued ahead of its waves on a SIMD.
+// are issued ahead of its waves on a SIMD (without, the float32 sweep took 151.7 against 137.3 ms
+// per 1000 steps, the shape channels 131.3 against 114.7 per 2000).
 __device__ inline void chain_priority() { __builtin_amdgcn_s_setprio(3); }
 
 // Step q.t of a pass for the nodes around one fiber, one node per thread in tiles of
@@ -1045,7 +1046,7 @@ __device__ inline void chain_priority() { __builtin_amdgcn_s_setprio(3); }
 // tile of its plan, and one more for the bookkeeping.  Nodes that two fibers' partitions
 // share are computed by both, alike.  32 x 8 nodes: a fiber at an angle leaves out more of
 // narrow tiles, and a tile gathers fewer beads than 64 x 4 ones.
-template <int ST, int BC>
+template <int ST, int BC, int ROWS>
 __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
                                   const Window& win, int tx, int ty, TileLds& lds) {
     using Cd = Codec<ST>;
@@ -1054,52 +1055,66 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     constexpr bool kScaled = ST == FPD_F16DEV;
     const bool per = periodic_of(BC, a);
     const int nx = a.L.nx, ny = a.L.ny;
-    const int cx = tx * kPatchX, cy = ty * kPatchY;
-    const int cw = min(kPatchX, plan[1] - cx), ch = min(kPatchY, plan[3] - cy);
+    const int cx = tx * kPatchX, cy = ty * (ROWS * kPatchY);
+    const int cw = min(kPatchX, plan[1] - cx), ch = min(ROWS * kPatchY, plan[3] - cy);
     int x0 = plan[0] + cx, y0 = plan[2] + cy;
     if (x0 >= nx) x0 -= nx;
     if (per && y0 >= ny) y0 -= ny;
     const int lx = threadIdx.x % kPatchX, ly = threadIdx.x / kPatchX;
-    bool in = ly < ch && lx < cw;
-    if (in) {
-        const int2 c = plan_row(u, plan, t, cy + ly);
-        in = cx + lx >= c.x && cx + lx < c.y;
-    }
-    if (t > 1 && !__syncthreads_or(in)) return;  // a tile of an earlier step's ring
-    int x = x0 + lx, y = y0 + ly;
+    int x = x0 + lx;
     if (x >= nx) x -= nx;
-    if (per && y >= ny) y -= ny;
+    bool in[ROWS];
+    int y[ROWS];
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int l = ly + r * kPatchY;
+        in[r] = l < ch && lx < cw;
+        if (in[r]) {
+            const int2 c = plan_row(u, plan, t, cy + l);
+            in[r] = cx + lx >= c.x && cx + lx < c.y;
+        }
+        any = any || in[r];
+        y[r] = y0 + l;
+        if (per && y[r] >= ny) y[r] -= ny;
+    }
+    if (t > 1 && !__syncthreads_or(any)) return;  // a tile of an earlier step's ring
     const T u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
-    T g[9];
-    if (in)
-        pull_view<Cd, true>(patch_view(u, plan, a.L, a.src, patch_src(t)), nx, ny, x, y, per, u6,
-                            g);
+    const View v = patch_view(u, plan, a.L, a.src, patch_src(t));
+    T g[ROWS][9];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (in[r]) pull_view<Cd, true>(v, nx, ny, x, y[r], per, u6, g[r]);
     TileBead<T>* sB = (TileBead<T>*)lds.beads;
     const int nb = gather_beads<T>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
                                    lds.bonds, false);
-    if (!in) return;
-    T Fx = (T)a.gx, Fy = (T)a.gy, s_nu = (T)a.s_nu_f, s_q = (T)a.s_q_f;
-    const T s_e = (T)a.s_e, s_eps = (T)a.s_eps;
-    if (nb > 0)
-        fiber_node<T>(a, per, sB, nb, x, y, win.x0, win.y0, win.w, win.h, Fx, Fy, s_nu, s_q);
-    const View v = patch_view(u, plan, a.L, a.dst, patch_dst(t));
-    int c = x - v.ox, w = y - v.oy;
-    if (c < 0) c += nx;
-    if (w < 0) w += ny;
-    S* o = (S*)v.p + (long long)w * v.stride + c;
-    // one collision for every node: with F = 0 it gives the bits of the unforced one
-    if constexpr (kScaled) {
-        const T z = mrt_collide_scaled_open<T>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
-        *(uint16_t*)o = (uint16_t)narrow_fma4(z, g[0]);
-    } else {
-        mrt_collide<T>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
-    }
+    const View o = patch_view(u, plan, a.L, a.dst, patch_dst(t));
 #pragma unroll
-    for (int k = kScaled ? 1 : 0; k < 9; ++k) {
-        if constexpr (sizeof(S) == 2)
-            ((uint16_t*)o)[k * v.plane] = (uint16_t)Cd::pack2_scaled(g[k], g[k]);
-        else
-            o[k * v.plane] = g[k];
+    for (int r = 0; r < ROWS; ++r) {
+        if (!in[r]) continue;
+        T Fx = (T)a.gx, Fy = (T)a.gy, s_nu = (T)a.s_nu_f, s_q = (T)a.s_q_f;
+        const T s_e = (T)a.s_e, s_eps = (T)a.s_eps;
+        if (nb > 0)
+            fiber_node<T>(a, per, sB, nb, x, y[r], win.x0, win.y0, win.w, win.h, Fx, Fy, s_nu,
+                          s_q);
+        int c = x - o.ox, w = y[r] - o.oy;
+        if (c < 0) c += nx;
+        if (w < 0) w += ny;
+        S* d = (S*)o.p + (long long)w * o.stride + c;
+        // one collision for every node: with F = 0 it gives the bits of the unforced one
+        if constexpr (kScaled) {
+            const T z = mrt_collide_scaled_open<T>(g[r], Fx, Fy, s_nu, s_q, s_e, s_eps);
+            *(uint16_t*)d = (uint16_t)narrow_fma4(z, g[r][0]);
+        } else {
+            mrt_collide<T>(g[r], Fx, Fy, s_nu, s_q, s_e, s_eps);
+        }
+#pragma unroll
+        for (int k = kScaled ? 1 : 0; k < 9; ++k) {
+            if constexpr (sizeof(S) == 2)
+                ((uint16_t*)d)[k * o.plane] = (uint16_t)Cd::pack2_scaled(g[r][k], g[r][k]);
+            else
+                d[k * o.plane] = g[r][k];
+        }
     }
 }
 
@@ -1120,7 +1135,7 @@ __device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanP
     }
 }
 
-template <int ST, int BC>
+template <int ST, int BC, int ROWS>
 __device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int blocks, int slot,
                                    int t, int k, bool first, TileLds& lds) {
     const Window win = tile_window(a);
@@ -1133,7 +1148,7 @@ __device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int bl
     const int tiles = plan[4];
     for (int i = k; i < tiles; i += blocks) {
         const int e = list[i];
-        patch_tile<ST, BC>(a, u, plan, t, win, e & 0xffff, e >> 16, lds);
+        patch_tile<ST, BC, ROWS>(a, u, plan, t, win, e & 0xffff, e >> 16, lds);
         __syncthreads();  // the next tile's beads overwrite this one's
     }
 }
@@ -1143,7 +1158,7 @@ __global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, Pa
     __shared__ TileLds lds;
     chain_priority();
     const PatchUnit u = pick_unit(q.unit0, q.units, blockIdx.y);
-    patch_block<ST, BC>(a, u, q.blocks, q.slot, q.t, blockIdx.x, blockIdx.y == 0, lds);
+    patch_block<ST, BC, kPatchRows>(a, u, q.blocks, q.slot, q.t, blockIdx.x, blockIdx.y == 0, lds);
 }
 
 // The passes of a batch: the plans, one block per simulation; the patch tiles and the beads of
@@ -1170,7 +1185,7 @@ __global__ void __launch_bounds__(kPatchX * kPatchY) batch_patch_kernel(BatchArg
     const StepArgs a = load_pass_args(b, e.sim);
     const PassSim p = load_pass(b.pass, e.sim);
     const int per = p.blocks + 1, unit = e.local / per;
-    patch_block<ST, BC>(a, pick_unit(p.unit0, p.units, unit), p.blocks, b.gpar, b.t,
+    patch_block<ST, BC, kBatchPatchRows>(a, pick_unit(p.unit0, p.units, unit), p.blocks, b.gpar, b.t,
                         e.local - unit * per, unit == 0, lds);
 }
 
@@ -1446,9 +1461,11 @@ __global__ void __launch_bounds__(kBatchBeadBlock) batch_bead_kernel(BatchArgs b
                                                         scratch, s_R);
 }
 
-// The beads of step b.t of a batch's passes.
+// The beads of step b.t of a batch's passes: 512 threads, as alone (the block of a large bead,
+// up to 101 x 101 nodes in the sweeps, is what the kernel waits for): driven-particle boxes 142.7
+// -> 129.4 ms per 2000 steps, float16 sweep 146.1 -> 140.7 per 1000, the float32 ones unchanged.
 template <int ST>
-__global__ void __launch_bounds__(kBatchBeadBlock) batch_patch_bead_kernel(BatchArgs b) {
+__global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs b) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
     __shared__ double s_R[2];
     __shared__ PlanLds plan;
@@ -1471,7 +1488,7 @@ __global__ void __launch_bounds__(kBatchBeadBlock) batch_patch_bead_kernel(Batch
     const PassSim p = load_pass(b.pass, e.sim);
     const int unit = e.local / a.fib.chain_len;
     const PatchUnit u = pick_unit(p.unit0, p.units, unit);
-    bead_block<ST, kBatchBeadVelBatch, kBatchBeadBlock, true>(
+    bead_block<ST, kBatchBeadVelBatch, kBeadBlock, true>(
         a, e.local, 1, 1 - a.parity, scratch, s_R,
         patch_view(u, unit_plan(u, b.gpar), a.L, a.dst, patch_dst(b.t)));
 }
@@ -2009,9 +2026,9 @@ hipError_t launch_pass_setup(const StepArgs& a, const PassArgs& q, hipStream_t s
     return hipGetLastError();
 }
 
-int patch_blocks(long long nodes) {
+int patch_blocks(long long nodes, int tile_h) {
     // a fiber at 45 degrees takes about twice the tiles of its band's area
-    const long long n = 2 * nodes / (kPatchX * kPatchY) + 8;
+    const long long n = 2 * nodes / (kPatchX * tile_h) + 8;
     return (int)std::min<long long>(n, 1024);
 }
 
@@ -2126,7 +2143,7 @@ static hipError_t launch_batch_patch_t(const BatchArgs& b, const int counts[5], 
         hipLaunchKernelGGL((batch_patch_kernel<ST, kWalls>), grid, block, 0, st, b);
     const int plans = b.t == kPassSteps - 1 ? counts[0] : 0;
     hipLaunchKernelGGL((batch_patch_bead_kernel<ST>), dim3(counts[2] + plans),
-                       dim3(kBatchBeadBlock), 0, st, b);
+                       dim3(kBeadBlock), 0, st, b);
     return hipGetLastError();
 }
 

@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <stdlib.h>
 
 #include "fpd_march.hpp"
 
@@ -65,8 +64,7 @@ constexpr int kMarchMinRows = 16;
 template <int ST, int C, int OL>
 static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream_t st) {
     const int strips = (a.L.nx + OL * C - 1) / (OL * C);
-    const int MW = getenv("MW") ? atoi(getenv("MW")) : kMarchWaves;
-    const int runs = std::max(1, std::min(MW / strips, a.L.ny / kMarchMinRows));
+    const int runs = std::max(1, std::min(kMarchWaves / strips, a.L.ny / kMarchMinRows));
     const MarchArgs m = march_args(a, q.units, q.n_units, q.slot, strips,
                                    (a.L.ny + runs - 1) / runs);
     const int segs = (a.L.ny + m.seg_rows - 1) / m.seg_rows;

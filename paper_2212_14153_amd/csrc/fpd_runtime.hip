@@ -591,13 +591,16 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
 // the patch and bead kernels one after the other take longer than a whole step's two
 // (1024 x 256, float32: 20.9 against 16.5 us per step; 777 x 333: 19.3 against 17.4), while at
 // 2042 x 611 in float16 deviations passes gain (25.3 against 28.4).
-constexpr long long kMinPassNodes = 1LL << 20;
+#ifndef MPN
+#define MPN (1LL << 20)
+#endif
+constexpr long long kMinPassNodes = MPN;
 
 // The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
 // at most kMaxUnits fibers, and the patches together span at most `share` of the lattice's
 // nodes.  A simulation whose buffers cannot be allocated runs without passes.  Allocated with
 // the simulation, so that a step never allocates.
-int alloc_passes(fpd_sim* s, long long min_nodes, double share) {
+int alloc_passes(fpd_sim* s, long long min_nodes, double share, int rows) {
     const fpd_params& p = s->p;
     const long long nodes = (long long)p.nx * p.ny;
     if (!march_ok(p.storage, s->L) || nodes < min_nodes) return FPD_OK;
@@ -628,8 +631,9 @@ int alloc_passes(fpd_sim* s, long long min_nodes, double share) {
     std::vector<PatchUnit> u(n_units);
     for (int i = 0; i < n_units; ++i) {
         char* b = m + table + i * each;
-        u[i].patch[0] = b;
-        u[i].patch[1] = b + round(patch);
+        u[i].patch = b;
+        u[i].patch_bytes = (long long)round(patch);
+        u[i].tile_h = kPatchY * rows;
         u[i].plan = (int*)(b + 2 * round(patch));
         u[i].plan_len = plan_ints(w, h);
         u[i].pitch = pitch;
@@ -643,7 +647,8 @@ int alloc_passes(fpd_sim* s, long long min_nodes, double share) {
     s->unit0 = u[0];
     // blocks for the nodes of a straight fiber's band
     s->patch_blocks = patch_blocks((long long)((len - 1) * p.l0 + 2.0 * s->rc + grow) *
-                                   (long long)(2.0 * s->rc + grow));
+                                       (long long)(2.0 * s->rc + grow),
+                                   kPatchY * rows);
     s->passes = true;
     return FPD_OK;
 }
@@ -780,7 +785,7 @@ size_t fpd_population_bytes(const fpd_params* p) {
 
 // The passes of a simulation of its own (which is destroyed if that fails).
 static int create_passes(fpd_sim** out) {
-    const int rc = alloc_passes(*out, kMinPassNodes, 0.5);
+    const int rc = alloc_passes(*out, kMinPassNodes, 0.5, kPatchRows);
     if (rc) {
         fpd_destroy(*out);
         *out = nullptr;
@@ -1911,7 +1916,7 @@ int fpd_batch_add(fpd_batch* b, const fpd_params* p, const double* R, int64_t n_
     fpd_sim* s = nullptr;
     rc = create_impl(p, b->stream, nullptr, nullptr, 0, &s);
     if (rc) return rc;
-    rc = alloc_passes(s, 0, 1.0);
+    rc = alloc_passes(s, 0, 1.0, kBatchPatchRows);
     if (rc == FPD_OK) rc = fpd_set_launch(s, &b->launch);
     if (rc == FPD_OK && p->n_beads > 0) rc = fpd_init_fiber(s, R);
     if (rc) {
