@@ -591,10 +591,7 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
 // the patch and bead kernels one after the other take longer than a whole step's two
 // (1024 x 256, float32: 20.9 against 16.5 us per step; 777 x 333: 19.3 against 17.4), while at
 // 2042 x 611 in float16 deviations passes gain (25.3 against 28.4).
-#ifndef MPN
-#define MPN (1LL << 20)
-#endif
-constexpr long long kMinPassNodes = MPN;
+constexpr long long kMinPassNodes = 1LL << 20;
 
 // The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
 // at most kMaxUnits fibers, and the patches together span at most `share` of the lattice's
@@ -1481,7 +1478,7 @@ struct fpd_batch {
     ItemRef* h_bead_items = nullptr;
     int cap_tiles = 0, cap_beads = 0;
     // passes: per simulation the patch buffers and tiling, the patch and march items (the
-    // latter sorted by kind), and the stream and events that run the marches beside the rest
+    // latter sorted by kind)
     PassSim* d_pass = nullptr;
     PassSim* h_pass = nullptr;
     ItemRef* d_patch_items = nullptr;
@@ -1493,8 +1490,6 @@ struct fpd_batch {
     bool passes = false;              // every active simulation takes passes
     bool any_record = false;          // some of them record
     bool graph_record = false;
-    hipStream_t side = nullptr;
-    hipEvent_t ev_fluid = nullptr, ev_fiber = nullptr;
     std::vector<int> table;  // entry index of table row r
     bool dirty = true;
     bool pending = false;        // steps enqueued by fpd_batch_launch, not yet waited for
@@ -1537,10 +1532,18 @@ size_t footprint_of(const fpd_params* p) {
     return 2 * pop + rect + sizeof(BeadState);
 }
 
-// Rows of a march tile in a batch: as many tiles as a single lattice's march, at least
-// kBatchMarchRows rows each.
-constexpr int kBatchMarchTiles = 2048;
-constexpr int kBatchMarchRows = 24;
+// Rows of a march tile in a batch: about kBatchMarchTiles tiles of at least kBatchMarchRows rows.
+// A small batch waits for its tiles' rows (64 lattices of various shapes, 2.3 M nodes, float32,
+// 40 / 24 / 16 / 8 rows at least: 55.7 / 47.8 / 44.6 / 43.3 us per step), a large one for its
+// last tiles (64 channels, 14.8 M nodes, float16, 2048 / 4096 / 8192 tiles: 150 / 133 / 131).
+constexpr int kBatchMarchTiles = 8192;
+constexpr int kBatchMarchRows = 8;
+// Nodes of the active simulations from which a batch takes passes.  Single steps / passes, us
+// per step in float32: shapes of 0.59 M nodes 27.1 / 27.8, 0.90 M 31.9 / 31.5, 1.46 M 40.5 /
+// 34.7, 2.3 M 53.4 / 46.5; two channels of 0.49 M 27.6 / 27.6, four of 0.96 M 33.6 / 30.1, 64 of
+// 14.8 M 229 / 126; the other formats gain more (four channels: float64 60.6 / 48.5, float16
+// 38.0 / 34.0).
+constexpr long long kBatchPassNodes = 3LL << 18;
 
 // Whether every active simulation takes passes, and then the counts of their items and each
 // one's tiling (h_pass; h_args filled).
@@ -1550,7 +1553,7 @@ void batch_plan_passes(fpd_batch* b) {
     for (int& k : b->kind_count) k = 0;
     b->any_record = false;
     b->passes = r > 0;
-    long long strip_rows = 0;
+    long long strip_rows = 0, nodes = 0;
     for (int q = 0; q < r; ++q) {
         const fpd_sim* s = b->entries[b->table[q]].sim;
         if (!use_passes(s) || has_ev(s)) {  // (the forces between fibers: batch_forces_kernel)
@@ -1559,6 +1562,11 @@ void batch_plan_passes(fpd_batch* b) {
         }
         const int cols = march_cols(s->p.storage, s->L);
         strip_rows += (long long)((s->L.nx + cols - 1) / cols) * s->L.ny;
+        nodes += (long long)s->L.nx * s->L.ny;
+    }
+    if (nodes < kBatchPassNodes) {
+        b->passes = false;
+        return;
     }
     const long long rows = std::max<long long>(kBatchMarchRows, strip_rows / kBatchMarchTiles);
     for (int q = 0; q < r; ++q) {
@@ -1700,27 +1708,24 @@ int batch_enqueue(fpd_batch* b, int gpar) {
     return FPD_OK;
 }
 
-// n passes from buffer gpar and window slot wpar (relative to the tables), as enqueue_pass
-// orders them for one simulation.
+// n passes from buffer gpar and window slot wpar (relative to the tables), the march ahead of
+// the steps of the nodes around the fibers on the batch's one stream.  Beside them on a second
+// stream it is 5-15 % faster for one batch alone (64 channels of 14.8 M nodes: float32 121
+// against 126 us per step, float16 120 against 131), but two batches at a time then need four
+// hardware queues, share some, and wait for each other: 142 against 115, 142 against 115.
 int batch_enqueue_passes(fpd_batch* b, int gpar, int wpar, int64_t n) {
     if (n <= 0) return FPD_OK;
     HIP_TRY(launch_batch_pass_setup(batch_args(b, gpar, wpar, 1), b->h_counts[0], b->stream));
-    HIP_TRY(hipEventRecord(b->ev_fiber, b->stream));
     for (int64_t i = 0; i < n; ++i) {
-        HIP_TRY(hipStreamWaitEvent(b->side, b->ev_fiber, 0));
         HIP_TRY(launch_batch_march(b->storage, batch_args(b, gpar, wpar, 1), b->kind_count,
-                                   b->side));
-        if (i > 0) HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_fluid, 0));
-        HIP_TRY(hipEventRecord(b->ev_fluid, b->side));
+                                   b->stream));
         for (int t = 1; t <= kPassSteps; ++t) {
             HIP_TRY(launch_batch_patch(b->storage, batch_args(b, gpar, wpar, t), b->h_counts,
                                        b->any_periodic, b->any_record, b->stream));
             wpar = 1 - wpar;
         }
-        HIP_TRY(hipEventRecord(b->ev_fiber, b->stream));
         gpar = 1 - gpar;
     }
-    HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_fluid, 0));
     return FPD_OK;
 }
 
@@ -1741,26 +1746,6 @@ int batch_enqueue_steps(fpd_batch* b, int64_t n, bool chunk) {
         if (rc) return rc;
     }
     return batch_enqueue_passes(b, (int)(singles & 1), (int)(singles & 1), passes);
-}
-
-// The stream of the marches and the events, on the device of the batch's stream.
-int batch_ensure_side(fpd_batch* b) {
-    if (!b->passes || (b->side && b->ev_fluid && b->ev_fiber)) return FPD_OK;
-    hipDevice_t dev = 0;
-    int cur = 0;
-    HIP_TRY(hipStreamGetDevice(b->stream, &dev));
-    HIP_TRY(hipGetDevice(&cur));
-    if (dev != cur) HIP_TRY(hipSetDevice(dev));
-    hipError_t e = hipSuccess;
-    if (!b->side) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
-    if (e == hipSuccess && !b->ev_fluid)
-        e = hipEventCreateWithFlags(&b->ev_fluid, hipEventDisableTiming);
-    if (e == hipSuccess && !b->ev_fiber)
-        e = hipEventCreateWithFlags(&b->ev_fiber, hipEventDisableTiming);
-    if (dev != cur) (void)hipSetDevice(cur);
-    if (e != hipSuccess)
-        return fail(FPD_EDEVICE, "batch pass stream or events: %s", hipGetErrorString(e));
-    return FPD_OK;
 }
 
 int batch_build_graph(fpd_batch* b, int chunk) {
@@ -1850,7 +1835,6 @@ int fpd_batch_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t storage
 void fpd_batch_destroy(fpd_batch* b) {
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
-    if (b->side) (void)hipStreamSynchronize(b->side);
     batch_drop_graph(b);
     for (auto& e : b->entries) fpd_destroy(e.sim);
     b->entries.clear();
@@ -1874,9 +1858,6 @@ void fpd_batch_destroy(fpd_batch* b) {
     (void)hipHostFree(b->h_pass);
     (void)hipHostFree(b->h_patch_items);
     (void)hipHostFree(b->h_march_items);
-    if (b->ev_fluid) (void)hipEventDestroy(b->ev_fluid);
-    if (b->ev_fiber) (void)hipEventDestroy(b->ev_fiber);
-    if (b->side) (void)hipStreamDestroy(b->side);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
 }
@@ -1956,8 +1937,6 @@ int fpd_batch_launch(fpd_batch* b, int64_t max_steps, int64_t* advanced) {
         rc = batch_rebuild(b);
         if (rc) return rc;
     }
-    rc = batch_ensure_side(b);
-    if (rc) return rc;
     int64_t left = steps;
     const int chunk = b->launch.graph_chunk;
     if (left >= chunk) {

@@ -111,3 +111,36 @@ def test_passes_of_several_fibers(storage):
                                    storage=storage, seed=11)
     centres = ((300.0, 200.0, 0.4), (322.0, 215.0, 1.9), (2046.0, 300.0, 0.1))
     same(w.with_(centres=centres, ev_k=1e-3, ev_range=9.0))
+
+
+@pytest.mark.parametrize("storage", STORAGE)
+def test_passes_of_a_batch(storage):
+    """Walls, a periodic box under a body force (odd columns where passes take them), no fiber and
+    two fibers in one batch, against single steps; members leave at different times, the rest is
+    then too small for passes, and one records its fiber's ends."""
+    odd = storage in ("f64", "f32")
+    two = workloads.fiber_suspension(n_fibers=2, beads=6, nx=800, ny=400, radius=3.0,
+                                     storage=storage, seed=5)
+    ws = [channel(702, 257, storage, cx=350.0, cy=120.0, theta=0.7),
+          channel(601 if odd else 602, 420, storage, cx=2.0, cy=418.0, theta=0.9, boundary=1,
+                  g_body=(1e-6, -2e-6)),
+          channel(1000, 301, storage, cx=0.0, cy=0.0, theta=0.0, beads=0),
+          two.with_(centres=((200.0, 200.0, 0.4), (222.0, 215.0, 1.9)))]
+    targets = [41, 29, 41, 36]
+    print(f"[case] batch passes {storage} {[(w.nx, w.ny, w.n_beads) for w in ws]}", flush=True)
+    out = []
+    for flags, chunk in ((_lib.FPD_FLAG_NO_SPLIT, 64), (0, 8), (0, 64), (0, 2)):
+        with _lib.Batch(hbm_budget=1 << 33, max_slots=8, storage=storage) as b:
+            b.set_launch(dict(graph_chunk=chunk))
+            ids = [b.add(_lib.params_from_mapping(w.params(), storage=storage, flags=flags),
+                         w.beads(), t) for w, t in zip(ws, targets)]
+            b.record_start(ids[0], every=3, capacity=16)
+            while b.run(17):
+                pass
+            got = [b.record(ids[0])]
+            for sid in ids:
+                got += [b.populations(sid), *b.beads(sid)]
+            out.append(got)
+    for got in out[1:]:
+        for x, y in zip(got, out[0]):
+            assert np.array_equal(x, y)
