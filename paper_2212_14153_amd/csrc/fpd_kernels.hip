@@ -326,7 +326,8 @@ template <typename T> struct TileBead {
 // [cx0, cx0 + cw) and rows [ry0, ry0 + rh): bead order is kept, so per-node sums over
 // beads run in the same order as in a full loop.  Bond tangents and forces are computed
 // only when some bead is near (with several fibers most window tiles have none).
-template <typename T>
+// WRAP: the tile may reach across the periodic edges.
+template <typename T, bool WRAP = false>
 __device__ inline int gather_beads(const Fiber& fib, int nx, int ny, bool per, int cx0, int cw,
                                    int ry0, int rh, TileBead<T>* sB, int* sIdx, int* s_wave,
                                    Bonds& B, bool forces_ready) {
@@ -388,7 +389,13 @@ __device__ inline int gather_beads(const Fiber& fib, int nx, int ny, bool per, i
             sB[i].C[1] = (T)C1;
             int ox, oy;
             sB[i].g.node(nx, ny, per, ox, oy);
-            if (imod(ox - cx0, nx) < cw && (per ? imod(oy - ry0, ny) : oy - ry0) < rh && (per || oy >= ry0))
+            bool own = ox >= cx0 && ox < cx0 + cw && oy >= ry0 && oy < ry0 + rh;
+            if (WRAP) {
+                const int dx = ox - cx0, dy = oy - ry0;
+                own = (dx < 0 ? dx + nx : dx) < cw && (per && dy < 0 ? dy + ny : dy) < rh &&
+                      (per || dy >= 0);
+            }
+            if (own)
                 own_bead(fib, B, b, F, C0, C1);
         }
     }
@@ -1086,7 +1093,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     for (int r = 0; r < ROWS; ++r)
         if (in[r]) pull_view<Cd, true>(v, nx, ny, x, y[r], per, u6, g[r]);
     TileBead<T>* sB = (TileBead<T>*)lds.beads;
-    const int nb = gather_beads<T>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
+    const int nb = gather_beads<T, true>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
                                    lds.bonds, false);
     const View o = patch_view(u, plan, a.L, a.dst, patch_dst(t));
 #pragma unroll
