@@ -59,12 +59,21 @@ __global__ void __launch_bounds__(64) batch_march_kernel(BatchArgs b, int first)
 // float64, 65.8 / 71.2 / 60.2 / 72.3 / 67.4 in bfloat16 deviations.  A wave recomputes up to
 // kPassSteps - 1 rows on either side of its own, so small lattices take fewer, taller runs.
 constexpr int kMarchWaves = 2048;
+// Many fibers: their patch and bead blocks are everywhere, and the waves beside them end late.  A
+// third wave per SIMD, in shorter runs of rows, evens that out.  8192 x 2048 with 25 fibers,
+// 2048 / 3072 / 4096 waves, us per step: float32 97.7 / 86.5 / 87.6, float64 185 / 156 / 162,
+// float16 94.9 / 73.8 / 77.3, bfloat16 91.0 / 74.2 / 76.3; 14 fibers, 2048 / 3072: float32
+// 88.4 / 74.6, float64 176 / 160, float16 66.6 / 64.8; 8 fibers: 68.6 / 70.0, 170 / 157,
+// 63.2 / 61.3, and 4096 x 1500 with 8: 31.1 / 39.2, 61.2 / 67.9, 30.0 / 31.3.
+constexpr int kMarchWavesMany = 3072;
+constexpr int kMarchManyUnits = 12;
 constexpr int kMarchMinRows = 16;
 
 template <int ST, int C, int OL>
 static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream_t st) {
     const int strips = (a.L.nx + OL * C - 1) / (OL * C);
-    const int runs = std::max(1, std::min(kMarchWaves / strips, a.L.ny / kMarchMinRows));
+    const int waves = q.n_units >= kMarchManyUnits ? kMarchWavesMany : kMarchWaves;
+    const int runs = std::max(1, std::min(waves / strips, a.L.ny / kMarchMinRows));
     const MarchArgs m = march_args(a, q.units, q.n_units, q.slot, strips,
                                    (a.L.ny + runs - 1) / runs);
     const int segs = (a.L.ny + m.seg_rows - 1) / m.seg_rows;

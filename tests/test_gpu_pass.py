@@ -113,6 +113,14 @@ def test_passes_of_several_fibers(storage):
     same(w.with_(centres=centres, ev_k=1e-3, ev_range=9.0))
 
 
+@pytest.mark.parametrize("nx,ny,storage", [(2048, 1024, "f32"), (2049, 1100, "f64"),
+                                           (8192, 300, "bf16dev")])
+def test_passes_of_many_fibers(nx, ny, storage):
+    """From 12 fibers on the march takes shorter runs of rows."""
+    same(workloads.fiber_suspension(n_fibers=13, beads=5, nx=nx, ny=ny, radius=2.5,
+                                    storage=storage, seed=3), counts=(3, 9))
+
+
 @pytest.mark.parametrize("storage", STORAGE)
 def test_passes_of_a_batch(storage):
     """Walls, a periodic box under a body force (odd columns where passes take them), no fiber and
