@@ -188,10 +188,12 @@ int fpd_init_fiber_line(fpd_sim *s, double cx, double cy, double theta);
  * step (2) runs as two kernels, the tiles away from the fiber on a second stream of the
  * library's own (non-blocking, default priority) while the bead kernel of the step before
  * finishes, and the tiles near it after that bead kernel; the results are the same bits.
- * Passes: a lattice of about a million nodes or more (one fiber or none, no fixed profile,
- * not FPD_FLAG_NO_SPLIT) advances four steps per pass over memory, the fluid away from the
- * fiber in one kernel on that second stream, the nodes around the fiber step by step in two
- * buffers of their size that the simulation holds besides its populations; the results are
+ * Passes: a lattice of about a million nodes or more (no fixed profile, at most 64 fibers, an
+ * even nx in the two-byte formats, not FPD_FLAG_NO_SPLIT) advances four steps per pass over
+ * memory: the fluid away from the fibers in one kernel on that second stream, the nodes around
+ * each fiber step by step in two buffers of their size.  These buffers belong to the simulation
+ * besides its populations (about the nodes of a fiber's window each, not counted by
+ * fpd_sim_footprint); without memory for them it takes split or whole steps.  The results are
  * the same bits, and steps left over by a multiple of four are split or whole ones.
  * The simulation's stream waits for the second stream before fpd_step returns, so work
  * enqueued on it afterwards follows every step.  The first step after fpd_init_fiber or
@@ -200,7 +202,8 @@ int fpd_init_fiber_line(fpd_sim *s, double cx, double cy, double theta);
 int fpd_step(fpd_sim *s, int64_t n_steps);
 
 /* Capture now, without running any step, the graph that fpd_step(s, n_steps) replays
- * (steps are replayed in captured chunks of graph_chunk steps when n_steps >= graph_chunk
+ * (steps are replayed in captured chunks of graph_chunk steps, rounded down to whole passes
+ * where fpd_step takes them, when n_steps is at least that many
  * and neither FPD_FLAG_NO_GRAPH nor FPD_FLAG_TIME_KERNELS is set; otherwise there is
  * nothing to capture and the call does nothing), so that the capture cost stays out of a
  * timed fpd_step; with split steps right after fpd_init_fiber or fpd_load, the graph of
@@ -227,7 +230,8 @@ const char *fpd_last_error(void);
 
 /* Host arrays [ny][nx], NULL to skip: density rho, velocity u = (j + f^n/2) / rho with the
  * force density of the current bead state (Guo's macroscopic velocity), viscosity eta^n of
- * Eq. (1).  Pressure is rho / 3. */
+ * Eq. (1).  Pressure is rho / 3.  Arrays in pinned host memory (hipHostMalloc, or a tensor
+ * allocated with pin_memory) are written in place by the kernel, without a staging array. */
 int fpd_read_fields(fpd_sim *s, double *rho, double *ux, double *uy, double *eta);
 
 /* Host f[9][ny][nx] (caller-owned, filled here): the pre-collision (post-stream)
@@ -364,7 +368,8 @@ int fpd_run_static(const fpd_params *p, void *hip_stream, void *f_a, void *f_b,
  * over every (simulation, bead) pair, replayed from a captured graph.  The parameter-sweep workload of the paper
  * (Sec. IV: stiffness, Re_ps 1-10, confinement) is the intended use.  Per-simulation
  * arithmetic is the single-simulation path's, so a result is bitwise the same alone and
- * in any mix. */
+ * in any mix.  Active simulations of about 0.8 million nodes or more together take passes of
+ * four steps (fpd_step), all on the batch's stream, where every one of them can. */
 
 typedef struct fpd_batch fpd_batch;
 

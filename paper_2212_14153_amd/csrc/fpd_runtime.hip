@@ -930,10 +930,18 @@ int fpd_init_fiber_line(fpd_sim* s, double cx, double cy, double theta) {
 
 namespace {
 
-// Whether n steps from the current state replay graphs, and the graph that replays the
-// first of them (after `skip` single steps) captured (nothing runs).
-int ensure_graph(fpd_sim* s, int from, int wpar, int64_t n, bool* replay) {
+// Steps of a captured chunk: graph_chunk, in passes a multiple of kPassSteps, since each single
+// step of a chunk costs three of a pass (8192 x 2048, float32, graph_chunk 50: 72.8 us per step
+// with two single steps in each chunk, 67 without).
+int replay_chunk(const fpd_sim* s) {
     const int chunk = s->launch.graph_chunk;
+    return use_passes(s) && chunk >= kPassSteps ? chunk - chunk % kPassSteps : chunk;
+}
+
+// Whether n steps from the current state replay graphs, and the graph that replays the
+// first of them captured (nothing runs).
+int ensure_graph(fpd_sim* s, int from, int wpar, int64_t n, bool* replay) {
+    const int chunk = replay_chunk(s);
     *replay = !(s->p.flags & (FPD_FLAG_NO_GRAPH | FPD_FLAG_TIME_KERNELS)) && chunk >= 2 &&
               n >= chunk;
     if (!*replay) return FPD_OK;
@@ -967,11 +975,11 @@ int fpd_capture(fpd_sim* s, int64_t n) {
     const int64_t w = whole_first(s, n) ? 1 : 0;
     int from = s->cur ^ (int)w, wpar = s->wpar ^ (int)w;
     int rc = ensure_graph(s, from, wpar, n - w, &replay);
-    if (rc || !replay || n - w < 2 * (int64_t)s->launch.graph_chunk) return rc;
-    // a chunk of an odd number of passes and single steps ends in the other buffer
+    if (rc || !replay || n - w < 2 * (int64_t)replay_chunk(s)) return rc;
+    // a chunk of an odd number of passes ends in the other buffer
     const int cur = s->cur;
     s->cur = from;
-    advance_state(s, s->launch.graph_chunk);
+    advance_state(s, replay_chunk(s));
     from = s->cur;
     s->cur = cur;
     return ensure_graph(s, from, wpar, n - w, &replay);
@@ -1002,7 +1010,7 @@ int fpd_step(fpd_sim* s, int64_t n) {
         flip(s);
         --left;
     }
-    const int chunk = s->launch.graph_chunk;
+    const int chunk = replay_chunk(s);
     for (;;) {
         bool replay = false;
         int rg = ensure_graph(s, s->cur, s->wpar, left, &replay);

@@ -85,6 +85,13 @@ def test_passes_in_graph_chunks(chunk):
          counts=(1, 2 * chunk + 7, 3))
 
 
+@pytest.mark.parametrize("chunk", [10, 22, 50])
+def test_chunks_are_rounded_to_whole_passes(chunk):
+    """Odd and even numbers of passes a chunk, calls just below and at the chunk's length."""
+    same(channel(2048, 520, "f32", cx=1000.0, cy=260.0, theta=1.2), chunk=chunk,
+         counts=(chunk - 3, chunk, 3 * chunk + 1, chunk - 1))
+
+
 def test_recording_and_checkpoint_between_passes(tmp_path):
     w = channel(2048, 512, "f32", cx=900.0, cy=256.0, theta=math.pi / 3)
     path = str(tmp_path / "pass.ckpt")
