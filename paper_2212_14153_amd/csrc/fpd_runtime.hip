@@ -612,8 +612,8 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
 
 // Passes pay from about a million nodes on: below, a step is the latency of its kernels, and
 // the patch and bead kernels one after the other take longer than a whole step's two
-// (1024 x 256, float32: 20.9 against 16.5 us per step; 777 x 333: 19.3 against 17.4), while at
-// 2042 x 611 in float16 deviations passes gain (25.3 against 28.4).
+// (1024 x 256, float32: 18.0 against 16.5 us per step; 777 x 333: 18.6 against 17.3), while at
+// 2042 x 611 in float16 deviations passes gain (22.5 against 28.4).
 constexpr long long kMinPassNodes = 1LL << 20;
 
 // The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
