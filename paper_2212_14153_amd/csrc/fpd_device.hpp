@@ -120,7 +120,7 @@ template <> struct Codec<FPD_BF16DEV> {
 
 // ------------------------------------------------------------------- helpers --------
 
-__device__ inline int imod(int a, int n) {
+__host__ __device__ inline int imod(int a, int n) {
     int r = a % n;
     return r < 0 ? r + n : r;
 }
@@ -138,40 +138,54 @@ __device__ inline int xcd_tile(int bid, int nblocks) {
 // columns i0 + [0, w) modulo nx (w <= nx), rows j0..j1 (clipped to the channel).
 // A bead that is not finite or has left any sensible range (a simulation that blew up)
 // gets an empty box, so no index is ever formed from it.
-__device__ inline bool bead_sane(double Rx, double Ry) {
+__host__ __device__ inline bool bead_sane(double Rx, double Ry) {
     return fabs(Rx) < 1.0e9 && fabs(Ry) < 1.0e9;  // false for NaN too
 }
 
+// A bead's support box: node columns and rows, unwrapped (publish_support's bounds).
+struct BeadSpan {
+    int x0, x1, y0, y1;
+};
+__host__ __device__ inline BeadSpan bead_span(double Rx, double Ry, double rc) {
+    return BeadSpan{(int)floor(Rx - 0.5 - rc), (int)ceil(Rx - 0.5 + rc),
+                    (int)floor(Ry - 0.5 - rc), (int)ceil(Ry - 0.5 + rc)};
+}
+
 // With walls, rows j0..j1 are clipped to the channel; in a periodic box (per) they are
-// j0 .. j1 with j0 in [0, ny) and j1 - j0 < ny, to be taken modulo ny.
-__device__ inline void bead_box(double Rx, double Ry, double rc, int nx, int ny, bool per,
-                                int& i0, int& w, int& j0, int& j1) {
+// j0 .. j1 with j0 in [0, ny) and j1 - j0 < ny, to be taken modulo ny.  s: the box unwrapped
+// (empty for a bead that is not sane).
+__host__ __device__ inline void bead_box(double Rx, double Ry, double rc, int nx, int ny,
+                                         bool per, int& i0, int& w, int& j0, int& j1,
+                                         BeadSpan& s) {
     if (!bead_sane(Rx, Ry)) {
         i0 = 0;
         w = 0;
         j0 = 0;
         j1 = -1;
+        s = BeadSpan{0, -1, 0, -1};
         return;
     }
-    const int lo = (int)floor(Rx - 0.5 - rc);
-    const int hi = (int)ceil(Rx - 0.5 + rc);
-    w = hi - lo + 1;
+    s = bead_span(Rx, Ry, rc);
+    w = s.x1 - s.x0 + 1;
     if (w >= nx) {
         w = nx;
         i0 = 0;
     } else {
-        i0 = imod(lo, nx);
+        i0 = imod(s.x0, nx);
     }
-    const int a = (int)floor(Ry - 0.5 - rc);
-    const int b = (int)ceil(Ry - 0.5 + rc);
     if (per) {
-        const int h = b - a + 1 < ny ? b - a + 1 : ny;
-        j0 = h == ny ? 0 : imod(a, ny);
+        const int h = s.y1 - s.y0 + 1 < ny ? s.y1 - s.y0 + 1 : ny;
+        j0 = h == ny ? 0 : imod(s.y0, ny);
         j1 = j0 + h - 1;
         return;
     }
-    j0 = a < 0 ? 0 : a;
-    j1 = b > ny - 1 ? ny - 1 : b;
+    j0 = s.y0 < 0 ? 0 : s.y0;
+    j1 = s.y1 > ny - 1 ? ny - 1 : s.y1;
+}
+__host__ __device__ inline void bead_box(double Rx, double Ry, double rc, int nx, int ny,
+                                         bool per, int& i0, int& w, int& j0, int& j1) {
+    BeadSpan s;
+    bead_box(Rx, Ry, rc, nx, ny, per, i0, w, j0, j1, s);
 }
 
 // Do the column sets c0 + [0, cw) and i0 + [0, w) (both modulo nx) intersect?
@@ -424,14 +438,20 @@ struct View {
     long long plane;
 };
 
+// Column (row) v of the lattice, counted from a view's first.
+__host__ __device__ inline int view_index(int v, int origin, int n) {
+    v -= origin;
+    return v < 0 ? v + n : v;
+}
+
 // pull() from a view.  SCALED: values in the collision's units (as pull_group).
 template <class Cd, bool SCALED>
 __device__ inline void pull_view(const View& v, int nx, int ny, int x, int y, bool per,
                                  typename Cd::T u6, typename Cd::T g[9]) {
     using S = typename Cd::store_t;
     const S* p = (const S*)v.p;
-    auto col = [&](int c) { c -= v.ox; return c < 0 ? c + nx : c; };
-    auto row = [&](int r) { r -= v.oy; return (long long)(r < 0 ? r + ny : r) * v.stride; };
+    auto col = [&](int c) { return view_index(c, v.ox, nx); };
+    auto row = [&](int r) { return (long long)view_index(r, v.oy, ny) * v.stride; };
     auto at = [&](int k, long long r, int c) -> typename Cd::T {
         const S* q = p + r + k * v.plane + c;
         if constexpr (SCALED && sizeof(S) == 2)

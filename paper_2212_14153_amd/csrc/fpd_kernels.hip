@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include "fpd_device.hpp"
+#include "fpd_plan.hpp"
 
 namespace fpd {
 
@@ -859,187 +860,25 @@ __device__ inline View patch_view(const PatchUnit& u, PlanPtr plan, const Lattic
 __device__ inline int patch_src(int t) { return t > 1 ? (t & 1) : -1; }
 __device__ inline int patch_dst(int t) { return t < kPassSteps ? ((t + 1) & 1) : -1; }
 
-// A bead's support box: node columns and rows, unwrapped (publish_support's bounds).
-struct BeadSpan {
-    int x0, x1, y0, y1;
-};
-__device__ inline BeadSpan bead_span(double Rx, double Ry, double rc) {
-    return BeadSpan{(int)floor(Rx - 0.5 - rc), (int)ceil(Rx - 0.5 + rc),
-                    (int)floor(Ry - 0.5 - rc), (int)ceil(Ry - 0.5 + rc)};
+// The plan of unit u for the pass that starts from buffer `slot`; every thread of one 1-D block.
+__device__ inline void unit_make_plan(const StepArgs& a, const PatchUnit& u, int slot,
+                                      PlanLds& sm) {
+    if (make_plan(PlanBlock(), a.L, a.fib.rc, a.fib.bs->R, u, u.plan + slot * u.plan_len, sm) &&
+        threadIdx.x == 0)
+        atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
 }
-
-// LDS of make_plan: the beads' boxes, and the partition's columns on a run of patch rows with
-// the kPassSteps - 1 rows on either side that the first step's growth looks at.
-constexpr int kPlanRun = 512;
-struct PlanLds {
-    int bound[4];
-    int box[kMaxBeads][4];  // x0, x1, y0, y1; x1 < x0: none
-    int lo[kPlanRun + 2 * (kPassSteps - 1)], hi[kPlanRun + 2 * (kPassSteps - 1)];
-    int tiles;
-};
-
-// The plan of unit u for a pass, from the current positions (every thread of one 1-D block).
-// A row's columns are the hull of the grown boxes that meet it, so a fiber at an angle does not
-// take its whole rectangle.
-__device__ inline void make_plan(const StepArgs& a, const PatchUnit& u, int* plan, PlanLds& sm) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int nx = a.L.nx, ny = a.L.ny;
-    const bool per = a.L.periodic != 0;
-    const BeadState* bs = a.fib.bs;
-    constexpr int M = kPassMargin, E = kPassSteps - 1, P = kPassAlign - 1;
-    if (tid < 4) sm.bound[tid] = tid & 1 ? -0x3fffffff : 0x3fffffff;
-    if (tid == 4) sm.tiles = 0;
-    __syncthreads();
-    for (int i = tid; i < u.n; i += nt) {
-        const double Rx = bs->R[u.first + i][0], Ry = bs->R[u.first + i][1];
-        BeadSpan s{0, -1, 0, -1};
-        if (bead_sane(Rx, Ry)) {
-            s = bead_span(Rx, Ry, a.fib.rc);
-            atomicMin(&sm.bound[0], s.x0);
-            atomicMax(&sm.bound[1], s.x1);
-            atomicMin(&sm.bound[2], s.y0);
-            atomicMax(&sm.bound[3], s.y1);
-        }
-        const int o[4] = {s.x0, s.x1, s.y0, s.y1};
-        for (int k = 0; k < 4; ++k) {
-            sm.box[i][k] = o[k];
-            plan[kPlanBoxes + 4 * i + k] = o[k];
-        }
-    }
-    __syncthreads();
-    // the patch rectangle: first column bx and row by (unwrapped), W x H nodes; a side that
-    // would span the lattice is the lattice (allx, ally)
-    const bool none = sm.bound[0] > sm.bound[1];
-    int bx = sm.bound[0] - M - E - P, W = sm.bound[1] - sm.bound[0] + 1 + 2 * (M + E + P);
-    int X0 = none ? 0 : imod(bx, nx);
-    const int lead = X0 % kPassAlign;
-    X0 -= lead;
-    bx -= lead;
-    W += lead;
-    const bool allx = W >= nx;
-    if (allx) {
-        X0 = bx = 0;
-        W = nx;
-    }
-    int by = sm.bound[2] - M - E, H = sm.bound[3] - sm.bound[2] + 1 + 2 * (M + E);
-    const bool ally = per && H >= ny;
-    if (ally) {
-        by = 0;
-        H = ny;
-    } else if (!per) {
-        const int top = min(by + H, ny);
-        by = max(by, 0);
-        H = max(top - by, 0);
-    }
-    if (none) W = H = 0;
-    if (W > u.cap_w || H > u.cap_h) {  // outgrew the reserved window
-        if (tid == 0) atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
-        W = min(W, u.cap_w);
-        H = min(H, u.cap_h);
-    }
-    if (tid == 0) {
-        plan[0] = X0;
-        plan[1] = W;
-        plan[2] = none ? 0 : (per ? imod(by, ny) : by);
-        plan[3] = H;
-    }
-    int tall = (int)ceil(2.0 * a.fib.rc) + 4 + 2 * M;  // rows of a grown box, at most
-    if (per) tall = min(tall, ny);
-    int* tiles = plan + plan_tiles_at(u.cap_h);
-    for (int r0 = 0; r0 < H; r0 += kPlanRun) {
-        const int run = min(kPlanRun, H - r0), span = run + 2 * E;
-        __syncthreads();
-        for (int i = tid; i < span; i += nt) {
-            sm.lo[i] = 0x3fffffff;
-            sm.hi[i] = -0x3fffffff;
-        }
-        __syncthreads();
-        // rows r0 - E .. r0 + run + E - 1 of the partition
-        for (int k = tid; k < u.n * tall; k += nt) {
-            const int i = k / tall, j = k - i * tall;
-            const int* o = sm.box[i];
-            if (o[1] < o[0] || j > o[3] - o[2] + 2 * M) continue;
-            int c0 = o[0] - M - bx, c1 = o[1] + M + 1 - bx;
-            if (allx) {
-                const int w = c1 - c0;
-                c0 = imod(c0, nx);
-                c1 = c0 + w;
-            }
-            c0 = c0 / kPassAlign * kPassAlign;  // (c0 >= 0); the march masks whole lanes
-            c1 = (c1 + P) / kPassAlign * kPassAlign;
-            if (allx && c1 > nx) {
-                c0 = 0;
-                c1 = nx;
-            }
-            const int r = o[2] - M + j - by;
-            for (int q = ally ? imod(r, ny) - ny : r; q < r0 + run + E; q += ny) {
-                if (q >= r0 - E && (ally || (q >= 0 && q < H))) {
-                    atomicMin(&sm.lo[q - r0 + E], c0);
-                    atomicMax(&sm.hi[q - r0 + E], c1);
-                }
-                if (!ally) break;
-            }
-        }
-        __syncthreads();
-        // each step's columns: m rows and columns more on either side, m = kPassSteps - t
-        int2* rows = (int2*)(plan + kPlanRows);
-        for (int i = tid; i < run; i += nt) {
-            int l = sm.lo[i + E], h = sm.hi[i + E];
-            for (int m = 0; m < kPassSteps; ++m) {
-                if (m > 0) {
-                    l = min(l, min(sm.lo[i + E - m], sm.lo[i + E + m]));
-                    h = max(h, max(sm.hi[i + E - m], sm.hi[i + E + m]));
-                }
-                int cl = l - m, ch = h + m;
-                if (allx && l < h && (cl < 0 || ch > nx)) {
-                    cl = 0;
-                    ch = nx;
-                }
-                cl = max(cl, 0);
-                ch = min(ch, W);
-                rows[(kPassSteps - 1 - m) * u.cap_h + r0 + i] = l < h && cl < ch ? int2{cl, ch}
-                                                                                : int2{0, 0};
-            }
-        }
-        // the tiles of the first step (kPlanRun is a multiple of a tile's rows)
-        for (int ty = tid; ty < (run + u.tile_h - 1) / u.tile_h; ty += nt) {
-            int l = 0x3fffffff, h = -0x3fffffff;
-            for (int i = ty * u.tile_h; i < min((ty + 1) * u.tile_h, run) + 2 * E; ++i) {
-                l = min(l, sm.lo[i]);
-                h = max(h, sm.hi[i]);
-            }
-            if (l >= h) continue;
-            l -= E;
-            h += E;
-            if (allx && (l < 0 || h > nx)) {
-                l = 0;
-                h = nx;
-            }
-            l = max(l, 0);
-            h = min(h, W);
-            if (l >= h) continue;
-            const int t0 = l / kPatchX, t1 = (h - 1) / kPatchX;
-            const int at = atomicAdd(&sm.tiles, t1 - t0 + 1);
-            for (int tx = t0; tx <= t1; ++tx)
-                tiles[at + tx - t0] = ((r0 / u.tile_h + ty) << 16) | tx;
-        }
-    }
-    __syncthreads();
-    if (tid == 0) plan[4] = sm.tiles;
-}
-static_assert(kPlanRun % (4 * kPatchY) == 0, "a run of plan rows is whole tiles");
 
 // The next pass's plan, by a block of the bead kernel of step kPassSteps - 1, beside the beads:
 // each position is read as it was before or after its update, either at most two steps from
 // the pass's first, which the margin covers.
 __device__ inline void next_plan(const StepArgs& a, const PatchUnit& u, int slot, PlanLds& sm) {
-    make_plan(a, u, u.plan + (1 - slot) * u.plan_len, sm);
+    unit_make_plan(a, u, 1 - slot, sm);
 }
 
 __global__ void __launch_bounds__(256) pass_setup_kernel(StepArgs a, PassArgs q) {
     __shared__ PlanLds sm;
     const PatchUnit u = load_unit(q.units, blockIdx.x);
-    make_plan(a, u, u.plan + q.slot * u.plan_len, sm);
+    unit_make_plan(a, u, q.slot, sm);
 }
 
 // The patch and bead kernels of a pass are the latency chain beside the march: their waves
@@ -1131,13 +970,10 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
 __device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
                                     bool first, const Window& win) {
     if (first) step_duties(a, win, false);
-    const int k = kPassMargin - max(kPassSteps - t, 1);
     for (int i = threadIdx.x; i < u.n; i += blockDim.x) {
         const double Rx = a.fib.bs->R[u.first + i][0], Ry = a.fib.bs->R[u.first + i][1];
         if (!bead_sane(Rx, Ry)) continue;
-        const BeadSpan s = bead_span(Rx, Ry, a.fib.rc);
-        PlanPtr g = plan + kPlanBoxes + 4 * i;
-        if (s.x0 < g[0] - k || s.x1 > g[1] + k || s.y0 < g[2] - k || s.y1 > g[3] + k)
+        if (!bead_in_plan(plan + kPlanBoxes + 4 * i, bead_span(Rx, Ry, a.fib.rc), t))
             atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
     }
 }
@@ -1178,7 +1014,7 @@ __global__ void __launch_bounds__(256) batch_pass_setup_kernel(BatchArgs b) {
     const PassSim p = load_pass(b.pass, s);
     for (int i = 0; i < p.n_units; ++i) {
         const PatchUnit u = load_unit(p.units, i);
-        make_plan(a, u, u.plan + b.gpar * u.plan_len, sm);
+        unit_make_plan(a, u, b.gpar, sm);
         __syncthreads();
     }
 }
@@ -1274,10 +1110,14 @@ __device__ inline void publish_support(const Fiber& fib, int win_out, double Rx,
 // only on the cutoff test, so phi is evaluated while they are in flight.  The sums run
 // over kBeadLanes virtual lanes (NT threads of R = kBeadLanes / NT lanes each): lane v
 // takes nodes t = v, v + kBeadLanes, ... in increasing t, whatever VB and NT.
-// PATCH: the step's populations are read from the view `pv` (a step of a pass).
+// PATCH: step t of a pass, whose populations are read from the view `pv` of the bead's patch;
+// pbox is the bead's box in the plan.  The support of a bead that has left it by more than the
+// margin (an unstable run; patch_duties raises FPD_HEALTH_SUPPORT) need not lie in the patch:
+// nothing is pulled for it, and its velocity is 0.
 template <int ST, int VB, int NT, bool PATCH = false>
 __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int win_out,
-                                  double* scratch, double* s_R, const View& pv = View{}) {
+                                  double* scratch, double* s_R, const View& pv = View{},
+                                  PlanPtr pbox = nullptr, int t = 0) {
     constexpr int R = kBeadLanes / NT;
     using Cd = Codec<ST>;
     using T = typename Cd::T;
@@ -1294,14 +1134,28 @@ __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int
     if (do_velocity)
 #pragma unroll
         for (int q = 0; q < 4; ++q) wraw[q] = bs->win[a.parity][q];
+    int box[4] = {0, -1, 0, -1};  // (read with them, not behind the position)
+    if constexpr (PATCH)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            box[q] = pbox[q];
+            asm volatile("" : "+s"(box[q]));
+        }
 
     double Vx = 0.0, Vy = 0.0;  // valid in thread 0
     if (do_velocity) {
+        if (PATCH && tid == 0) {  // (kept there: the sums need the registers)
+            s_R[0] = Rx;
+            s_R[1] = Ry;
+        }
         int i0, w, j0, j1;
-        bead_box(Rx, Ry, fib.rc, nx, ny, per, i0, w, j0, j1);
+        BeadSpan span;
+        bead_box(Rx, Ry, fib.rc, nx, ny, per, i0, w, j0, j1, span);
         const BeadGeom<T> geo = BeadGeom<T>::make(Rx, Ry, nx, ny, per);
         const int rows = j1 - j0 + 1;
-        const int total = (rows > 0 && w > 0) ? rows * w : 0;
+        int total = (rows > 0 && w > 0) ? rows * w : 0;
+        if constexpr (PATCH)
+            if (!bead_in_plan(box, span, t)) total = 0;
         const Window win = decode_window(wraw, nx, ny, per, fib.rect_wmax, fib.rect_hmax);
         const int wx0 = win.x0, wy0 = win.y0, ww = win.w, wh = win.h;
         const T* rf = (const T*)fib.rect_f;
@@ -1372,8 +1226,8 @@ __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int
             Vy = Sy / A_old;
             bs->V[b][0] = Vx;
             bs->V[b][1] = Vy;
-            s_R[0] = Rx + Vx;  // forward Euler, dt = 1
-            s_R[1] = Ry + Vy;
+            s_R[0] = (PATCH ? s_R[0] : Rx) + Vx;  // forward Euler, dt = 1
+            s_R[1] = (PATCH ? s_R[1] : Ry) + Vy;
             bs->R[b][0] = s_R[0];
             bs->R[b][1] = s_R[1];
         }
@@ -1442,17 +1296,18 @@ __global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArg
                                                                          int win_out) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
     __shared__ double s_R[2];
-    __shared__ PlanLds plan;
+    __shared__ PlanLds sm;
     chain_priority();
     if ((int)blockIdx.x >= a.fib.n) {  // (step kPassSteps - 1 only)
-        next_plan(a, pick_unit(q.unit0, q.units, (int)blockIdx.x - a.fib.n), q.slot, plan);
+        next_plan(a, pick_unit(q.unit0, q.units, (int)blockIdx.x - a.fib.n), q.slot, sm);
         return;
     }
     const int unit = (int)blockIdx.x / a.fib.chain_len;
     const PatchUnit u = pick_unit(q.unit0, q.units, unit);
+    PlanPtr plan = unit_plan(u, q.slot);
     bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
-        a, blockIdx.x, 1, win_out, scratch, s_R,
-        patch_view(u, unit_plan(u, q.slot), a.L, a.dst, patch_dst(q.t)));
+        a, blockIdx.x, 1, win_out, scratch, s_R, patch_view(u, plan, a.L, a.dst, patch_dst(q.t)),
+        plan + kPlanBoxes + 4 * ((int)blockIdx.x - u.first), q.t);
 }
 
 // Bead kernel over a batch: one block per (simulation, bead) item.
@@ -1475,7 +1330,7 @@ template <int ST>
 __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs b) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
     __shared__ double s_R[2];
-    __shared__ PlanLds plan;
+    __shared__ PlanLds sm;
     chain_priority();
     const int beads = b.counts[2];
     if ((int)blockIdx.x >= beads) {  // (step kPassSteps - 1 only)
@@ -1484,7 +1339,7 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
         const StepArgs a = load_pass_args(b, s);
         const PassSim p = load_pass(b.pass, s);
         for (int i = 0; i < p.n_units; ++i) {
-            next_plan(a, pick_unit(p.unit0, p.units, i), b.gpar, plan);
+            next_plan(a, pick_unit(p.unit0, p.units, i), b.gpar, sm);
             __syncthreads();
         }
         return;
@@ -1495,9 +1350,10 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
     const PassSim p = load_pass(b.pass, e.sim);
     const int unit = e.local / a.fib.chain_len;
     const PatchUnit u = pick_unit(p.unit0, p.units, unit);
+    PlanPtr plan = unit_plan(u, b.gpar);
     bead_block<ST, kBatchBeadVelBatch, kBeadBlock, true>(
-        a, e.local, 1, 1 - a.parity, scratch, s_R,
-        patch_view(u, unit_plan(u, b.gpar), a.L, a.dst, patch_dst(b.t)));
+        a, e.local, 1, 1 - a.parity, scratch, s_R, patch_view(u, plan, a.L, a.dst, patch_dst(b.t)),
+        plan + kPlanBoxes + 4 * (e.local - u.first), b.t);
 }
 
 // Excluded-volume forces of every bead at the step's start (one block).

@@ -21,6 +21,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "fpd_internal.hpp"
+#include "fpd_plan.hpp"
 
 using namespace fpd;
 
@@ -630,11 +631,9 @@ int alloc_passes(fpd_sim* s, long long min_nodes, double share, int rows) {
     }
     const int n_units = chains_of(&p), len = p.n_beads / n_units;
     if (n_units > kMaxUnits) return FPD_OK;
-    // one fiber's reserved window (window_size) and the margins around it
-    const double span = 1.5 * (len - 1) * p.l0 + 2.0 * s->rc + 4.0;
+    int w = 0, h = 0;
+    plan_caps(len, p.l0, s->rc, p.nx, p.ny, w, h);
     const int grow = 2 * (kPassMargin + kPassSteps - 1);
-    const int w = (int)fmin(ceil(span) + grow + 3 * kPassAlign, (double)p.nx);
-    const int h = (int)fmin(ceil(span) + grow, (double)p.ny);
     if ((double)w * h * n_units > share * (double)nodes) return FPD_OK;
     const int pitch = (w + 15) / 16 * 16;
     const size_t patch = (size_t)9 * pitch * h * s->elem;
