@@ -90,7 +90,16 @@ constexpr int kMaxUnits = 64;      // fibers of a simulation that takes passes (
 
 // One fiber's part of a pass: two buffers for its nodes' populations between the steps (nine
 // rows of `pitch` nodes side by side, cap_w x cap_h nodes at most) and two plans (by the
-// buffer a pass starts from).
+// buffer a pass starts from).  A fiber longer than they hold (1.5 times its contour: a run that
+// has raised FPD_HEALTH_STRAIN): alone it has outgrown the force window too, its plan is empty and
+// FPD_HEALTH_SUPPORT raised.  Among several fibers, whose window is the lattice, it makes its
+// simulation's passes whole: the march does nothing, the patch blocks of all units take the four
+// steps over the whole lattice, to and fro between its two buffers, and the last bead kernel
+// copies the result to where a pass leaves it.  That is decided with the plans (plan[kPlanWhole]
+// of every unit); a whole pass is followed by whole ones until the fibers are placed anew, since
+// the next march may start before that copy has ended.  The kernels know whole passes where
+// their simulation (some simulation of the batch) has several fibers (SEV): one fiber's would
+// take 1-3 % longer with them (64 channels, float32: 132.7 against 134.6 ms per 1000 steps).
 struct PatchUnit {
     char* patch;                   // the first buffer; the second patch_bytes further
     long long patch_bytes;
@@ -101,8 +110,8 @@ struct PatchUnit {
     int tile_h;                    // rows of a tile: kPatchY times the rows of a thread
 };
 // A plan: the patch rectangle (first column, width, first row, height: the partition grown by
-// the kPassSteps - 1 nodes the first step needs around it) and the number of its tiles that
-// any step updates; each bead's support box when the plan was made; per step t = 1 ..
+// the kPassSteps - 1 nodes the first step needs around it), the number of its tiles that any
+// step updates and whether the pass is a whole one; each bead's support box when the plan was made; per step t = 1 ..
 // kPassSteps and patch row the columns [lo, hi) that the step updates, relative to the
 // rectangle (the last step's are the partition itself); and those tiles (ty << 16 | tx).
 constexpr int kPatchX = 32, kPatchY = 8;   // threads of a tile of the patch kernel
@@ -110,6 +119,7 @@ constexpr int kPatchRows = 1;              // rows of a thread: one simulation
 // and a batch, where the tiles fill the device several times over and a block's fixed chain of
 // loads and barriers counts (float32 sweep: 142.7 / 137.3 / 142.2 ms per 1000 steps with 1 / 2 / 4)
 constexpr int kBatchPatchRows = 2;
+constexpr int kPlanWhole = 5;
 constexpr int kPlanBoxes = 8;
 constexpr int kPlanRows = kPlanBoxes + 4 * kMaxBeads;
 constexpr int plan_tiles_at(int cap_h) { return kPlanRows + 2 * kPassSteps * cap_h; }
@@ -267,7 +277,8 @@ int march_kind(int storage, const Lattice& L, bool force);
 int march_cols(int storage, const Lattice& L);
 hipError_t launch_batch_pass_setup(const BatchArgs& b, int sims, hipStream_t st);
 hipError_t launch_batch_patch(int storage, const BatchArgs& b, const int counts[5],
-                              bool any_periodic, bool any_record, hipStream_t st);
+                              bool any_periodic, bool any_several, bool any_record,
+                              hipStream_t st);
 hipError_t launch_batch_march(int storage, const BatchArgs& b, const int kind_count[kMarchKinds],
                               hipStream_t st);
 // excluded-volume forces of the step's start into BeadState::Fev (before the lattice step;

@@ -851,34 +851,42 @@ __global__ void __launch_bounds__(256) fiber_kernel(StepArgs a) {
 
 // ------------------------------------------------------- the fibers' part of a pass ----
 
-__device__ inline View patch_view(const PatchUnit& u, PlanPtr plan, const Lattice& L,
-                                  const void* whole, int which) {
-    if (which < 0) return View{whole, 0, 0, L.stride, L.plane};
-    return View{u.patch + which * u.patch_bytes, plan[0], plan[2], 9 * u.pitch, u.pitch};
+// Where step t of a pass has left its populations (t = 0: where the pass starts).
+__device__ inline View step_view(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
+                                 bool whole) {
+    if (whole) return View{t & 1 ? a.dst : a.src, 0, 0, a.L.stride, a.L.plane};
+    if (t == 0) return View{a.src, 0, 0, a.L.stride, a.L.plane};
+    if (t == kPassSteps) return View{a.dst, 0, 0, a.L.stride, a.L.plane};
+    return View{u.patch + ((t + 1) & 1) * u.patch_bytes, plan[0], plan[2], 9 * u.pitch, u.pitch};
 }
-// The patch buffer step t reads (t - 1 wrote it) and the one it writes; -1: the lattice's.
-__device__ inline int patch_src(int t) { return t > 1 ? (t & 1) : -1; }
-__device__ inline int patch_dst(int t) { return t < kPassSteps ? ((t + 1) & 1) : -1; }
+static_assert(kPassSteps % 2 == 0, "a whole pass ends in the buffer that it started from");
 
-// The plan of unit u for the pass that starts from buffer `slot`; every thread of one 1-D block.
-__device__ inline void unit_make_plan(const StepArgs& a, const PatchUnit& u, int slot,
-                                      PlanLds& sm) {
-    if (make_plan(PlanBlock(), a.L, a.fib.rc, a.fib.bs->R, u, u.plan + slot * u.plan_len, sm) &&
-        threadIdx.x == 0)
-        atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
+// The plan of unit u, one of n, for the pass that starts from buffer `slot`; every thread of one
+// 1-D block.
+__device__ inline void unit_make_plan(const StepArgs& a, const PatchUnit& u,
+                                      const PatchUnit* units, int n, int slot, PlanLds& sm) {
+    if (!make_plan(PlanBlock(), a.L, a.fib.rc, a.fib.bs->R, u, u.plan + slot * u.plan_len, sm))
+        return;
+    if (n == 1) {
+        if (threadIdx.x == 0) atomicOr(&a.fib.bs->health, FPD_HEALTH_SUPPORT);
+        return;
+    }
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+        units[i].plan[slot * u.plan_len + kPlanWhole] = 1;
 }
 
 // The next pass's plan, by a block of the bead kernel of step kPassSteps - 1, beside the beads:
 // each position is read as it was before or after its update, either at most two steps from
 // the pass's first, which the margin covers.
-__device__ inline void next_plan(const StepArgs& a, const PatchUnit& u, int slot, PlanLds& sm) {
-    unit_make_plan(a, u, 1 - slot, sm);
+__device__ inline void next_plan(const StepArgs& a, const PatchUnit& u, const PatchUnit* units,
+                                 int n, int slot, PlanLds& sm) {
+    unit_make_plan(a, u, units, n, 1 - slot, sm);
 }
 
 __global__ void __launch_bounds__(256) pass_setup_kernel(StepArgs a, PassArgs q) {
     __shared__ PlanLds sm;
     const PatchUnit u = load_unit(q.units, blockIdx.x);
-    unit_make_plan(a, u, q.slot, sm);
+    unit_make_plan(a, u, q.units, q.n_units, q.slot, sm);
 }
 
 // The patch and bead kernels of a pass are the latency chain beside the march: their waves
@@ -892,9 +900,10 @@ __device__ inline void chain_priority() { __builtin_amdgcn_s_setprio(3); }
 // tile of its plan, and one more for the bookkeeping.  Nodes that two fibers' partitions
 // share are computed by both, alike.  32 x 8 nodes: a fiber at an angle leaves out more of
 // narrow tiles, and a tile gathers fewer beads than 64 x 4 ones.
+// whole: a tile of the lattice.
 template <int ST, int BC, int ROWS>
 __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
-                                  const Window& win, int tx, int ty, TileLds& lds) {
+                                  bool whole, const Window& win, int tx, int ty, TileLds& lds) {
     using Cd = Codec<ST>;
     using T = typename Cd::T;
     using S = typename Cd::store_t;
@@ -902,8 +911,9 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     const bool per = periodic_of(BC, a);
     const int nx = a.L.nx, ny = a.L.ny;
     const int cx = tx * kPatchX, cy = ty * (ROWS * kPatchY);
-    const int cw = min(kPatchX, plan[1] - cx), ch = min(ROWS * kPatchY, plan[3] - cy);
-    int x0 = plan[0] + cx, y0 = plan[2] + cy;
+    const int cw = min(kPatchX, (whole ? nx : plan[1]) - cx);
+    const int ch = min(ROWS * kPatchY, (whole ? ny : plan[3]) - cy);
+    int x0 = whole ? cx : plan[0] + cx, y0 = whole ? cy : plan[2] + cy;
     if (x0 >= nx) x0 -= nx;
     if (per && y0 >= ny) y0 -= ny;
     const int lx = threadIdx.x % kPatchX, ly = threadIdx.x / kPatchX;
@@ -916,7 +926,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     for (int r = 0; r < ROWS; ++r) {
         const int l = ly + r * kPatchY;
         in[r] = l < ch && lx < cw;
-        if (in[r]) {
+        if (in[r] && !whole) {
             const int2 c = plan_row(u, plan, t, cy + l);
             in[r] = cx + lx >= c.x && cx + lx < c.y;
         }
@@ -926,7 +936,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     }
     if (t > 1 && !__syncthreads_or(any)) return;  // a tile of an earlier step's ring
     const T u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
-    const View v = patch_view(u, plan, a.L, a.src, patch_src(t));
+    const View v = step_view(a, u, plan, t - 1, whole);
     T g[ROWS][9];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -934,7 +944,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     TileBead<T>* sB = (TileBead<T>*)lds.beads;
     const int nb = gather_beads<T, true>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
                                    lds.bonds, false);
-    const View o = patch_view(u, plan, a.L, a.dst, patch_dst(t));
+    const View o = step_view(a, u, plan, t, whole);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         if (!in[r]) continue;
@@ -967,9 +977,13 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
 // The bookkeeping of a unit (its last block): for the first unit that of any step, and the
 // check that the unit's beads stayed near enough to where the plan found them for the partition
 // to hold what the rest of the pass needs.
-__device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
-                                    bool first, const Window& win) {
+__device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int slot,
+                                    int t, bool whole, bool first, const Window& win) {
     if (first) step_duties(a, win, false);
+    if (whole) {
+        if (threadIdx.x == 0) u.plan[(1 - slot) * u.plan_len + kPlanWhole] = 1;
+        return;
+    }
     for (int i = threadIdx.x; i < u.n; i += blockDim.x) {
         const double Rx = a.fib.bs->R[u.first + i][0], Ry = a.fib.bs->R[u.first + i][1];
         if (!bead_sane(Rx, Ry)) continue;
@@ -978,30 +992,40 @@ __device__ inline void patch_duties(const StepArgs& a, const PatchUnit& u, PlanP
     }
 }
 
-template <int ST, int BC, int ROWS>
-__device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int blocks, int slot,
-                                   int t, int k, bool first, TileLds& lds) {
+// Block k of unit `unit` of n_units, `blocks` (and the bookkeeping) each.
+template <int ST, int BC, int ROWS, bool SEV>
+__device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int unit, int n_units,
+                                   int blocks, int slot, int t, int k, TileLds& lds) {
     const Window win = tile_window(a);
     PlanPtr plan = unit_plan(u, slot);
+    const bool whole = SEV && plan[kPlanWhole] != 0;
     if (k == blocks) {
-        patch_duties(a, u, plan, t, first, win);
+        patch_duties(a, u, plan, slot, t, whole, unit == 0, win);
         return;
     }
     PlanPtr list = plan + plan_tiles_at(u.cap_h);
-    const int tiles = plan[4];
-    for (int i = k; i < tiles; i += blocks) {
-        const int e = list[i];
-        patch_tile<ST, BC, ROWS>(a, u, plan, t, win, e & 0xffff, e >> 16, lds);
+    int tiles = plan[4], step = blocks, across = 1;
+    if (whole) {
+        across = (a.L.nx + kPatchX - 1) / kPatchX;
+        tiles = across * ((a.L.ny + ROWS * kPatchY - 1) / (ROWS * kPatchY));
+        step = blocks * n_units;
+        k += unit * blocks;
+    }
+    for (int i = k; i < tiles; i += step) {
+        const int e = whole ? 0 : list[i];
+        patch_tile<ST, BC, ROWS>(a, u, plan, t, whole, win, whole ? i % across : e & 0xffff,
+                                 whole ? i / across : e >> 16, lds);
         __syncthreads();  // the next tile's beads overwrite this one's
     }
 }
 
-template <int ST, int BC>
+template <int ST, int BC, bool SEV>
 __global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, PassArgs q) {
     __shared__ TileLds lds;
     chain_priority();
-    const PatchUnit u = pick_unit(q.unit0, q.units, blockIdx.y);
-    patch_block<ST, BC, kPatchRows>(a, u, q.blocks, q.slot, q.t, blockIdx.x, blockIdx.y == 0, lds);
+    const PatchUnit u = pick_unit(q.unit0, q.units, SEV ? blockIdx.y : 0);
+    patch_block<ST, BC, kPatchRows, SEV>(a, u, SEV ? blockIdx.y : 0, gridDim.y, q.blocks, q.slot, q.t,
+                                         blockIdx.x, lds);
 }
 
 // The passes of a batch: the plans, one block per simulation; the patch tiles and the beads of
@@ -1014,12 +1038,12 @@ __global__ void __launch_bounds__(256) batch_pass_setup_kernel(BatchArgs b) {
     const PassSim p = load_pass(b.pass, s);
     for (int i = 0; i < p.n_units; ++i) {
         const PatchUnit u = load_unit(p.units, i);
-        unit_make_plan(a, u, b.gpar, sm);
+        unit_make_plan(a, u, p.units, p.n_units, b.gpar, sm);
         __syncthreads();
     }
 }
 
-template <int ST, int BC>
+template <int ST, int BC, bool SEV>
 __global__ void __launch_bounds__(kPatchX * kPatchY) batch_patch_kernel(BatchArgs b) {
     __shared__ TileLds lds;
     chain_priority();
@@ -1027,9 +1051,9 @@ __global__ void __launch_bounds__(kPatchX * kPatchY) batch_patch_kernel(BatchArg
     if ((int)blockIdx.x >= b.counts[3] || e.sim < 0) return;
     const StepArgs a = load_pass_args(b, e.sim);
     const PassSim p = load_pass(b.pass, e.sim);
-    const int per = p.blocks + 1, unit = e.local / per;
-    patch_block<ST, BC, kBatchPatchRows>(a, pick_unit(p.unit0, p.units, unit), p.blocks, b.gpar, b.t,
-                        e.local - unit * per, unit == 0, lds);
+    const int per = p.blocks + 1, unit = SEV ? e.local / per : 0;
+    patch_block<ST, BC, kBatchPatchRows, SEV>(a, pick_unit(p.unit0, p.units, unit), unit, p.n_units,
+                                              p.blocks, b.gpar, b.t, e.local - unit * per, lds);
 }
 
 // The fiber-ends recorders of a batch's simulations, ahead of a step of a pass.
@@ -1113,11 +1137,11 @@ __device__ inline void publish_support(const Fiber& fib, int win_out, double Rx,
 // PATCH: step t of a pass, whose populations are read from the view `pv` of the bead's patch;
 // pbox is the bead's box in the plan.  The support of a bead that has left it by more than the
 // margin (an unstable run; patch_duties raises FPD_HEALTH_SUPPORT) need not lie in the patch:
-// nothing is pulled for it, and its velocity is 0.
+// nothing is pulled for it, and its velocity is 0.  whole: the view is the lattice.
 template <int ST, int VB, int NT, bool PATCH = false>
 __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int win_out,
                                   double* scratch, double* s_R, const View& pv = View{},
-                                  PlanPtr pbox = nullptr, int t = 0) {
+                                  PlanPtr pbox = nullptr, int t = 0, bool whole = false) {
     constexpr int R = kBeadLanes / NT;
     using Cd = Codec<ST>;
     using T = typename Cd::T;
@@ -1155,7 +1179,7 @@ __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int
         const int rows = j1 - j0 + 1;
         int total = (rows > 0 && w > 0) ? rows * w : 0;
         if constexpr (PATCH)
-            if (!bead_in_plan(box, span, t)) total = 0;
+            if (!whole && !bead_in_plan(box, span, t)) total = 0;
         const Window win = decode_window(wraw, nx, ny, per, fib.rect_wmax, fib.rect_hmax);
         const int wx0 = win.x0, wy0 = win.y0, ww = win.w, wh = win.h;
         const T* rf = (const T*)fib.rect_f;
@@ -1286,12 +1310,24 @@ __global__ void __launch_bounds__(kBeadBlock) bead_kernel(StepArgs a, int do_vel
                                               s_R);
 }
 
+// The end of a whole pass: block k of n copies its share of the lattice, which step kPassSteps
+// left where the pass started, to where it ends.
+template <int ST>
+__device__ inline void copy_whole(const StepArgs& a, int k, int n) {
+    const long long words = (long long)a.L.ny * a.L.stride * (int)sizeof(typename Codec<ST>::store_t) / 16;
+    const uint4* s = (const uint4*)a.src;
+    uint4* d = (uint4*)a.dst;
+    for (long long i = (long long)k * blockDim.x + threadIdx.x; i < words;
+         i += (long long)n * blockDim.x)
+        d[i] = s[i];
+}
+
 // The bead kernel of a step of a pass.  It runs beside the march, whose waves hold most of
 // the registers: in FP64 a block of a wave per SIMD still fits where the usual two do not
 // (the sums are over the same virtual lanes in the same order).
 template <int ST> constexpr int kPatchBeadBlock = ST == FPD_F64 ? 256 : kBeadBlock;
 
-template <int ST>
+template <int ST, bool SEV>
 __global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArgs a, PassArgs q,
                                                                          int win_out) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
@@ -1299,15 +1335,17 @@ __global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArg
     __shared__ PlanLds sm;
     chain_priority();
     if ((int)blockIdx.x >= a.fib.n) {  // (step kPassSteps - 1 only)
-        next_plan(a, pick_unit(q.unit0, q.units, (int)blockIdx.x - a.fib.n), q.slot, sm);
+        next_plan(a, pick_unit(q.unit0, q.units, (int)blockIdx.x - a.fib.n), q.units, q.n_units, q.slot, sm);
         return;
     }
-    const int unit = (int)blockIdx.x / a.fib.chain_len;
+    const int unit = SEV ? (int)blockIdx.x / a.fib.chain_len : 0;
     const PatchUnit u = pick_unit(q.unit0, q.units, unit);
     PlanPtr plan = unit_plan(u, q.slot);
+    const bool whole = SEV && plan[kPlanWhole] != 0;
     bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
-        a, blockIdx.x, 1, win_out, scratch, s_R, patch_view(u, plan, a.L, a.dst, patch_dst(q.t)),
-        plan + kPlanBoxes + 4 * ((int)blockIdx.x - u.first), q.t);
+        a, blockIdx.x, 1, win_out, scratch, s_R, step_view(a, u, plan, q.t, whole),
+        plan + kPlanBoxes + 4 * ((int)blockIdx.x - (SEV ? u.first : 0)), q.t, whole);
+    if (whole && q.t == kPassSteps) copy_whole<ST>(a, blockIdx.x, a.fib.n);
 }
 
 // Bead kernel over a batch: one block per (simulation, bead) item.
@@ -1326,7 +1364,7 @@ __global__ void __launch_bounds__(kBatchBeadBlock) batch_bead_kernel(BatchArgs b
 // The beads of step b.t of a batch's passes: 512 threads, as alone (the block of a large bead,
 // up to 101 x 101 nodes in the sweeps, is what the kernel waits for): driven-particle boxes 142.7
 // -> 129.4 ms per 2000 steps, float16 sweep 146.1 -> 140.7 per 1000, the float32 ones unchanged.
-template <int ST>
+template <int ST, bool SEV>
 __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs b) {
     __shared__ double scratch[2 * (kBeadLanes / 64)];
     __shared__ double s_R[2];
@@ -1339,7 +1377,7 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
         const StepArgs a = load_pass_args(b, s);
         const PassSim p = load_pass(b.pass, s);
         for (int i = 0; i < p.n_units; ++i) {
-            next_plan(a, pick_unit(p.unit0, p.units, i), b.gpar, sm);
+            next_plan(a, pick_unit(p.unit0, p.units, i), p.units, p.n_units, b.gpar, sm);
             __syncthreads();
         }
         return;
@@ -1348,12 +1386,14 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
     if (e.sim < 0) return;
     const StepArgs a = load_pass_args(b, e.sim);
     const PassSim p = load_pass(b.pass, e.sim);
-    const int unit = e.local / a.fib.chain_len;
+    const int unit = SEV ? e.local / a.fib.chain_len : 0;
     const PatchUnit u = pick_unit(p.unit0, p.units, unit);
     PlanPtr plan = unit_plan(u, b.gpar);
+    const bool whole = SEV && plan[kPlanWhole] != 0;
     bead_block<ST, kBatchBeadVelBatch, kBeadBlock, true>(
-        a, e.local, 1, 1 - a.parity, scratch, s_R, patch_view(u, plan, a.L, a.dst, patch_dst(b.t)),
-        plan + kPlanBoxes + 4 * (e.local - u.first), b.t);
+        a, e.local, 1, 1 - a.parity, scratch, s_R, step_view(a, u, plan, b.t, whole),
+        plan + kPlanBoxes + 4 * (e.local - (SEV ? u.first : 0)), b.t, whole);
+    if (whole && b.t == kPassSteps) copy_whole<ST>(a, e.local, a.fib.n);
 }
 
 // Excluded-volume forces of every bead at the step's start (one block).
@@ -1893,15 +1933,21 @@ int patch_blocks(long long nodes, int tile_h) {
     return (int)std::min<long long>(n, 1024);
 }
 
+template <int ST> static void (*patch_kernel_for(bool per, bool sev))(StepArgs, PassArgs) {
+    if (sev) return per ? patch_kernel<ST, kPeriodic, true> : patch_kernel<ST, kWalls, true>;
+    return per ? patch_kernel<ST, kPeriodic, false> : patch_kernel<ST, kWalls, false>;
+}
+
 hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st) {
     const dim3 grid(q.blocks + 1, q.n_units), block(kPatchX * kPatchY);
     const bool per = a.L.periodic != 0;
+    const bool sev = q.n_units > 1;
     void (*k)(StepArgs, PassArgs) = nullptr;
     switch (storage) {
-        case FPD_F64: k = per ? patch_kernel<FPD_F64, kPeriodic> : patch_kernel<FPD_F64, kWalls>; break;
-        case FPD_F32: k = per ? patch_kernel<FPD_F32, kPeriodic> : patch_kernel<FPD_F32, kWalls>; break;
-        case FPD_F16DEV: k = per ? patch_kernel<FPD_F16DEV, kPeriodic> : patch_kernel<FPD_F16DEV, kWalls>; break;
-        case FPD_BF16DEV: k = per ? patch_kernel<FPD_BF16DEV, kPeriodic> : patch_kernel<FPD_BF16DEV, kWalls>; break;
+        case FPD_F64: k = patch_kernel_for<FPD_F64>(per, sev); break;
+        case FPD_F32: k = patch_kernel_for<FPD_F32>(per, sev); break;
+        case FPD_F16DEV: k = patch_kernel_for<FPD_F16DEV>(per, sev); break;
+        case FPD_BF16DEV: k = patch_kernel_for<FPD_BF16DEV>(per, sev); break;
         default: return hipErrorInvalidValue;
     }
     return launch_k(k, grid, block, st, nullptr, nullptr, a, q);
@@ -1910,12 +1956,13 @@ hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipSt
 hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, int win_out,
                              hipStream_t st) {
     if (a.fib.n <= 0) return hipSuccess;
+    const bool sev = q.n_units > 1;
     void (*k)(StepArgs, PassArgs, int) = nullptr;
     switch (storage) {
-        case FPD_F64: k = patch_bead_kernel<FPD_F64>; break;
-        case FPD_F32: k = patch_bead_kernel<FPD_F32>; break;
-        case FPD_F16DEV: k = patch_bead_kernel<FPD_F16DEV>; break;
-        case FPD_BF16DEV: k = patch_bead_kernel<FPD_BF16DEV>; break;
+        case FPD_F64: k = sev ? patch_bead_kernel<FPD_F64, true> : patch_bead_kernel<FPD_F64, false>; break;
+        case FPD_F32: k = sev ? patch_bead_kernel<FPD_F32, true> : patch_bead_kernel<FPD_F32, false>; break;
+        case FPD_F16DEV: k = sev ? patch_bead_kernel<FPD_F16DEV, true> : patch_bead_kernel<FPD_F16DEV, false>; break;
+        case FPD_BF16DEV: k = sev ? patch_bead_kernel<FPD_BF16DEV, true> : patch_bead_kernel<FPD_BF16DEV, false>; break;
         default: return hipErrorInvalidValue;
     }
     const int threads = storage == FPD_F64 ? kPatchBeadBlock<FPD_F64> : kPatchBeadBlock<FPD_F32>;
@@ -1993,28 +2040,35 @@ hipError_t launch_batch_pass_setup(const BatchArgs& b, int sims, hipStream_t st)
 
 template <int ST>
 static hipError_t launch_batch_patch_t(const BatchArgs& b, const int counts[5], bool any_periodic,
-                                       bool any_record, hipStream_t st) {
+                                       bool any_several, bool any_record, hipStream_t st) {
     if (counts[2] <= 0) return hipSuccess;
     if (any_record)
         hipLaunchKernelGGL(batch_record_kernel, dim3(counts[0]), dim3(kBeadThreads), 0, st, b);
     const dim3 grid(counts[3]), block(kPatchX * kPatchY);
-    if (any_periodic)
-        hipLaunchKernelGGL((batch_patch_kernel<ST, kAnyBoundary>), grid, block, 0, st, b);
+    void (*patch)(BatchArgs) = nullptr;
+    if (any_several)
+        patch = any_periodic ? batch_patch_kernel<ST, kAnyBoundary, true>
+                             : batch_patch_kernel<ST, kWalls, true>;
     else
-        hipLaunchKernelGGL((batch_patch_kernel<ST, kWalls>), grid, block, 0, st, b);
+        patch = any_periodic ? batch_patch_kernel<ST, kAnyBoundary, false>
+                             : batch_patch_kernel<ST, kWalls, false>;
+    hipLaunchKernelGGL(patch, grid, block, 0, st, b);
     const int plans = b.t == kPassSteps - 1 ? counts[0] : 0;
-    hipLaunchKernelGGL((batch_patch_bead_kernel<ST>), dim3(counts[2] + plans),
-                       dim3(kBeadBlock), 0, st, b);
+    hipLaunchKernelGGL((any_several ? batch_patch_bead_kernel<ST, true>
+                                    : batch_patch_bead_kernel<ST, false>),
+                       dim3(counts[2] + plans), dim3(kBeadBlock), 0, st, b);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_patch(int storage, const BatchArgs& b, const int counts[5],
-                              bool any_periodic, bool any_record, hipStream_t st) {
+                              bool any_periodic, bool any_several, bool any_record,
+                              hipStream_t st) {
+    const bool p = any_periodic, s = any_several, r = any_record;
     switch (storage) {
-        case FPD_F64: return launch_batch_patch_t<FPD_F64>(b, counts, any_periodic, any_record, st);
-        case FPD_F32: return launch_batch_patch_t<FPD_F32>(b, counts, any_periodic, any_record, st);
-        case FPD_F16DEV: return launch_batch_patch_t<FPD_F16DEV>(b, counts, any_periodic, any_record, st);
-        case FPD_BF16DEV: return launch_batch_patch_t<FPD_BF16DEV>(b, counts, any_periodic, any_record, st);
+        case FPD_F64: return launch_batch_patch_t<FPD_F64>(b, counts, p, s, r, st);
+        case FPD_F32: return launch_batch_patch_t<FPD_F32>(b, counts, p, s, r, st);
+        case FPD_F16DEV: return launch_batch_patch_t<FPD_F16DEV>(b, counts, p, s, r, st);
+        case FPD_BF16DEV: return launch_batch_patch_t<FPD_BF16DEV>(b, counts, p, s, r, st);
     }
     return hipErrorInvalidValue;
 }

@@ -142,6 +142,7 @@ struct fpd_sim {
     // (nullptr: no passes), and the patch kernel's blocks per unit
     PatchUnit* units = nullptr;
     PatchUnit unit0{};
+    size_t unit_bytes = 0;       // from one unit's buffers to the next's
     int n_units = 0, patch_blocks = 1;
     bool passes = false;         // the lattice takes passes
     // split steps: the fluid kernels on a side stream, the fiber and bead kernels on
@@ -617,6 +618,15 @@ bool params_equal(const fpd_params& a, const fpd_params& b) {
 // 2042 x 611 in float16 deviations passes gain (22.5 against 28.4).
 constexpr long long kMinPassNodes = 1LL << 20;
 
+// No whole passes (PatchUnit) until a plan asks for them.
+hipError_t clear_whole(fpd_sim* s) {
+    hipError_t e = hipSuccess;
+    for (int slot = 0; slot < 2 && s->n_units > 0 && e == hipSuccess; ++slot)
+        e = hipMemset2DAsync(s->unit0.plan + slot * s->unit0.plan_len + kPlanWhole, s->unit_bytes,
+                             0, sizeof(int), s->n_units, s->stream);
+    return e;
+}
+
 // The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
 // at most kMaxUnits fibers, and the patches together span at most `share` of the lattice's
 // nodes.  A simulation whose buffers cannot be allocated runs without passes.  Allocated with
@@ -664,6 +674,8 @@ int alloc_passes(fpd_sim* s, long long min_nodes, double share, int rows) {
     HIP_TRY(hipMemcpy(m, u.data(), sizeof(PatchUnit) * n_units, hipMemcpyHostToDevice));
     s->n_units = n_units;
     s->unit0 = u[0];
+    s->unit_bytes = each;
+    HIP_TRY(clear_whole(s));
     // blocks for the nodes of a straight fiber's band
     s->patch_blocks = patch_blocks((long long)((len - 1) * p.l0 + 2.0 * s->rc + grow) *
                                        (long long)(2.0 * s->rc + grow),
@@ -899,6 +911,7 @@ int fpd_init_fiber(fpd_sim* s, const double* R) {
         h.win[k][3] = -0x7fffffff;
     }
     HIP_TRY(hipMemcpyAsync(s->bs, &h, sizeof h, hipMemcpyHostToDevice, s->stream));
+    HIP_TRY(clear_whole(s));
     drop_graphs(s);
     s->part_valid = false;
     s->fiber = true;  // make_args hands the beads to the kernels only with a fiber
@@ -1479,6 +1492,7 @@ int fpd_load(fpd_sim* s, const char* path) {
     drop_graphs(s);
     s->part_valid = false;
     s->cur = s->wpar = par;
+    HIP_TRY(clear_whole(s));
     HIP_TRY(hipMemcpy(s->buf[s->cur], pops.data(), bytes, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->bs, &h, sizeof h, hipMemcpyHostToDevice));
     s->steps = steps;
@@ -1539,7 +1553,8 @@ struct fpd_batch {
     int kind_count[kMarchKinds] = {};
     bool passes = false;              // every active simulation takes passes
     bool any_record = false;          // some of them record
-    bool graph_record = false;
+    bool any_several = false;         // some of them have several fibers
+    bool graph_record = false, graph_several = false;
     std::vector<int> table;  // entry index of table row r
     bool dirty = true;
     bool pending = false;        // steps enqueued by fpd_batch_launch, not yet waited for
@@ -1601,7 +1616,7 @@ void batch_plan_passes(fpd_batch* b) {
     const int r = b->h_counts[0];
     b->h_counts[3] = b->h_counts[4] = 0;
     for (int& k : b->kind_count) k = 0;
-    b->any_record = false;
+    b->any_record = b->any_several = false;
     b->passes = r > 0;
     long long strip_rows = 0, nodes = 0;
     for (int q = 0; q < r; ++q) {
@@ -1629,6 +1644,7 @@ void batch_plan_passes(fpd_batch* b) {
         p.blocks = s->patch_blocks;
         b->h_counts[3] += p.n_units * (p.blocks + 1);
         if (s->rec) b->any_record = true;
+        if (s->n_units > 1) b->any_several = true;
         const int cols = march_cols(s->p.storage, s->L);
         p.strips = (s->L.nx + cols - 1) / cols;
         const int runs = (int)std::max<long long>(1, (s->L.ny + rows / 2) / rows);
@@ -1687,7 +1703,7 @@ int batch_rebuild(fpd_batch* b) {
     if (b->graph && (memcmp(b->graph_counts, b->h_counts, sizeof b->graph_counts) != 0 ||
                      memcmp(b->graph_kinds, b->kind_count, sizeof b->graph_kinds) != 0 ||
                      b->graph_periodic != b->any_periodic || b->graph_passes != b->passes ||
-                     b->graph_record != b->any_record))
+                     b->graph_record != b->any_record || b->graph_several != b->any_several))
         batch_drop_graph(b);  // its grids or kernel variants no longer match the tables
     // item tables (grown geometrically; a new pointer drops the graph)
     auto grow = [&](int need, int& cap, ItemRef*& d, ItemRef*& h) -> int {
@@ -1771,7 +1787,8 @@ int batch_enqueue_passes(fpd_batch* b, int gpar, int wpar, int64_t n) {
                                    b->stream));
         for (int t = 1; t <= kPassSteps; ++t) {
             HIP_TRY(launch_batch_patch(b->storage, batch_args(b, gpar, wpar, t), b->h_counts,
-                                       b->any_periodic, b->any_record, b->stream));
+                                       b->any_periodic, b->any_several, b->any_record,
+                                       b->stream));
             wpar = 1 - wpar;
         }
         gpar = 1 - gpar;
@@ -1818,6 +1835,7 @@ int batch_build_graph(fpd_batch* b, int chunk) {
     memcpy(b->graph_kinds, b->kind_count, sizeof b->graph_kinds);
     b->graph_passes = b->passes;
     b->graph_record = b->any_record;
+    b->graph_several = b->any_several;
     b->graph_periodic = b->any_periodic;
     return FPD_OK;
 }
