@@ -369,7 +369,8 @@ int fpd_run_static(const fpd_params *p, void *hip_stream, void *f_a, void *f_b,
  * (Sec. IV: stiffness, Re_ps 1-10, confinement) is the intended use.  Per-simulation
  * arithmetic is the single-simulation path's, so a result is bitwise the same alone and
  * in any mix.  Active simulations of about 0.8 million nodes or more together take passes of
- * four steps (fpd_step), all on the batch's stream, where every one of them can. */
+ * four steps (fpd_step), all on the batch's stream, where every one of them can and their
+ * patch buffers fit the budget. */
 
 typedef struct fpd_batch fpd_batch;
 
@@ -377,12 +378,17 @@ typedef struct fpd_batch fpd_batch;
 #define FPD_SIM_DONE    1   /* reached its step target; results readable until release   */
 #define FPD_SIM_FAILED  2   /* evicted by a health check (FPD_HEALTH_* bits set)          */
 
-/* Device bytes one simulation of p occupies in a batch (populations, fiber window, bead
- * state). */
+/* Device bytes one simulation of p occupies in a batch: populations, fiber window, bead
+ * state and, from 16384 nodes on and where p can take passes (not FPD_FLAG_NO_SPLIT, no
+ * excluded volume), its patch buffers.  A budget of the members' footprints holds them with
+ * their passes. */
 size_t fpd_sim_footprint(const fpd_params *p);
 
-/* A batch for the parameter sweeps of Sec. IV (Figs. 7-10): hbm_budget_bytes caps the sum
- * of footprints of held simulations; max_slots caps their number (<= 4096); storage is one
+/* A batch for the parameter sweeps of Sec. IV (Figs. 7-10): hbm_budget_bytes caps the device
+ * bytes of the held simulations.  Populations, windows and bead states come first; patch
+ * buffers are allocated when the active members can take passes, if all of them fit the rest,
+ * and freed when a new member needs their room (single steps then; the results are the same
+ * bits).  max_slots caps their number (<= 4096); storage is one
  * of FPD_F64..FPD_BF16DEV for every member (FPD_EINVAL otherwise).  hip_stream as for
  * fpd_create.  The caller owns *out and frees it with fpd_batch_destroy. */
 int fpd_batch_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t storage,
@@ -393,8 +399,8 @@ int fpd_batch_set_launch(fpd_batch *b, const fpd_launch *cfg);
 
 /* Admit one simulation of the problem of Sec. IV.A (as fpd_create + fpd_init_fiber):
  * p->storage must be the batch's; R is host [n_beads][2] (NULL when n_beads = 0); it will
- * run n_steps >= 0 steps.  FPD_ENOMEM when no slot is free or the footprint would exceed
- * the budget (nothing is allocated then); FPD_EINVAL for invalid parameters or beads.
+ * run n_steps >= 0 steps.  FPD_ENOMEM when no slot is free or the populations, windows and
+ * bead states would exceed the budget (nothing is allocated then); FPD_EINVAL for invalid parameters or beads.
  * *sim_id > 0. */
 int fpd_batch_add(fpd_batch *b, const fpd_params *p, const double *R, int64_t n_steps,
                   int64_t *sim_id);
@@ -438,7 +444,7 @@ int fpd_batch_sim_info(fpd_batch *b, int64_t sim_id, int64_t *steps, int32_t *st
 /* Free a held simulation (any status). */
 int fpd_batch_release(fpd_batch *b, int64_t sim_id);
 
-/* Active and held simulation counts and device bytes in use. */
+/* Active and held simulation counts and device bytes in use (patch buffers included). */
 int fpd_batch_stats(fpd_batch *b, int32_t *active, int32_t *held, size_t *bytes_in_use);
 
 void fpd_batch_destroy(fpd_batch *b);

@@ -1141,7 +1141,7 @@ __device__ inline void publish_support(const Fiber& fib, int win_out, double Rx,
 template <int ST, int VB, int NT, bool PATCH = false>
 __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int win_out,
                                   double* scratch, double* s_R, const View& pv = View{},
-                                  PlanPtr pbox = nullptr, int t = 0, bool whole = false) {
+                                  const int* pbox = nullptr, int t = 0, bool whole = false) {
     constexpr int R = kBeadLanes / NT;
     using Cd = Codec<ST>;
     using T = typename Cd::T;
@@ -1161,10 +1161,7 @@ __device__ inline void bead_block(const StepArgs& a, int b, int do_velocity, int
     int box[4] = {0, -1, 0, -1};  // (read with them, not behind the position)
     if constexpr (PATCH)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            box[q] = pbox[q];
-            asm volatile("" : "+s"(box[q]));
-        }
+        for (int q = 0; q < 4; ++q) box[q] = pbox[q];
 
     double Vx = 0.0, Vy = 0.0;  // valid in thread 0
     if (do_velocity) {
@@ -1344,7 +1341,8 @@ __global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArg
     const bool whole = SEV && plan[kPlanWhole] != 0;
     bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
         a, blockIdx.x, 1, win_out, scratch, s_R, step_view(a, u, plan, q.t, whole),
-        plan + kPlanBoxes + 4 * ((int)blockIdx.x - (SEV ? u.first : 0)), q.t, whole);
+        u.plan + q.slot * u.plan_len + kPlanBoxes + 4 * ((int)blockIdx.x - (SEV ? u.first : 0)),
+        q.t, whole);
     if (whole && q.t == kPassSteps) copy_whole<ST>(a, blockIdx.x, a.fib.n);
 }
 
@@ -1392,7 +1390,8 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
     const bool whole = SEV && plan[kPlanWhole] != 0;
     bead_block<ST, kBatchBeadVelBatch, kBeadBlock, true>(
         a, e.local, 1, 1 - a.parity, scratch, s_R, step_view(a, u, plan, b.t, whole),
-        plan + kPlanBoxes + 4 * (e.local - (SEV ? u.first : 0)), b.t, whole);
+        u.plan + b.gpar * u.plan_len + kPlanBoxes + 4 * (e.local - (SEV ? u.first : 0)), b.t,
+        whole);
     if (whole && b.t == kPassSteps) copy_whole<ST>(a, e.local, a.fib.n);
 }
 

@@ -8,9 +8,14 @@
 
 namespace fpd {
 
+// Whether the patch blocks take the whole lattice in the pass of plan `slot` (PatchUnit).
+__device__ static inline bool whole_pass(const PatchUnit* units, int n, int slot) {
+    return n > 1 && unit_plan(load_unit(units, 0), slot)[kPlanWhole] != 0;
+}
+
 template <int ST, int C, int OL, int BC, bool FORCE>
 __global__ void __launch_bounds__(64) march_kernel(MarchArgs a) {
-    if (a.whole && *(PlanPtr)a.whole) return;
+    if (whole_pass(a.units, a.n_units, a.slot)) return;
     const int strip = (int)blockIdx.x % a.strips, seg = (int)blockIdx.x / a.strips;
     const int y0 = seg * a.seg_rows, y1 = min(y0 + a.seg_rows, a.L.ny);
     March<ST, kPassSteps, C, OL, BC, FORCE> m;
@@ -18,8 +23,7 @@ __global__ void __launch_bounds__(64) march_kernel(MarchArgs a) {
 }
 
 __host__ __device__ static inline MarchArgs march_args(const StepArgs& a,
-                                                       const PatchUnit* units,
-                                                       const PatchUnit& unit0, int n_units,
+                                                       const PatchUnit* units, int n_units,
                                                        int slot, int strips, int seg_rows) {
     MarchArgs m;
     m.src = a.src;
@@ -33,7 +37,6 @@ __host__ __device__ static inline MarchArgs march_args(const StepArgs& a,
     m.gx = a.gx;
     m.gy = a.gy;
     m.units = units;
-    m.whole = n_units > 1 ? unit0.plan + slot * unit0.plan_len + kPlanWhole : nullptr;
     m.n_units = n_units;
     m.slot = slot;
     m.strips = strips;
@@ -48,8 +51,8 @@ __global__ void __launch_bounds__(64) batch_march_kernel(BatchArgs b, int first)
     if (first + (int)blockIdx.x >= b.counts[4] || e.sim < 0) return;
     const StepArgs s = load_args(b.args, 2 * e.sim + b.gpar);
     const PassSim p = load_pass(b.pass, e.sim);
-    const MarchArgs a = march_args(s, p.units, p.unit0, p.n_units, b.gpar, p.strips, p.seg_rows);
-    if (a.whole && *(PlanPtr)a.whole) return;
+    const MarchArgs a = march_args(s, p.units, p.n_units, b.gpar, p.strips, p.seg_rows);
+    if (whole_pass(a.units, a.n_units, a.slot)) return;
     const int strip = e.local % a.strips, seg = e.local / a.strips;
     const int y0 = seg * a.seg_rows, y1 = min(y0 + a.seg_rows, a.L.ny);
     March<ST, kPassSteps, C, OL, BC, FORCE> m;
@@ -78,7 +81,7 @@ static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream
     const int strips = (a.L.nx + OL * C - 1) / (OL * C);
     const int waves = q.n_units >= kMarchManyUnits ? kMarchWavesMany : kMarchWaves;
     const int runs = std::max(1, std::min(waves / strips, a.L.ny / kMarchMinRows));
-    const MarchArgs m = march_args(a, q.units, q.unit0, q.n_units, q.slot, strips,
+    const MarchArgs m = march_args(a, q.units, q.n_units, q.slot, strips,
                                    (a.L.ny + runs - 1) / runs);
     const int segs = (a.L.ny + m.seg_rows - 1) / m.seg_rows;
     const bool force = a.gx != 0.0 || a.gy != 0.0, per = a.L.periodic != 0;

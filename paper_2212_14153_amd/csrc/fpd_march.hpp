@@ -150,7 +150,6 @@ struct MarchArgs {
     Lattice L;
     double u6, s_nu, s_q, s_e, s_eps, gx, gy;
     const PatchUnit* units;     // whose partitions (in plan `slot`) are not stored
-    const int* whole;           // of unit 0's plan (one unit or none: nullptr)
     int n_units, slot;
     int strips, seg_rows;       // tiles: strips of columns, runs of rows
 };

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -143,6 +144,7 @@ struct fpd_sim {
     PatchUnit* units = nullptr;
     PatchUnit unit0{};
     size_t unit_bytes = 0;       // from one unit's buffers to the next's
+    size_t pass_bytes = 0;       // of that allocation
     int n_units = 0, patch_blocks = 1;
     bool passes = false;         // the lattice takes passes
     // split steps: the fluid kernels on a side stream, the fiber and bead kernels on
@@ -620,68 +622,113 @@ constexpr long long kMinPassNodes = 1LL << 20;
 
 // No whole passes (PatchUnit) until a plan asks for them.
 hipError_t clear_whole(fpd_sim* s) {
-    hipError_t e = hipSuccess;
-    for (int slot = 0; slot < 2 && s->n_units > 0 && e == hipSuccess; ++slot)
-        e = hipMemset2DAsync(s->unit0.plan + slot * s->unit0.plan_len + kPlanWhole, s->unit_bytes,
-                             0, sizeof(int), s->n_units, s->stream);
+    const PatchUnit& u = s->unit0;
+    const size_t slot = sizeof(int) * u.plan_len;
+    if (s->n_units == 0) return hipSuccess;
+    if (s->n_units == 1)
+        return hipMemset2DAsync(u.plan + kPlanWhole, slot, 0, sizeof(int), 2, s->stream);
+    hipError_t e = hipMemset2DAsync(u.plan + kPlanWhole, s->unit_bytes, 0, sizeof(int),
+                                    s->n_units, s->stream);
+    if (e == hipSuccess)
+        e = hipMemset2DAsync(u.plan + u.plan_len + kPlanWhole, s->unit_bytes, 0, sizeof(int),
+                             s->n_units, s->stream);
     return e;
 }
 
-// The patch buffers and plans of the passes, where a lattice takes them: the march handles it,
-// at most kMaxUnits fibers, and the patches together span at most `share` of the lattice's
-// nodes.  A simulation whose buffers cannot be allocated runs without passes.  Allocated with
-// the simulation, so that a step never allocates.
-int alloc_passes(fpd_sim* s, long long min_nodes, double share, int rows) {
+Lattice lattice_of(const fpd_params& p) {
+    Lattice L{};
+    L.nx = p.nx;
+    L.ny = p.ny;
+    // the nine direction rows of a lattice row lie side by side: value (k, y, x) sits at
+    // y * stride + k * plane + x with plane = padded nx and stride = 9 * plane
+    L.plane = padded_stride(p.nx);
+    L.stride = 9 * padded_stride(p.nx);
+    L.periodic = p.boundary == FPD_PERIODIC ? 1 : 0;
+    return L;
+}
+
+double cutoff_radius(const fpd_params& p) {
+    return p.radius + (p.cutoff > 0.0 ? p.cutoff : default_cutoff(p.storage)) * p.xi;
+}
+
+size_t round_256(size_t v) { return (v + 255) / 256 * 256; }
+
+// What the passes of a simulation need: its fibers' patch buffers and plans, in one allocation of
+// `bytes` that starts with the units (0 without beads).
+struct PassNeed {
+    int n_units = 0, len = 0, w = 0, h = 0, pitch = 0;
+    size_t patch = 0, each = 0, bytes = 0;
+};
+
+// Whether a lattice can take passes, and what they need: the march handles it, at most kMaxUnits
+// fibers, and the patches together span at most `share` of the lattice's nodes.
+bool pass_need(const fpd_params& p, double share, PassNeed& q) {
+    q = PassNeed{};
+    if (!march_ok(p.storage, lattice_of(p))) return false;
+    if (p.n_beads <= 0) return true;
+    q.n_units = chains_of(&p);
+    q.len = p.n_beads / q.n_units;
+    if (q.n_units > kMaxUnits) return false;
+    plan_caps(q.len, p.l0, cutoff_radius(p), p.nx, p.ny, q.w, q.h);
+    if ((double)q.w * q.h * q.n_units > share * (double)p.nx * p.ny) return false;
+    q.pitch = (q.w + 15) / 16 * 16;
+    q.patch = round_256((size_t)9 * q.pitch * q.h * storage_elem(p.storage));
+    q.each = 2 * q.patch + round_256(sizeof(int) * 2 * (size_t)plan_ints(q.w, q.h));
+    q.bytes = round_256(sizeof(PatchUnit) * q.n_units) + q.n_units * q.each;
+    return true;
+}
+
+// Gives a simulation what pass_need found (rows: of a thread of the patch kernel); without memory
+// for it, it runs without passes.
+int give_passes(fpd_sim* s, const PassNeed& q, int rows) {
     const fpd_params& p = s->p;
-    const long long nodes = (long long)p.nx * p.ny;
-    if (!march_ok(p.storage, s->L) || nodes < min_nodes) return FPD_OK;
-    if (p.n_beads <= 0) {
+    if (q.bytes == 0) {
         s->passes = true;
         return FPD_OK;
     }
-    const int n_units = chains_of(&p), len = p.n_beads / n_units;
-    if (n_units > kMaxUnits) return FPD_OK;
-    int w = 0, h = 0;
-    plan_caps(len, p.l0, s->rc, p.nx, p.ny, w, h);
-    const int grow = 2 * (kPassMargin + kPassSteps - 1);
-    if ((double)w * h * n_units > share * (double)nodes) return FPD_OK;
-    const int pitch = (w + 15) / 16 * 16;
-    const size_t patch = (size_t)9 * pitch * h * s->elem;
-    const size_t plan = sizeof(int) * 2 * (size_t)plan_ints(w, h);
-    auto round = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t table = round(sizeof(PatchUnit) * n_units);
-    const size_t each = 2 * round(patch) + round(plan);
     char* m = nullptr;
-    if (hipMalloc((void**)&m, table + n_units * each) != hipSuccess) {
+    if (hipMalloc((void**)&m, q.bytes) != hipSuccess) {
         (void)hipGetLastError();
         return FPD_OK;
     }
     s->units = (PatchUnit*)m;
-    std::vector<PatchUnit> u(n_units);
-    for (int i = 0; i < n_units; ++i) {
-        char* b = m + table + i * each;
+    s->pass_bytes = q.bytes;
+    std::vector<PatchUnit> u(q.n_units);
+    for (int i = 0; i < q.n_units; ++i) {
+        char* b = m + round_256(sizeof(PatchUnit) * q.n_units) + i * q.each;
         u[i].patch = b;
-        u[i].patch_bytes = (long long)round(patch);
+        u[i].patch_bytes = (long long)q.patch;
         u[i].tile_h = kPatchY * rows;
-        u[i].plan = (int*)(b + 2 * round(patch));
-        u[i].plan_len = plan_ints(w, h);
-        u[i].pitch = pitch;
-        u[i].cap_w = w;
-        u[i].cap_h = h;
-        u[i].first = i * len;
-        u[i].n = len;
+        u[i].plan = (int*)(b + 2 * q.patch);
+        u[i].plan_len = plan_ints(q.w, q.h);
+        u[i].pitch = q.pitch;
+        u[i].cap_w = q.w;
+        u[i].cap_h = q.h;
+        u[i].first = i * q.len;
+        u[i].n = q.len;
     }
-    HIP_TRY(hipMemcpy(m, u.data(), sizeof(PatchUnit) * n_units, hipMemcpyHostToDevice));
-    s->n_units = n_units;
+    HIP_TRY(hipMemcpy(m, u.data(), sizeof(PatchUnit) * q.n_units, hipMemcpyHostToDevice));
+    s->n_units = q.n_units;
     s->unit0 = u[0];
-    s->unit_bytes = each;
+    s->unit_bytes = q.each;
     HIP_TRY(clear_whole(s));
     // blocks for the nodes of a straight fiber's band
-    s->patch_blocks = patch_blocks((long long)((len - 1) * p.l0 + 2.0 * s->rc + grow) *
-                                       (long long)(2.0 * s->rc + grow),
+    const double grow = 2 * (kPassMargin + kPassSteps - 1), wide = 2.0 * s->rc + grow;
+    s->patch_blocks = patch_blocks((long long)fmin(((q.len - 1) * p.l0 + wide) * wide,
+                                                   (double)p.nx * p.ny),
                                    kPatchY * rows);
     s->passes = true;
     return FPD_OK;
+}
+
+// Takes them back (no kernel of the simulation running).
+void drop_passes(fpd_sim* s) {
+    if (s->units) (void)hipFree(s->units);
+    s->units = nullptr;
+    s->unit0 = PatchUnit{};
+    s->n_units = 0;
+    s->pass_bytes = 0;
+    s->passes = false;
 }
 
 int create_impl(const fpd_params* p, void* stream, void* fa, void* fb, size_t bytes_each,
@@ -693,16 +740,10 @@ int create_impl(const fpd_params* p, void* stream, void* fa, void* fb, size_t by
     fpd_sim* s = new fpd_sim();
     memset(&s->p, 0, sizeof s->p);
     s->p = *p;
-    s->L.nx = p->nx;
-    s->L.ny = p->ny;
-    // the nine direction rows of a lattice row lie side by side: value (k, y, x) sits at
-    // y * stride + k * plane + x with plane = padded nx and stride = 9 * plane
-    s->L.plane = padded_stride(p->nx);
-    s->L.stride = 9 * padded_stride(p->nx);
-    s->L.periodic = p->boundary == FPD_PERIODIC ? 1 : 0;
+    s->L = lattice_of(*p);
     s->elem = storage_elem(p->storage);
     s->buf_bytes = (size_t)p->ny * (size_t)s->L.stride * s->elem;
-    s->rc = p->radius + (p->cutoff > 0.0 ? p->cutoff : default_cutoff(p->storage)) * p->xi;
+    s->rc = cutoff_radius(*p);
     s->launch = default_launch(p->storage, 64, (long long)p->nx * p->ny);
     auto bail = [&](int code) {
         fpd_destroy(s);
@@ -814,9 +855,13 @@ size_t fpd_population_bytes(const fpd_params* p) {
     return (size_t)9 * (size_t)p->ny * padded_stride(p->nx) * storage_elem(p->storage);
 }
 
-// The passes of a simulation of its own (which is destroyed if that fails).
+// The passes of a simulation of its own (which is destroyed if that fails), allocated with it, so
+// that a step never allocates.
 static int create_passes(fpd_sim** out) {
-    const int rc = alloc_passes(*out, kMinPassNodes, 0.5, kPatchRows);
+    const fpd_params& p = (*out)->p;
+    PassNeed q;
+    if ((long long)p.nx * p.ny < kMinPassNodes || !pass_need(p, 0.5, q)) return FPD_OK;
+    const int rc = give_passes(*out, q, kPatchRows);
     if (rc) {
         fpd_destroy(*out);
         *out = nullptr;
@@ -854,7 +899,7 @@ void fpd_destroy(fpd_sim* s) {
             if (b) (void)hipFree(b);
     if (s->bs) (void)hipFree(s->bs);
     if (s->rect_f) (void)hipFree(s->rect_f);
-    if (s->units) (void)hipFree(s->units);
+    drop_passes(s);
     if (s->row_phi) (void)hipFree(s->row_phi);
     if (s->rec) (void)hipFree(s->rec);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -1519,6 +1564,8 @@ struct BatchEntry {
 
 struct fpd_batch {
     size_t budget = 0, used = 0;
+    size_t pass_bytes = 0;       // patch buffers of its members, in what `used` leaves of the budget
+    size_t pass_spare = 0;       // room left free for members when they are taken (batch_add)
     int max_slots = 0, storage = FPD_F32;
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -1589,9 +1636,8 @@ size_t footprint_of(const fpd_params* p) {
     const size_t pop = fpd_population_bytes(p);
     size_t rect = 0;
     if (p->n_beads > 0) {
-        const double rc = p->radius + (p->cutoff > 0.0 ? p->cutoff : default_cutoff(p->storage)) * p->xi;
         int w = 0, h = 0;
-        window_size(p, rc, w, h);
+        window_size(p, cutoff_radius(*p), w, h);
         rect = (size_t)w * (size_t)h * 2 * (p->storage == FPD_F64 ? 8 : 4);
     }
     return 2 * pop + rect + sizeof(BeadState);
@@ -1609,6 +1655,56 @@ constexpr int kBatchMarchRows = 8;
 // 14.8 M 229 / 126; the other formats gain more (four channels: float64 60.6 / 48.5, float16
 // 38.0 / 34.0).
 constexpr long long kBatchPassNodes = 3LL << 18;
+// Nodes of a simulation from which its footprint counts the patch buffers: a batch of smaller ones
+// alone needs 48 members or more for passes, and theirs (at most the populations' bytes again, 1.2
+// MB at this size in float32) find room in the slack of any budget that holds so many.
+constexpr long long kCountedPassNodes = 1LL << 14;
+
+// Whether a simulation of a batch can take passes, and what they need.  (The excluded volume between
+// fibers: batch_forces_kernel.)
+bool batch_pass_need(const fpd_params& p, PassNeed& q) {
+    if (p.flags & FPD_FLAG_NO_SPLIT) return false;
+    if (chains_of(&p) > 1 && p.ev_k > 0.0) return false;
+    return pass_need(p, 1.0, q);
+}
+
+// Takes back every member's patch buffers (with the stream idle).
+void batch_drop_passes(fpd_batch* b) {
+    for (auto& e : b->entries) drop_passes(e.sim);
+    b->pass_bytes = 0;
+    batch_drop_graph(b);
+    b->dirty = true;
+}
+
+// Whether the active simulations take passes: every one of them can, together they are large
+// enough, and their patch buffers fit what the members leave of the budget.  Allocates those.
+bool batch_take_passes(fpd_batch* b) {
+    long long nodes = 0;
+    size_t need = 0;
+    std::vector<std::pair<fpd_sim*, PassNeed>> lack;
+    for (auto& e : b->entries) {
+        if (e.status != FPD_SIM_ACTIVE || e.remaining <= 0) continue;
+        fpd_sim* s = e.sim;
+        if (s->row_phi) return false;
+        nodes += (long long)s->L.nx * s->L.ny;
+        if (s->passes) continue;
+        PassNeed q;
+        if (!batch_pass_need(s->p, q)) return false;
+        need += q.bytes;
+        lack.emplace_back(s, q);
+    }
+    if (nodes < kBatchPassNodes) return false;
+    if (need > 0 && b->used + b->pass_bytes + need + b->pass_spare > b->budget) return false;
+    for (auto& l : lack) {
+        const int rc = give_passes(l.first, l.second, kBatchPatchRows);
+        b->pass_bytes += l.first->pass_bytes;
+        if (rc || !l.first->passes) {
+            batch_drop_passes(b);
+            return false;
+        }
+    }
+    return true;
+}
 
 // Whether every active simulation takes passes, and then the counts of their items and each
 // one's tiling (h_pass; h_args filled).
@@ -1617,21 +1713,13 @@ void batch_plan_passes(fpd_batch* b) {
     b->h_counts[3] = b->h_counts[4] = 0;
     for (int& k : b->kind_count) k = 0;
     b->any_record = b->any_several = false;
-    b->passes = r > 0;
-    long long strip_rows = 0, nodes = 0;
+    b->passes = r > 0 && batch_take_passes(b);
+    if (!b->passes) return;
+    long long strip_rows = 0;
     for (int q = 0; q < r; ++q) {
         const fpd_sim* s = b->entries[b->table[q]].sim;
-        if (!use_passes(s) || has_ev(s)) {  // (the forces between fibers: batch_forces_kernel)
-            b->passes = false;
-            return;
-        }
         const int cols = march_cols(s->p.storage, s->L);
         strip_rows += (long long)((s->L.nx + cols - 1) / cols) * s->L.ny;
-        nodes += (long long)s->L.nx * s->L.ny;
-    }
-    if (nodes < kBatchPassNodes) {
-        b->passes = false;
-        return;
     }
     const long long rows = std::max<long long>(kBatchMarchRows, strip_rows / kBatchMarchTiles);
     for (int q = 0; q < r; ++q) {
@@ -1846,7 +1934,9 @@ extern "C" {
 
 size_t fpd_sim_footprint(const fpd_params* p) {
     if (!p || validate(p) != FPD_OK) return 0;
-    return footprint_of(p);
+    PassNeed q;
+    const bool counted = (long long)p->nx * p->ny >= kCountedPassNodes && batch_pass_need(*p, q);
+    return footprint_of(p) + (counted ? q.bytes : 0);
 }
 
 // FPD_EINVAL while steps enqueued by fpd_batch_launch await fpd_batch_wait.
@@ -1962,11 +2052,21 @@ int fpd_batch_add(fpd_batch* b, const fpd_params* p, const double* R, int64_t n_
     if (b->used + need > b->budget)
         return fail(FPD_ENOMEM, "HBM budget: %zu + %zu > %zu bytes", b->used, need, b->budget);
     HIP_TRY(hipStreamSynchronize(b->stream));
+    // the patch buffers make room for the member; they are taken again when there is room for
+    // them and for one more like it
+    if (b->pass_bytes > 0 && b->used + b->pass_bytes + need > b->budget) {
+        batch_drop_passes(b);
+        b->pass_spare = need;
+    }
     fpd_sim* s = nullptr;
     rc = create_impl(p, b->stream, nullptr, nullptr, 0, &s);
+    if (rc == FPD_ENOMEM && b->pass_bytes > 0) {
+        batch_drop_passes(b);
+        b->pass_spare = need;
+        rc = create_impl(p, b->stream, nullptr, nullptr, 0, &s);
+    }
     if (rc) return rc;
-    rc = alloc_passes(s, 0, 1.0, kBatchPatchRows);
-    if (rc == FPD_OK) rc = fpd_set_launch(s, &b->launch);
+    rc = fpd_set_launch(s, &b->launch);
     if (rc == FPD_OK && p->n_beads > 0) rc = fpd_init_fiber(s, R);
     if (rc) {
         fpd_destroy(s);
@@ -1981,6 +2081,7 @@ int fpd_batch_add(fpd_batch* b, const fpd_params* p, const double* R, int64_t n_
     b->entries.push_back(e);
     b->used += need;
     b->dirty = true;
+    (void)batch_take_passes(b);  // (here rather than in the first launch)
     *sim_id = e.id;
     return FPD_OK;
 }
@@ -2162,6 +2263,7 @@ int fpd_batch_release(fpd_batch* b, int64_t id) {
     for (size_t i = 0; i < b->entries.size(); ++i)
         if (b->entries[i].id == id) {
             HIP_TRY(hipStreamSynchronize(b->stream));
+            b->pass_bytes -= b->entries[i].sim->pass_bytes;
             fpd_destroy(b->entries[i].sim);
             b->used -= b->entries[i].bytes;
             b->entries.erase(b->entries.begin() + (long)i);
@@ -2178,7 +2280,7 @@ int fpd_batch_stats(fpd_batch* b, int32_t* active, int32_t* held, size_t* bytes_
         if (e.status == FPD_SIM_ACTIVE) ++a;
     if (active) *active = a;
     if (held) *held = (int)b->entries.size();
-    if (bytes_in_use) *bytes_in_use = b->used;
+    if (bytes_in_use) *bytes_in_use = b->used + b->pass_bytes;
     return FPD_OK;
 }
 
