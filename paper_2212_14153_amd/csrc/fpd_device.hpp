@@ -67,7 +67,7 @@ template <> struct Codec<FPD_F16DEV> {
         return __builtin_bit_cast(uint16_t, (_Float16)(v * kScale));
     }
     // The two-node lattice path collides the stored values as they are, g * 2^14
-    // (mrt_collide_scaled): the scale leaves the nine decodes per node.
+    // (mrt_collide_scaled_open): the scale leaves the nine decodes per node.
     static constexpr bool kScaledCollide = true;
     __device__ static inline T from_bits_scaled(uint32_t b) {
         return (float)__builtin_bit_cast(_Float16, (uint16_t)b);
@@ -813,15 +813,9 @@ __device__ inline T mrt_collide_scaled_open(T g[9], T Fx, T Fy, T s_nu, T s_q, T
     return c;
 }
 
-template <typename T, bool kForce = true>
-__device__ inline void mrt_collide_scaled(T g[9], T Fx, T Fy, T s_nu, T s_q, T s_e, T s_eps) {
-    const T z = mrt_collide_scaled_open<T, kForce>(g, Fx, Fy, s_nu, s_q, s_e, s_eps);
-    g[0] = g[0] + T(4) * z;
-}
-
 // 4 z + t rounded once to binary16, in the low (resp. low and high) half of the result.
-// Written out because the compiler narrows this FMA with one rounding in some kernels and,
-// where it packs two conversions, with two; every kernel has to store the same bits.
+// Written out in every kernel that collides binary16, since the compiler narrows this FMA with
+// one rounding in some kernels and, where it packs two conversions, with two.
 __device__ inline uint32_t narrow_fma4(float z, float t) {
     uint32_t w;
     asm("v_fma_mixlo_f16 %0, 4.0, %1, %2" : "=v"(w) : "v"(z), "v"(t));

@@ -729,14 +729,16 @@ __device__ inline void lattice_tile_group(const StepArgs& a, const Window& win, 
         pull_group<Cd, G>(src, nx, ny, stride, plane, x0, y, per, first, last, u6, g);
         if (x0 >= nx) continue;
         uint32_t bits[9][G / 2];
+        T z[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) {
             if constexpr (kScaled) {
                 if (plain)
-                    mrt_collide_scaled<T, false>(g[i], T(0), T(0), (T)a.s_nu_f, (T)a.s_q_f,
-                                                 s_e, s_eps);
+                    z[i] = mrt_collide_scaled_open<T, false>(g[i], T(0), T(0), (T)a.s_nu_f,
+                                                             (T)a.s_q_f, s_e, s_eps);
                 else
-                    mrt_collide_scaled<T>(g[i], Fx[i], Fy[i], s_nu[i], s_q[i], s_e, s_eps);
+                    z[i] = mrt_collide_scaled_open<T>(g[i], Fx[i], Fy[i], s_nu[i], s_q[i], s_e,
+                                                      s_eps);
             } else {
                 if (plain)  // no force anywhere on this tile: the unforced collision
                     mrt_collide<T, false>(g[i], T(0), T(0), (T)a.s_nu_f, (T)a.s_q_f, s_e,
@@ -746,9 +748,13 @@ __device__ inline void lattice_tile_group(const StepArgs& a, const Window& win, 
             }
         }
 #pragma unroll
-        for (int i = 0; i < G; i += 2)
+        for (int i = 0; i < G; i += 2) {
+            if constexpr (kScaled)
+                bits[0][i >> 1] = narrow_fma4(z[i], g[i][0], z[i + 1], g[i + 1][0]);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) bits[k][i >> 1] = Cd::pack2_scaled(g[i][k], g[i + 1][k]);
+            for (int k = kScaled ? 1 : 0; k < 9; ++k)
+                bits[k][i >> 1] = Cd::pack2_scaled(g[i][k], g[i + 1][k]);
+        }
         uint16_t* o = dst + (long long)y * stride + x0;
         if (x0 + G - 1 < nx) {
 #pragma unroll
