@@ -865,6 +865,25 @@ __device__ inline View step_view(const StepArgs& a, const PatchUnit& u, PlanPtr 
     if (t == kPassSteps) return View{a.dst, 0, 0, a.L.stride, a.L.plane};
     return View{u.patch + ((t + 1) & 1) * u.patch_bytes, plan[0], plan[2], 9 * u.pitch, u.pitch};
 }
+// The same for the bead kernel of step t, and whether the pass is a whole one: the plan's entries
+// are read at once, as none of them waits for another.
+template <bool SEV>
+__device__ inline View bead_view(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
+                                 bool& whole) {
+    if constexpr (!SEV) {
+        whole = false;
+        return step_view(a, u, plan, t, false);
+    } else {
+        int x0 = plan[0], y0 = plan[2], w = plan[kPlanWhole];
+        asm volatile("" : "+s"(x0), "+s"(y0), "+s"(w));
+        whole = w != 0;
+        const bool lattice = whole || t == kPassSteps;
+        const void* p = whole && !(t & 1) ? a.src : a.dst;
+        return View{lattice ? p : u.patch + ((t + 1) & 1) * u.patch_bytes, lattice ? 0 : x0,
+                    lattice ? 0 : y0, lattice ? a.L.stride : 9 * u.pitch,
+                    lattice ? a.L.plane : (long long)u.pitch};
+    }
+}
 static_assert(kPassSteps % 2 == 0, "a whole pass ends in the buffer that it started from");
 
 // The plan of unit u, one of n, for the pass that starts from buffer `slot`; every thread of one
@@ -906,10 +925,10 @@ __device__ inline void chain_priority() { __builtin_amdgcn_s_setprio(3); }
 // tile of its plan, and one more for the bookkeeping.  Nodes that two fibers' partitions
 // share are computed by both, alike.  32 x 8 nodes: a fiber at an angle leaves out more of
 // narrow tiles, and a tile gathers fewer beads than 64 x 4 ones.
-// whole: a tile of the lattice.
-template <int ST, int BC, int ROWS>
+// WHOLE: a tile of the lattice, in a whole pass.
+template <int ST, int BC, int ROWS, bool WHOLE = false>
 __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr plan, int t,
-                                  bool whole, const Window& win, int tx, int ty, TileLds& lds) {
+                                  const Window& win, int tx, int ty, TileLds& lds) {
     using Cd = Codec<ST>;
     using T = typename Cd::T;
     using S = typename Cd::store_t;
@@ -917,9 +936,9 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     const bool per = periodic_of(BC, a);
     const int nx = a.L.nx, ny = a.L.ny;
     const int cx = tx * kPatchX, cy = ty * (ROWS * kPatchY);
-    const int cw = min(kPatchX, (whole ? nx : plan[1]) - cx);
-    const int ch = min(ROWS * kPatchY, (whole ? ny : plan[3]) - cy);
-    int x0 = whole ? cx : plan[0] + cx, y0 = whole ? cy : plan[2] + cy;
+    const int cw = min(kPatchX, (WHOLE ? nx : plan[1]) - cx);
+    const int ch = min(ROWS * kPatchY, (WHOLE ? ny : plan[3]) - cy);
+    int x0 = WHOLE ? cx : plan[0] + cx, y0 = WHOLE ? cy : plan[2] + cy;
     if (x0 >= nx) x0 -= nx;
     if (per && y0 >= ny) y0 -= ny;
     const int lx = threadIdx.x % kPatchX, ly = threadIdx.x / kPatchX;
@@ -932,7 +951,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     for (int r = 0; r < ROWS; ++r) {
         const int l = ly + r * kPatchY;
         in[r] = l < ch && lx < cw;
-        if (in[r] && !whole) {
+        if (!WHOLE && in[r]) {
             const int2 c = plan_row(u, plan, t, cy + l);
             in[r] = cx + lx >= c.x && cx + lx < c.y;
         }
@@ -940,9 +959,9 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
         y[r] = y0 + l;
         if (per && y[r] >= ny) y[r] -= ny;
     }
-    if (t > 1 && !__syncthreads_or(any)) return;  // a tile of an earlier step's ring
+    if (!WHOLE && t > 1 && !__syncthreads_or(any)) return;  // a tile of an earlier step's ring
     const T u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
-    const View v = step_view(a, u, plan, t - 1, whole);
+    const View v = step_view(a, u, plan, t - 1, WHOLE);
     T g[ROWS][9];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -950,7 +969,7 @@ __device__ inline void patch_tile(const StepArgs& a, const PatchUnit& u, PlanPtr
     TileBead<T>* sB = (TileBead<T>*)lds.beads;
     const int nb = gather_beads<T, true>(a.fib, nx, ny, per, x0, cw, y0, ch, sB, lds.idx, lds.wave,
                                    lds.bonds, false);
-    const View o = step_view(a, u, plan, t, whole);
+    const View o = step_view(a, u, plan, t, WHOLE);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         if (!in[r]) continue;
@@ -1004,29 +1023,32 @@ __device__ inline void patch_block(const StepArgs& a, const PatchUnit& u, int un
                                    int blocks, int slot, int t, int k, TileLds& lds) {
     const Window win = tile_window(a);
     PlanPtr plan = unit_plan(u, slot);
+    const int tiles = plan[4];
     const bool whole = SEV && plan[kPlanWhole] != 0;
     if (k == blocks) {
         patch_duties(a, u, plan, slot, t, whole, unit == 0, win);
         return;
     }
-    PlanPtr list = plan + plan_tiles_at(u.cap_h);
-    int tiles = plan[4], step = blocks, across = 1;
-    if (whole) {
-        across = (a.L.nx + kPatchX - 1) / kPatchX;
-        tiles = across * ((a.L.ny + ROWS * kPatchY - 1) / (ROWS * kPatchY));
-        step = blocks * n_units;
-        k += unit * blocks;
+    if (SEV && __builtin_expect(whole, 0)) {  // (code of its own, out of the others' way)
+        const int across = (a.L.nx + kPatchX - 1) / kPatchX;
+        const int all = across * ((a.L.ny + ROWS * kPatchY - 1) / (ROWS * kPatchY));
+        for (int i = unit * blocks + k; i < all; i += n_units * blocks) {
+            patch_tile<ST, BC, ROWS, true>(a, u, plan, t, win, i % across, i / across, lds);
+            __syncthreads();
+        }
+        return;
     }
-    for (int i = k; i < tiles; i += step) {
-        const int e = whole ? 0 : list[i];
-        patch_tile<ST, BC, ROWS>(a, u, plan, t, whole, win, whole ? i % across : e & 0xffff,
-                                 whole ? i / across : e >> 16, lds);
+    PlanPtr list = plan + plan_tiles_at(u.cap_h);
+    for (int i = k; i < tiles; i += blocks) {
+        const int e = list[i];
+        patch_tile<ST, BC, ROWS>(a, u, plan, t, win, e & 0xffff, e >> 16, lds);
         __syncthreads();  // the next tile's beads overwrite this one's
     }
 }
 
 template <int ST, int BC, bool SEV>
-__global__ void __launch_bounds__(kPatchX * kPatchY) patch_kernel(StepArgs a, PassArgs q) {
+__global__ void __launch_bounds__(kPatchX * kPatchY)
+patch_kernel(StepArgs a, PassArgs q) {
     __shared__ TileLds lds;
     chain_priority();
     const PatchUnit u = pick_unit(q.unit0, q.units, SEV ? blockIdx.y : 0);
@@ -1050,7 +1072,8 @@ __global__ void __launch_bounds__(256) batch_pass_setup_kernel(BatchArgs b) {
 }
 
 template <int ST, int BC, bool SEV>
-__global__ void __launch_bounds__(kPatchX * kPatchY) batch_patch_kernel(BatchArgs b) {
+__global__ void __launch_bounds__(kPatchX * kPatchY)
+batch_patch_kernel(BatchArgs b) {
     __shared__ TileLds lds;
     chain_priority();
     const ItemRef e = item_ref(b.patch_items, blockIdx.x);
@@ -1344,12 +1367,13 @@ __global__ void __launch_bounds__(kPatchBeadBlock<ST>) patch_bead_kernel(StepArg
     const int unit = SEV ? (int)blockIdx.x / a.fib.chain_len : 0;
     const PatchUnit u = pick_unit(q.unit0, q.units, unit);
     PlanPtr plan = unit_plan(u, q.slot);
-    const bool whole = SEV && plan[kPlanWhole] != 0;
+    bool whole;
+    const View v = bead_view<SEV>(a, u, plan, q.t, whole);
     bead_block<ST, kBeadVelBatch, kPatchBeadBlock<ST>, true>(
-        a, blockIdx.x, 1, win_out, scratch, s_R, step_view(a, u, plan, q.t, whole),
+        a, blockIdx.x, 1, win_out, scratch, s_R, v,
         u.plan + q.slot * u.plan_len + kPlanBoxes + 4 * ((int)blockIdx.x - (SEV ? u.first : 0)),
         q.t, whole);
-    if (whole && q.t == kPassSteps) copy_whole<ST>(a, blockIdx.x, a.fib.n);
+    if (__builtin_expect(whole, 0) && q.t == kPassSteps) copy_whole<ST>(a, blockIdx.x, a.fib.n);
 }
 
 // Bead kernel over a batch: one block per (simulation, bead) item.
@@ -1393,12 +1417,13 @@ __global__ void __launch_bounds__(kBeadBlock) batch_patch_bead_kernel(BatchArgs 
     const int unit = SEV ? e.local / a.fib.chain_len : 0;
     const PatchUnit u = pick_unit(p.unit0, p.units, unit);
     PlanPtr plan = unit_plan(u, b.gpar);
-    const bool whole = SEV && plan[kPlanWhole] != 0;
+    bool whole;
+    const View v = bead_view<SEV>(a, u, plan, b.t, whole);
     bead_block<ST, kBatchBeadVelBatch, kBeadBlock, true>(
-        a, e.local, 1, 1 - a.parity, scratch, s_R, step_view(a, u, plan, b.t, whole),
+        a, e.local, 1, 1 - a.parity, scratch, s_R, v,
         u.plan + b.gpar * u.plan_len + kPlanBoxes + 4 * (e.local - (SEV ? u.first : 0)), b.t,
         whole);
-    if (whole && b.t == kPassSteps) copy_whole<ST>(a, e.local, a.fib.n);
+    if (__builtin_expect(whole, 0) && b.t == kPassSteps) copy_whole<ST>(a, e.local, a.fib.n);
 }
 
 // Excluded-volume forces of every bead at the step's start (one block).

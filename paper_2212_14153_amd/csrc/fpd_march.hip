@@ -8,14 +8,8 @@
 
 namespace fpd {
 
-// Whether the patch blocks take the whole lattice in the pass of plan `slot` (PatchUnit).
-__device__ static inline bool whole_pass(const PatchUnit* units, int n, int slot) {
-    return n > 1 && unit_plan(load_unit(units, 0), slot)[kPlanWhole] != 0;
-}
-
 template <int ST, int C, int OL, int BC, bool FORCE>
 __global__ void __launch_bounds__(64) march_kernel(MarchArgs a) {
-    if (whole_pass(a.units, a.n_units, a.slot)) return;
     const int strip = (int)blockIdx.x % a.strips, seg = (int)blockIdx.x / a.strips;
     const int y0 = seg * a.seg_rows, y1 = min(y0 + a.seg_rows, a.L.ny);
     March<ST, kPassSteps, C, OL, BC, FORCE> m;
@@ -52,7 +46,6 @@ __global__ void __launch_bounds__(64) batch_march_kernel(BatchArgs b, int first)
     const StepArgs s = load_args(b.args, 2 * e.sim + b.gpar);
     const PassSim p = load_pass(b.pass, e.sim);
     const MarchArgs a = march_args(s, p.units, p.n_units, b.gpar, p.strips, p.seg_rows);
-    if (whole_pass(a.units, a.n_units, a.slot)) return;
     const int strip = e.local % a.strips, seg = e.local / a.strips;
     const int y0 = seg * a.seg_rows, y1 = min(y0 + a.seg_rows, a.L.ny);
     March<ST, kPassSteps, C, OL, BC, FORCE> m;

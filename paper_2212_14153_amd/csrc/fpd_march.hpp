@@ -203,16 +203,19 @@ struct March {
         return off;
     }
     // The units (bits) whose patch rectangle meets the wave's tile: lane i looks at unit i.
-    __device__ inline unsigned long long units_near(int n, int c0, int cols) const {
+    // whole: the pass is a whole one (PatchUnit), in which the march does nothing.
+    __device__ inline unsigned long long units_near(int n, int c0, int cols, bool& whole) const {
         const int lane = (int)threadIdx.x & 63;
-        bool hit = false;
+        bool hit = false, all = false;
         if (lane < n) {
             const PatchUnit u = units[lane];
             const int* plan = u.plan + slot * u.plan_len;
             const int w = plan[1], h = plan[3], p0 = plan[2];
+            all = plan[kPlanWhole] != 0;
             hit = w > 0 && h > 0 && cols_overlap(c0 % nx, min(cols, nx), plan[0], w, nx) &&
                   (per ? cols_overlap(y0, y1 - y0, p0, h, ny) : (y0 < p0 + h && p0 < y1));
         }
+        whole = __ballot(all) != 0ull;
         return __ballot(hit);
     }
     __device__ inline int wrap(int y) const {
@@ -364,7 +367,8 @@ struct March {
         st = lane >= HL && lane < HL + OL && x0 < nx ? (unsigned)(x0 * (int)sizeof(S)) : kLaneOff;
         units = a.units;
         slot = a.slot;
-        near = a.n_units > 0 ? units_near(a.n_units, strip * OL * C, OL * C) : 0ull;
+        bool whole = false;
+        near = a.n_units > 0 ? units_near(a.n_units, strip * OL * C, OL * C, whole) : 0ull;
         u6 = kScaled ? (T)(a.u6 * 16384.0) : (T)a.u6;
         s_nu = (T)a.s_nu;
         s_q = (T)a.s_q;
@@ -386,6 +390,7 @@ struct March {
         const int f0 = max(y0 + NT, 1);
         const int f1 = min(hi1, ny - 1) - 3;   // last pair start: i + 3 < hi1, row i + 3 exists
         fetch<false>(lo1, q[0]);
+        if (whole) return;   // (behind the loads, which need not wait for it)
         int i = lo1;
         while (i < end) {
             row_step<false, 0>(i);
