@@ -9,8 +9,8 @@ steps replay captured graphs (the chunk divides the timed step count; the graph 
 before the timing starts).
 
 Prints ONE JSON line with MLUPS (whole step, inputs resident in HBM), the lattice kernel's
-HBM roofline (algorithmic 18 * sizeof(population) bytes per node per step over its
-dispatch-stamped duration) and a CPU baseline (the FP64 oracle on a bounded sample of the
+HBM roofline (algorithmic 18 * sizeof(population) bytes per node and launch over its
+dispatch-stamped duration; a launch takes one step, or the four of a pass: steps_per_launch) and a CPU baseline (the FP64 oracle on a bounded sample of the
 same workload).  Bounded runs of the other configurations are added as keys of the same
 line (skip them with --no-extras):
   c2          the 1024 x 256 channel with the 20-bead fiber, FP32: MLUPS and effective GB/s
@@ -658,12 +658,14 @@ def main_shapes(args):
 
 
 def choose_chunk(steps: int):
-    """Graph chunk for `steps` timed steps: the largest even c <= 64 that divides steps (then
-    every timed step runs in a replayed graph); for odd steps the largest even c <= 64 below
+    """Graph chunk for `steps` timed steps: the largest multiple of four <= 64 that divides steps,
+    else the largest even number (then every timed step runs in a replayed graph; a lattice
+    that takes passes of four rounds its chunks down to whole ones); for odd steps the largest even c <= 64 below
     steps (the last step then runs as direct launches); None below two steps."""
-    for c in range(min(64, steps), 1, -1):
-        if c % 2 == 0 and steps % c == 0:
-            return c
+    for m in (4, 2):
+        for c in range(min(64, steps), 1, -1):
+            if c % m == 0 and steps % c == 0:
+                return c
     c = min(64, steps - steps % 2)
     return c if c >= 2 else None
 
@@ -697,20 +699,24 @@ def time_steps(sim, stream, steps, warmup):
 
 
 def kernel_pass(sim, steps, warmup=4, flags=0):
-    """The same number of steps again with every lattice and bead launch stamped by its own
-    dispatch (FPD_FLAG_TIME_KERNELS added to `flags`: the steps split or whole as in the
+    """The same number of steps again (from four on a multiple of four, whole passes where
+    fpd_step takes them) with every lattice and bead launch stamped by its own dispatch
+    (FPD_FLAG_TIME_KERNELS added to `flags`: the steps in passes, split or whole as in the
     timed region), after `warmup` untimed steps in the same mode: average lattice-pass and
-    bead kernel durations in ms.  The simulation's flags are `flags` afterwards."""
+    bead kernel durations in ms and the steps of a lattice launch.  The simulation's flags are
+    `flags` afterwards."""
     from paper_2212_14153_amd import _lib
     sim.set_flags(_lib.FPD_FLAG_TIME_KERNELS | flags)
     sim.step(warmup)
     sim.sync()
     sim.reset_kernel_times()
+    steps = steps - steps % 4 if steps >= 4 else steps
     sim.step(steps)
     sim.sync()
     ms_lat, n_lat, ms_bead, n_bead = sim.kernel_times()
     sim.set_flags(flags)
-    return ms_lat / max(n_lat, 1), (ms_bead / n_bead if n_bead else 0.0)
+    return (ms_lat / max(n_lat, 1), (ms_bead / n_bead if n_bead else 0.0),
+            round(steps / max(n_lat, 1)))
 
 
 def c2_run(stream, steps=200, warmup=50, tune=True):
@@ -728,7 +734,7 @@ def c2_run(stream, steps=200, warmup=50, tune=True):
         cfg, _ = autotune.tune_simulation(sim, "f32", nodes)
         log(f"c2: autotuned launch {cfg}")
     ms_step, path = time_steps(sim, stream, steps, warmup)
-    lat_ms, bead_ms = kernel_pass(sim, steps)
+    lat_ms, bead_ms, _ = kernel_pass(sim, steps)
     flags, _ = sim.health()
     sim.close()
     eff = 18 * 4 * nodes / (lat_ms * 1e-3) / 1e9
@@ -842,19 +848,18 @@ def main():
            if path["graph_replays"] else "direct launches")
     if path["graph_replays"] and path["direct_steps"]:
         how += f" + {path['direct_steps']} direct steps"
-    if path["split_steps"]:
-        how += " (split steps)"
     log(f"{how}: {ms_step * 1e3:.1f} us/step, {mlups:.0f} MLUPS")
 
     # the same simulation, every lattice and bead launch stamped by its own dispatch (split
     # steps: the lattice pass from the earlier start to the later end of the fluid and
-    # fiber kernels, beside each other)
-    lat_ms, bead_ms = kernel_pass(sim, args.steps, flags=base_flags)
-    lattice = "fluid_kernel+fiber_kernel" if path["split_steps"] else "step_kernel"
+    # fiber kernels, beside each other; passes: their march, which takes four steps)
+    lat_ms, bead_ms, per_launch = kernel_pass(sim, args.steps, flags=base_flags)
+    lattice = ("march_kernel" if per_launch > 1 else
+               "fluid_kernel+fiber_kernel" if path["split_steps"] else "step_kernel")
     bytes_alg = 18 * BYTES_PER_VALUE[args.storage] * nodes
     achieved = bytes_alg / (lat_ms * 1e-3) / 1e9
-    log(f"lattice kernel {lat_ms * 1e3:.1f} us ({achieved:.0f} GB/s), bead kernel "
-        f"{bead_ms * 1e3:.1f} us")
+    log(f"{lattice} {lat_ms * 1e3:.1f} us for {per_launch} step(s) ({achieved:.0f} GB/s), bead "
+        f"kernel {bead_ms * 1e3:.1f} us")
     flags, strain = sim.health()
     sim.close()
 
@@ -871,7 +876,8 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                      "traffic": traffic, "kernel": lattice,
-                     "bytes_per_launch_alg": bytes_alg, "avg_launch_ms": round(lat_ms, 5)},
+                     "bytes_per_launch_alg": bytes_alg, "avg_launch_ms": round(lat_ms, 5),
+                     "steps_per_launch": per_launch},
         "bead_kernel_ms": round(bead_ms, 5),
         "copy_probe_gbps": round(copy_gbps, 1),
         "frac_of_copy_probe": round(achieved / copy_gbps, 4),

@@ -294,8 +294,9 @@ int fpd_set_launch(fpd_sim *s, const fpd_launch *cfg);
 int fpd_set_flags(fpd_sim *s, uint32_t flags);
 int fpd_get_launch(fpd_sim *s, fpd_launch *cfg);
 
-/* Whether fpd_step splits its steps as things stand (see fpd_step): *on = 1 or 0.  The
- * first step after fpd_init_fiber or fpd_load runs whole either way. */
+/* Whether fpd_step splits the steps that it takes outside passes, as things stand (see
+ * fpd_step): *on = 1 or 0.  The first such step after fpd_init_fiber or fpd_load runs whole
+ * either way. */
 int fpd_split_active(fpd_sim *s, int32_t *on);
 
 /* Kernel timing with FPD_FLAG_TIME_KERNELS: summed duration (ms) and count of the lattice
@@ -303,8 +304,9 @@ int fpd_split_active(fpd_sim *s, int32_t *on);
  * dispatches themselves: their events are stamped by the launch (hipExtLaunchKernel), not
  * recorded as separate queue entries around it.  A whole step's lattice pass is its fused
  * lattice kernel; a split step's (fpd_step) runs from the earlier start to the later end of
- * its fluid and fiber kernels, which run beside each other.  The first split step after
- * fpd_init_fiber or fpd_load runs whole and untimed. */
+ * its fluid and fiber kernels, which run beside each other; a pass's, one for its four steps,
+ * is the kernel of the nodes away from the fibers, and each of its steps counts a bead kernel.
+ * The first split step after fpd_init_fiber or fpd_load runs whole and untimed. */
 int fpd_kernel_times(fpd_sim *s, double *ms_lattice, int64_t *n_lattice, double *ms_bead,
                      int64_t *n_bead);
 int fpd_reset_kernel_times(fpd_sim *s);

@@ -1,6 +1,7 @@
 // fpd_internal.hpp -- structures shared by the host runtime and the kernels.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -247,6 +248,21 @@ struct PassArgs {
     int t;                     // step, 1 .. kPassSteps
 };
 
+template <class T>
+struct same_type {
+    using type = T;
+};
+
+// One launch of kernel k; with events, hipExtLaunchKernel stamps them with the dispatch's
+// own start and end, without extra packets in the queue around the kernel.
+template <typename... P>
+inline hipError_t launch_k(void (*k)(P...), dim3 grid, dim3 block, hipStream_t st,
+                           hipEvent_t t0, hipEvent_t t1, typename same_type<P>::type... args) {
+    void* argv[] = {(void*)&args...};
+    if (t0 || t1) return hipExtLaunchKernel((const void*)k, grid, block, argv, 0, st, t0, t1, 0);
+    return hipLaunchKernel((const void*)k, grid, block, argv, 0, st);
+}
+
 // Kernel launchers (fpd_kernels.hip).  Given events t0 and t1, the lattice and bead
 // launches stamp them with the dispatch's own start and end (hipExtLaunchKernel); they are
 // then not for stream capture.
@@ -266,9 +282,10 @@ hipError_t launch_forces(const StepArgs& a, hipStream_t st);
 hipError_t launch_pass_setup(const StepArgs& a, const PassArgs& q, hipStream_t st);
 hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st);
 hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, int win_out,
-                             hipStream_t st);
+                             hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 bool march_ok(int storage, const Lattice& L);
-hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st);
+hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st,
+                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 // Blocks of the patch kernel for a unit whose partition covers about `nodes` nodes.
 int patch_blocks(long long nodes, int tile_h);
 // The same for the simulations of a batch: march_kind and march_cols (columns of a march

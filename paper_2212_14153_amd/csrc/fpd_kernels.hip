@@ -1811,21 +1811,6 @@ __global__ void copy_kernel(const copy_vec* __restrict__ src, copy_vec* __restri
 
 // -------------------------------------------------------------------- launchers ----
 
-template <class T>
-struct same_type {
-    using type = T;
-};
-
-// One launch of kernel k; with events, hipExtLaunchKernel stamps them with the dispatch's
-// own start and end, without extra packets in the queue around the kernel.
-template <typename... P>
-static hipError_t launch_k(void (*k)(P...), dim3 grid, dim3 block, hipStream_t st,
-                           hipEvent_t t0, hipEvent_t t1, typename same_type<P>::type... args) {
-    void* argv[] = {(void*)&args...};
-    if (t0 || t1) return hipExtLaunchKernel((const void*)k, grid, block, argv, 0, st, t0, t1, 0);
-    return hipLaunchKernel((const void*)k, grid, block, argv, 0, st);
-}
-
 // Dynamic LDS (unused by the kernel) that leaves room for `blocks` resident blocks of it
 // per compute unit on the current device, not more: midway between the shares of `blocks`
 // and `blocks + 1` of the device's LDS per compute unit, so that the allocation granule
@@ -1984,7 +1969,7 @@ hipError_t launch_patch(int storage, const StepArgs& a, const PassArgs& q, hipSt
 }
 
 hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, int win_out,
-                             hipStream_t st) {
+                             hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
     if (a.fib.n <= 0) return hipSuccess;
     const bool sev = q.n_units > 1;
     void (*k)(StepArgs, PassArgs, int) = nullptr;
@@ -1997,7 +1982,7 @@ hipError_t launch_patch_bead(int storage, const StepArgs& a, const PassArgs& q, 
     }
     const int threads = storage == FPD_F64 ? kPatchBeadBlock<FPD_F64> : kPatchBeadBlock<FPD_F32>;
     const int plans = q.t == kPassSteps - 1 ? q.n_units : 0;
-    return launch_k(k, dim3(a.fib.n + plans), dim3(threads), st, nullptr, nullptr, a, q, win_out);
+    return launch_k(k, dim3(a.fib.n + plans), dim3(threads), st, t0, t1, a, q, win_out);
 }
 
 // Forces F^n, F/A and bond strains of every simulation of a batch, one block per

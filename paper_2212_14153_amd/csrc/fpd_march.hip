@@ -70,7 +70,8 @@ constexpr int kMarchManyUnits = 12;
 constexpr int kMarchMinRows = 16;
 
 template <int ST, int C, int OL>
-static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream_t st) {
+static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream_t st,
+                                 hipEvent_t t0, hipEvent_t t1) {
     const int strips = (a.L.nx + OL * C - 1) / (OL * C);
     const int waves = q.n_units >= kMarchManyUnits ? kMarchWavesMany : kMarchWaves;
     const int runs = std::max(1, std::min(waves / strips, a.L.ny / kMarchMinRows));
@@ -83,8 +84,7 @@ static hipError_t launch_march_t(const StepArgs& a, const PassArgs& q, hipStream
         k = force ? march_kernel<ST, C, OL, 1, true> : march_kernel<ST, C, OL, 1, false>;
     else
         k = force ? march_kernel<ST, C, OL, 0, true> : march_kernel<ST, C, OL, 0, false>;
-    hipLaunchKernelGGL(k, dim3((unsigned)strips * segs), dim3(64), 0, st, m);
-    return hipGetLastError();
+    return launch_k(k, dim3((unsigned)strips * segs), dim3(64), st, t0, t1, m);
 }
 
 bool march_ok(int storage, const Lattice& L) {
@@ -100,14 +100,15 @@ bool march_ok(int storage, const Lattice& L) {
 // to idle lanes than to the ends (240 bytes 56.7, 224 bytes 62.1).  Two columns of
 // float32 and of the two-byte formats, or one of float64, fit three waves per SIMD.
 // Four columns of float32 (320 registers, one wave per SIMD) took 67.0, four of float16 65.1.
-hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st) {
+hipError_t launch_march(int storage, const StepArgs& a, const PassArgs& q, hipStream_t st,
+                        hipEvent_t t0, hipEvent_t t1) {
     switch (storage) {
-        case FPD_F64: return launch_march_t<FPD_F64, 1, 56>(a, q, st);
+        case FPD_F64: return launch_march_t<FPD_F64, 1, 56>(a, q, st, t0, t1);
         case FPD_F32:
-            return a.L.nx % 2 == 0 ? launch_march_t<FPD_F32, 2, 56>(a, q, st)
-                                   : launch_march_t<FPD_F32, 1, 56>(a, q, st);
-        case FPD_F16DEV: return launch_march_t<FPD_F16DEV, 2, 60>(a, q, st);
-        case FPD_BF16DEV: return launch_march_t<FPD_BF16DEV, 2, 60>(a, q, st);
+            return a.L.nx % 2 == 0 ? launch_march_t<FPD_F32, 2, 56>(a, q, st, t0, t1)
+                                   : launch_march_t<FPD_F32, 1, 56>(a, q, st, t0, t1);
+        case FPD_F16DEV: return launch_march_t<FPD_F16DEV, 2, 60>(a, q, st, t0, t1);
+        case FPD_BF16DEV: return launch_march_t<FPD_BF16DEV, 2, 60>(a, q, st, t0, t1);
     }
     return hipErrorInvalidValue;
 }

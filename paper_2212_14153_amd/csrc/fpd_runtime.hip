@@ -382,15 +382,20 @@ PassArgs pass_args(const fpd_sim* s, int from, int t) {
 // overwrites the buffer that pass read, so it waits for that pass's last patch kernel
 // (ev_fiber; its fluid kernel is before it on the side stream); the first patch kernel
 // waits for the fluid kernel of the pass before (ev_fluid).  first: the start of a run,
-// whose stream is already after every earlier kernel.
-int enqueue_pass(fpd_sim* s, int from, int wpar, bool first) {
+// whose stream is already after every earlier kernel.  ev: events for the start and end of the
+// fluid kernel and of each step's bead kernel (kPassEvents).
+constexpr int kPassEvents = 2 + 2 * kPassSteps;
+
+int enqueue_pass(fpd_sim* s, int from, int wpar, bool first, hipEvent_t* ev = nullptr) {
     StepArgs a = make_args(s, from, wpar);
+    hipEvent_t none[kPassEvents] = {};
+    if (!ev) ev = none;
     if (a.fib.n <= 0) {
-        HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->stream));
+        HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->stream, ev[0], ev[1]));
         return FPD_OK;
     }
     HIP_TRY(hipStreamWaitEvent(s->side, s->ev_fiber, 0));
-    HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->side));
+    HIP_TRY(launch_march(s->p.storage, a, pass_args(s, from, 1), s->side, ev[0], ev[1]));
     if (!first) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
     HIP_TRY(hipEventRecord(s->ev_fluid, s->side));
     for (int t = 1; t <= kPassSteps; ++t) {
@@ -400,9 +405,27 @@ int enqueue_pass(fpd_sim* s, int from, int wpar, bool first) {
         if (has_ev(s)) HIP_TRY(launch_ev(a, s->stream));
         HIP_TRY(launch_patch(s->p.storage, a, q, s->stream));
         if (t == kPassSteps) HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
-        HIP_TRY(launch_patch_bead(s->p.storage, a, q, 1 - wpar, s->stream));
+        HIP_TRY(launch_patch_bead(s->p.storage, a, q, 1 - wpar, s->stream, ev[2 * t],
+                                  ev[2 * t + 1]));
         wpar = 1 - wpar;
     }
+    return FPD_OK;
+}
+
+// n passes (events: kPassEvents each, or nullptr), after which `stream` follows all of them.
+int enqueue_passes(fpd_sim* s, int from, int wpar, int64_t n, hipEvent_t* ev = nullptr) {
+    static_assert(kPassSteps % 2 == 0, "a pass keeps the window slot");
+    const bool fib = s->fiber && s->p.n_beads > 0;
+    if (fib) {
+        HIP_TRY(launch_pass_setup(make_args(s, from, wpar), pass_args(s, from, 1), s->stream));
+        HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
+    }
+    for (int64_t i = 0; i < n; ++i) {
+        int rc = enqueue_pass(s, from, wpar, i == 0, ev ? ev + i * kPassEvents : nullptr);
+        if (rc) return rc;
+        from = 1 - from;
+    }
+    if (fib) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
     return FPD_OK;
 }
 
@@ -410,19 +433,10 @@ int enqueue_pass(fpd_sim* s, int from, int wpar, bool first) {
 // passes while they last, then single steps.
 int enqueue_steps(fpd_sim* s, int from, int wpar, int64_t n) {
     if (use_passes(s) && n >= kPassSteps) {
-        const bool fib = s->fiber && s->p.n_beads > 0;
-        if (fib) {
-            HIP_TRY(launch_pass_setup(make_args(s, from, wpar), pass_args(s, from, 1),
-                                      s->stream));
-            HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
-        }
-        for (bool first = true; n >= kPassSteps; n -= kPassSteps, first = false) {
-            int rc = enqueue_pass(s, from, wpar, first);
-            if (rc) return rc;
-            from = 1 - from;
-            wpar ^= kPassSteps & 1;
-        }
-        if (fib) HIP_TRY(hipStreamWaitEvent(s->stream, s->ev_fluid, 0));
+        int rc = enqueue_passes(s, from, wpar, n / kPassSteps);
+        if (rc) return rc;
+        if (n / kPassSteps & 1) from = 1 - from;
+        n %= kPassSteps;
     }
     if (n > 0 && use_split(s)) return split_steps(s, from, wpar, n);
     for (; n > 0; --n) {
@@ -470,13 +484,59 @@ void flip(fpd_sim* s) {
     s->wpar = 1 - s->wpar;
 }
 
+int need_events(fpd_sim* s, size_t n) {
+    while (s->events.size() < n) {
+        hipEvent_t e;
+        HIP_TRY(hipEventCreate(&e));
+        s->events.push_back(e);
+    }
+    return FPD_OK;
+}
+
+// Passes launched one by one, the march and the bead kernels stamped as in step_timed.
+int passes_timed(fpd_sim* s, int64_t n) {
+    const bool fib = s->fiber && s->p.n_beads > 0;
+    int rc = ensure_split(s);
+    if (rc) return rc;
+    while (n > 0) {
+        const int64_t batch = n < 128 ? n : 128;
+        rc = need_events(s, (size_t)batch * kPassEvents);
+        if (rc) return rc;
+        rc = enqueue_passes(s, s->cur, s->wpar, batch, s->events.data());
+        if (rc) return rc;
+        if (batch & 1) s->cur = 1 - s->cur;
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        for (int64_t i = 0; i < batch; ++i) {
+            const hipEvent_t* ev = &s->events[(size_t)i * kPassEvents];
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, ev[0], ev[1]));
+            s->ms_lat += ms;
+            s->n_lat += 1;
+            for (int t = 1; fib && t <= kPassSteps; ++t) {
+                HIP_TRY(hipEventElapsedTime(&ms, ev[2 * t], ev[2 * t + 1]));
+                s->ms_bead += ms;
+                s->n_bead += 1;
+            }
+        }
+        n -= batch;
+    }
+    s->part_valid = true;
+    return FPD_OK;
+}
+
 // Steps launched one by one, the lattice and bead kernels each stamped with the start and
-// end of their own dispatch (durations summed into ms_lat and ms_bead).  Split steps (the
+// end of their own dispatch (durations summed into ms_lat and ms_bead), in passes where fpd_step
+// takes them.  Split steps (the
 // order of enqueue_split_step) stamp the fluid and the fiber kernel; their lattice pass
 // runs from the earlier start to the later end of the two.
 int step_timed(fpd_sim* s, int64_t n) {
     const bool fib = s->fiber && s->p.n_beads > 0;
     const bool split = use_split(s);
+    if (use_passes(s) && n >= kPassSteps) {
+        int rc = passes_timed(s, n / kPassSteps);
+        if (rc) return rc;
+        n %= kPassSteps;
+    }
     if (split) {
         int rc = ensure_split(s);
         if (rc) return rc;
@@ -493,12 +553,8 @@ int step_timed(fpd_sim* s, int64_t n) {
     const int rpt = s->launch.rows_per_thread;
     for (int64_t done = 0; done < n;) {
         const int64_t batch = n - done < 512 ? n - done : 512;
-        const size_t need = (size_t)batch * per;
-        while (s->events.size() < need) {
-            hipEvent_t e;
-            HIP_TRY(hipEventCreate(&e));
-            s->events.push_back(e);
-        }
+        int rc = need_events(s, (size_t)batch * per);
+        if (rc) return rc;
         if (split) HIP_TRY(hipEventRecord(s->ev_fiber, s->stream));
         for (int64_t i = 0; i < batch; ++i) {
             const StepArgs a = make_args(s, s->cur, s->wpar);
