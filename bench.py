@@ -658,14 +658,12 @@ def main_shapes(args):
 
 
 def choose_chunk(steps: int):
-    """Graph chunk for `steps` timed steps: the largest multiple of four <= 64 that divides steps,
-    else the largest even number (then every timed step runs in a replayed graph; a lattice
-    that takes passes of four rounds its chunks down to whole ones); for odd steps the largest even c <= 64 below
+    """Graph chunk for `steps` timed steps: the largest even c <= 64 that divides steps (then
+    every timed step runs in a replayed graph); for odd steps the largest even c <= 64 below
     steps (the last step then runs as direct launches); None below two steps."""
-    for m in (4, 2):
-        for c in range(min(64, steps), 1, -1):
-            if c % m == 0 and steps % c == 0:
-                return c
+    for c in range(min(64, steps), 1, -1):
+        if c % 2 == 0 and steps % c == 0:
+            return c
     c = min(64, steps - steps % 2)
     return c if c >= 2 else None
 
@@ -841,7 +839,13 @@ def main():
 
     # timed region: the production path (captured graphs replayed), whole step
     ms_step, path = time_steps(sim, stream, args.steps, args.warmup)
-    path["split_steps"] = sim.split_active()
+    # the same simulation, every lattice and bead launch stamped by its own dispatch (split
+    # steps: the lattice pass from the earlier start to the later end of the fluid and
+    # fiber kernels, beside each other; passes: their march, which takes four steps)
+    lat_ms, bead_ms, per_launch = kernel_pass(sim, args.steps, flags=base_flags)
+    if per_launch > 1 and path["graph_chunk"]:  # chunks are rounded down to whole passes
+        path = timed_path(args.steps, max(path["graph_chunk"] // 4 * 4, 2))
+    path["split_steps"] = sim.split_active()    # (of the steps that no pass takes)
     cfg = sim.get_launch()
     mlups = nodes / (ms_step * 1e-3) / 1e6
     how = (f"{path['graph_replays']} graph replays of {path['graph_chunk']} steps"
@@ -850,10 +854,6 @@ def main():
         how += f" + {path['direct_steps']} direct steps"
     log(f"{how}: {ms_step * 1e3:.1f} us/step, {mlups:.0f} MLUPS")
 
-    # the same simulation, every lattice and bead launch stamped by its own dispatch (split
-    # steps: the lattice pass from the earlier start to the later end of the fluid and
-    # fiber kernels, beside each other; passes: their march, which takes four steps)
-    lat_ms, bead_ms, per_launch = kernel_pass(sim, args.steps, flags=base_flags)
     lattice = ("march_kernel" if per_launch > 1 else
                "fluid_kernel+fiber_kernel" if path["split_steps"] else "step_kernel")
     bytes_alg = 18 * BYTES_PER_VALUE[args.storage] * nodes
