@@ -2,7 +2,9 @@
 
 Candidates are (block_x, block_y, rows_per_thread, xcd_remap) shapes.  Every candidate is
 timed on the real workload for a few steps, in several interleaved rounds (so clock and
-thermal drift hit all candidates alike), and the fastest minimum wins.  Results are cached
+thermal drift hit all candidates alike), and the fastest minimum wins.  A launch shape is one of whole
+and split steps: workloads large enough for passes of four steps, which do not use it, are timed
+in graphs of two steps, which hold none.  Results are cached
 in JSON keyed by GPU architecture, storage format and problem-size class; the cache lives
 at $FPD_AUTOTUNE_CACHE or ~/.cache/fpdlbm/autotune.json.
 """
@@ -16,6 +18,8 @@ import sys
 import tempfile
 import time
 
+# Nodes from which fpd_step (one simulation, a batch) may take passes.
+PASS_NODES_SIM, PASS_NODES_BATCH = 1 << 20, 3 << 18
 SHAPES = [(256, 1), (128, 2), (128, 1), (64, 4), (64, 2), (64, 1)]
 CANDIDATES = [dict(block_x=bx, block_y=by, rows_per_thread=spt, xcd_remap=xr)
               for (bx, by), spt, xr in itertools.product(SHAPES, (1, 2), (2, 1))]
@@ -95,8 +99,10 @@ def tune_simulation(sim, storage: str, nodes: int, steps: int = 40, rounds: int 
         os.close(fd)
         sim.save(ckpt)
 
+    single = dict(graph_chunk=2) if nodes >= PASS_NODES_SIM else {}
+
     def run(cfg):
-        sim.set_launch(cfg)
+        sim.set_launch(dict(cfg, **single))
         sim.step(2)
         sim.sync()
         t0 = time.perf_counter()
@@ -126,9 +132,10 @@ def tune_batch(make_batch, storage: str, nodes: int, steps: int = 16, rounds: in
         _log_cached(key, cache[key]["cfg"])
         return cache[key]["cfg"], None
     b = make_batch()
+    chunk = 2 if nodes >= PASS_NODES_BATCH else 8
     try:
         def run(cfg):
-            b.set_launch(dict(cfg, graph_chunk=8))
+            b.set_launch(dict(cfg, graph_chunk=chunk))
             b.run(8)
             t0 = time.perf_counter()
             b.run(steps)
