@@ -164,7 +164,9 @@ int fpd_create(const fpd_params *p, void *hip_stream, fpd_sim **out);
 /* As fpd_create (the problem of Sec. IV.A), but the two population buffers of the pull
  * scheme are caller-owned device memory of bytes_each >= fpd_population_bytes(p) bytes
  * each (e.g. torch tensors), 16-byte aligned (FPD_EINVAL otherwise); the library writes
- * the initial state into f_a and never frees them; they must outlive the simulation. */
+ * the initial state into f_a and never frees them; they must outlive the simulation.  Which
+ * of the two holds the state after fpd_step is not specified (a pass of four steps changes
+ * buffers once): read it through the calls below. */
 int fpd_create_with_buffers(const fpd_params *p, void *hip_stream, void *f_a, void *f_b,
                             size_t bytes_each, fpd_sim **out);
 
@@ -192,13 +194,14 @@ int fpd_init_fiber_line(fpd_sim *s, double cx, double cy, double theta);
  * even nx in the two-byte formats, not FPD_FLAG_NO_SPLIT) advances four steps per pass over
  * memory: the fluid away from the fibers in one kernel on that second stream, the nodes around
  * each fiber step by step in two buffers of their size.  These buffers belong to the simulation
- * besides its populations (about the nodes of a fiber's window each, not counted by
- * fpd_sim_footprint); without memory for them it takes split or whole steps.  The results are
- * the same bits, and steps left over by a multiple of four are split or whole ones.
+ * besides its populations (about the nodes of a fiber's window each); without memory for them
+ * it takes split or whole steps.  The results are the same bits, and steps left over by a
+ * multiple of four are split or whole ones.
  * The simulation's stream waits for the second stream before fpd_step returns, so work
  * enqueued on it afterwards follows every step.  The first step after fpd_init_fiber or
- * fpd_load runs whole.  FPD_HEALTH_SUPPORT is raised if a bead outran the split's margin
- * of three nodes (far beyond FPD_HEALTH_MACH). */
+ * fpd_load runs whole where it would be a split one (a pass finds its own partition).
+ * FPD_HEALTH_SUPPORT is raised if a bead outran the margin of three nodes that a split step or
+ * a pass leaves it (far beyond FPD_HEALTH_MACH); a pass takes such a bead's velocity as 0. */
 int fpd_step(fpd_sim *s, int64_t n_steps);
 
 /* Capture now, without running any step, the graph that fpd_step(s, n_steps) replays

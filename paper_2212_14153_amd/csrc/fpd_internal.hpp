@@ -208,14 +208,14 @@ struct PassSim {
 };
 
 // A batch step: per simulation two StepArgs (the step parities of a chunk), item tables
-// and counts {simulations, tiles, beads}; all in device memory, so a captured graph stays
+// and counts {simulations, tiles, beads, patch items, march items}; all in device memory, so a captured graph stays
 // valid while the tables are rewritten with the same counts (the grids are sized from the
 // counts at launch).
 struct BatchArgs {
     const StepArgs* args;       // [2 * n]
     const ItemRef* tile_items;  // [tiles]: simulation and tile of each lattice item
     const ItemRef* bead_items;  // [beads]: simulation and bead of each bead item
-    const int* counts;          // [3]
+    const int* counts;          // [5]
     int gpar;                   // parity of this step within the chunk
     // passes: `gpar` is then the buffer the pass starts from, wpar the window slot of its step
     // t, both relative to the chunk's start

@@ -10,11 +10,13 @@
 // one row per step on either side, which neighbouring waves recompute.  Intermediate rows are
 // kept in the storage format, so the result has the bits of NT single steps.
 //
-// What bounds it (8192 x 2048, measured): vector ALU issue (94 instructions per node and step
-// in float32, 113 in float64, 107 in float16, about 48 us per step at 4 cycles each with the
-// recomputed columns and rows) beside HBM (a quarter of a step's traffic with NT = 4, plus 25-60 %
-// of the reads for the overlaps).  Whole run with the 40-bead fiber, per step: float32
-// 195 -> 66 us, float64 385 -> 139, bfloat16 deviations 107 -> 60.
+// What bounds it, from counters at 8192 x 2048 (us of a march of four steps / its HBM bytes at
+// the 6.65 TB/s of a copy / its vector instructions at 4, in float64 4.5, cycles each on 1024 SIMDs):
+// float32 258 / 231 (1.54 GB) / 193, float64 527 / 451 (3.00 GB) / 256: HBM, which the overlapping
+// columns and rows make read 1.5 times; float16 249 / 128 (0.85 GB) / 206, bfloat16 244 / 128 /
+// 206: vector issue.  Instructions per node and step, recomputed ones included: 113 in
+// float32 (94 without), 133 (113) in float64, 121 in the two-byte formats.  Whole run with the
+// 40-bead fiber, per step: float32 195 -> 67 us, float64 385 -> 134, bfloat16 107 -> 60.
 #pragma once
 
 #include "fpd_device.hpp"

@@ -81,3 +81,24 @@ def test_binary16_passes_against_every_shape_of_whole_steps(g_body):
     got = alone(w, 0, (16,))
     for rows in (1, 2, 4):
         same(got, alone(w, _lib.FPD_FLAG_NO_SPLIT, (16,), rows_per_thread=rows))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev", "bf16dev"])
+def test_passes_of_the_smallest_lattices(storage):
+    """One to nine nodes a side, with and without walls, in a batch that takes passes: a wave's
+    columns go round the lattice many times, a row is its own neighbour."""
+    ws = [channel(nx, ny, storage, per, n_beads=0, f_ext=(0.0, 0.0))
+          for nx in ((1, 2, 3, 5, 8, 9) if storage in ("f64", "f32") else (2, 4, 6, 8))
+          for ny in (1, 2, 3, 4, 5, 9) for per in (0, 1)]
+    ws.append(channel(1024, 768, storage, n_beads=0))
+    print(f"[case] smallest lattices {storage}", flush=True)
+    out = []
+    for flags in (_lib.FPD_FLAG_NO_SPLIT, 0):
+        with _lib.Batch(1 << 33, len(ws), storage=storage) as b:
+            b.set_launch(dict(graph_chunk=8))
+            ids = [b.add(_lib.params_from_mapping(w.params(), storage=storage, flags=flags,
+                                                  g_body=(1e-5, -2e-5)), None, 1 << 20)
+                   for w in ws]
+            b.run(21)
+            out.append([b.populations(sid) for sid in ids])
+    same(*out)
