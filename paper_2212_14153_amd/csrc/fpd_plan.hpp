@@ -119,8 +119,8 @@ __host__ __device__ inline bool make_plan(const B& blk, const Lattice& L, double
         plan[2] = none ? 0 : (per ? imod(by, ny) : by);
         plan[3] = H;
     }
-    int tall = (int)ceil(2.0 * rc) + 4 + 2 * M;  // rows of a grown box, at most
-    if (per && tall > ny) tall = ny;
+    // rows of a grown box in the rectangle, at most
+    const int tall = (int)fmin(ceil(2.0 * rc) + 4 + 2 * M, (double)H);
     int* tiles = plan + plan_tiles_at(u.cap_h);
     for (int r0 = 0; r0 < H; r0 += kPlanRun) {
         const int run = H - r0 < kPlanRun ? H - r0 : kPlanRun, span = run + 2 * E;
@@ -134,7 +134,8 @@ __host__ __device__ inline bool make_plan(const B& blk, const Lattice& L, double
         for (int k = tid; k < u.n * tall; k += nt) {
             const int i = k / tall, j = k - i * tall;
             const int* o = sm.box[i];
-            if (o[1] < o[0] || j > o[3] - o[2] + 2 * M) continue;
+            const int top = o[2] - M - by, r = (ally || top > 0 ? top : 0) + j;
+            if (o[1] < o[0] || r > o[3] + M - by) continue;
             int c0 = o[0] - M - bx, c1 = o[1] + M + 1 - bx;
             if (allx) {
                 const int w = c1 - c0;
@@ -147,7 +148,6 @@ __host__ __device__ inline bool make_plan(const B& blk, const Lattice& L, double
                 c0 = 0;
                 c1 = nx;
             }
-            const int r = o[2] - M + j - by;
             for (int q = ally ? imod(r, ny) - ny : r; q < r0 + run + E; q += ny) {
                 if (q >= r0 - E && (ally || (q >= 0 && q < H))) {
                     blk.low(&sm.lo[q - r0 + E], c0);

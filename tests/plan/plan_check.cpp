@@ -1,6 +1,8 @@
 // The index arithmetic of a pass on the host: plans (make_plan) of random fibers on random lattices,
 // and every index that the patch and bead kernels form with them, against the sets of nodes that
 // they stand for.  Prints what was covered; the first fault ends the run with status 1.
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -136,9 +138,12 @@ struct Check {
         for (int i = 0; i < u.n; ++i) {
             if (!bead_sane(pos()[i][0], pos()[i][1])) continue;
             const BeadSpan s = bead_span(pos()[i][0], pos()[i][1], rc);
-            for (int y = s.y0 - kPassMargin; y <= s.y1 + kPassMargin; ++y) {
-                if (!per() && (y < 0 || y >= L.ny)) continue;
-                for (int x = s.x0 - kPassMargin; x <= s.x1 + kPassMargin; ++x)
+            const int ylo = per() ? s.y0 - kPassMargin : std::max(s.y0 - kPassMargin, 0);
+            const int yhi = std::min(s.y1 + kPassMargin, ylo + L.ny - 1);
+            const int xhi = std::min(s.x1 + kPassMargin, s.x0 - kPassMargin + L.nx - 1);
+            for (int y = ylo; y <= yhi; ++y) {
+                if (!per() && y >= L.ny) continue;
+                for (int x = s.x0 - kPassMargin; x <= xhi; ++x)
                     NEED(in(kPassSteps, imod(x, L.nx), per() ? imod(y, L.ny) : y),
                          "bead %d: node %d, %d not in the partition", i, x, y);
             }
@@ -211,6 +216,8 @@ int main(int argc, char** argv) {
         k.u.first = num(0, 3);
         k.u.tile_h = kPatchY << num(0, 1);
         k.rc = uni(1.0, 9.0);
+        if (k.L.nx * k.L.ny < 15000 && num(0, 7) == 0)  // (up to the lattice and far past it)
+            k.rc = std::exp(uni(2.0, 16.0));
         const bool tall = k.L.ny > 520 && num(0, 2) > 0;
         const double l0 = tall ? 1.02 * k.L.ny / k.u.n : uni(1.0, 12.0);
         plan_caps(k.u.n, l0, k.rc, k.L.nx, k.L.ny, k.u.cap_w, k.u.cap_h);
